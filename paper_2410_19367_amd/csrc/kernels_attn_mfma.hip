@@ -60,8 +60,9 @@ template <int D> __device__ __forceinline__ int tile_off(int row, int chunk) {
 
 // Direct global->LDS copy of a [64][D] tile by NW waves.  Which 16-byte chunk a lane fetches
 // depends only on its position, so the per-lane source offsets are computed once per kernel and a
-// step only adds the tile's base address (the sequence length is a multiple of 64: every tile
-// lies inside its tensor).  dr is the real row width; with PAD, chunks beyond it come from zeros.
+// step only adds the tile's base address.  dr is the real row width; with PAD, chunks beyond it come
+// from zeros.  A tile that reaches past the last row of its sequence is requested with issue_rows,
+// which takes the rows beyond the valid ones from the same zeros.
 template <int D, int NW, bool PAD>
 struct TilePlan {
     static constexpr int CPR = D / 8;              // chunks per row
@@ -70,11 +71,13 @@ struct TilePlan {
                                                    // of 16, the period of the swizzle, so the column stays
     int off0;                                      // element offset of the first chunk; < 0: padded column
     int ld;                                        // row pitch in elements (wave-uniform)
+    int row0;                                      // row of the first chunk
     __device__ __forceinline__ void init(int wave, int lane, int ld_, int dr) {
         const int P = wave * 64 + lane;
         const int row = P / CPR;
         const int c = (P % CPR) ^ swz<D>(row);
         ld = ld_;
+        row0 = row;
         off0 = (!PAD || c * 8 < dr) ? row * ld + c * 8 : -1;
     }
     // gbase points at (row 0, col 0) of the tile
@@ -83,6 +86,17 @@ struct TilePlan {
         for (int i = 0; i < NI; ++i) {
             const bf16_t* src = (!PAD || off0 >= 0) ? gbase + (size_t)i * ROWSTEP * ld + off0
                                                     : (const bf16_t*)g_zero_chunk;
+            __builtin_amdgcn_global_load_lds(
+                (const void __attribute__((address_space(1)))*)src,
+                (void __attribute__((address_space(3)))*)(lds + (wave + NW * i) * 1024), 16, 0, 0);
+        }
+    }
+    // the same with only the first `rows` rows of the tile inside the tensor
+    __device__ __forceinline__ void issue_rows(const bf16_t* gbase, char* lds, int wave, int rows) const {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const bool ok = (!PAD || off0 >= 0) && row0 + i * ROWSTEP < rows;
+            const bf16_t* src = ok ? gbase + (size_t)i * ROWSTEP * ld + off0 : (const bf16_t*)g_zero_chunk;
             __builtin_amdgcn_global_load_lds(
                 (const void __attribute__((address_space(1)))*)src,
                 (void __attribute__((address_space(3)))*)(lds + (wave + NW * i) * 1024), 16, 0, 0);
@@ -153,7 +167,12 @@ __device__ __forceinline__ void block_coords(int nblk, int heads, bool causal, b
 // causal block then needs half as many steps, and because blocks are dealt out heaviest first
 // as CUs become free the tail of the launch stays short.
 // =====================================================================================
-template <int D, int DR, int NT>
+// RAG: the sequence length is not a multiple of 64.  The last query block and the last key tile are
+// then partly filled: tile rows past the end are zeros, keys past the end are masked like padded
+// ones, queries past the end repeat the last one and are not stored.  (The guards cost a branch per
+// tile, so multiples of 64 keep kernels without them.  Before, such lengths went to the kernels of
+// one row per block: 8 micro-batches of 2 layers with H = 1600, S = 1000, B = 1: 46.7 ms, now 16.0 ms.)
+template <int D, int DR, int NT, bool RAG>
 __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kernel(AttnArgs a, float scale) {
     constexpr int NW = 4 * NT, NSUB = 2 * NT, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = NT * 2 * TILE;   // per tile: K then V
@@ -165,7 +184,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     const int tj = sub >> 1, kh = sub & 1;
     const int h = lane >> 5;
     int qblk, head, b;
-    block_coords(a.S / 64, a.heads, a.causal != 0, true, NT == 1, qblk, head, b);
+    block_coords((a.S + 63) / 64, a.heads, a.causal != 0, true, NT == 1, qblk, head, b);
     // real head dimension: the tile width (no padding, every guard below folds away), a fixed narrower
     // width (the guards fold to constants), or with DR = 0 whatever the call says
     constexpr bool PAD = DR != D;
@@ -177,7 +196,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     const int q_wave = qblk * 64 + qg * 32;
     const int q_lane = q_wave + (lane & 31);
     const int klen = a.causal ? a.S : (a.lens ? a.lens[b] : a.S);
-    const int kend = a.causal ? qblk * 64 + 64 : klen;     // keys [0, kend) matter to this block
+    const int kend = a.causal ? (RAG ? min(qblk * 64 + 64, a.S) : qblk * 64 + 64) : klen;   // keys [0, kend) matter to this block
     const int nt = (kend + 63) / 64;                        // tiles
     const int nsteps = (nt + NT - 1) / NT;
     const float c = scale * kLog2e;
@@ -185,7 +204,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     bf16x8 qf[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s)
-        qf[s] = load_frag(qkv + (size_t)q_lane * ld, 16 * s + 8 * h, dr);
+        qf[s] = load_frag(qkv + (size_t)(RAG ? min(q_lane, a.S - 1) : q_lane) * ld, 16 * s + 8 * h, dr);
 
     f32x16 ot[DT];
 #pragma unroll
@@ -201,6 +220,11 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
         for (int j = 0; j < NT; ++j) {
             const int k0 = (step * NT + j) * 64;
             if (step * NT + j < nt) {
+                if (RAG && k0 + 64 > a.S) {
+                    plan.issue_rows(kbase + (size_t)k0 * ld, st + j * 2 * TILE, wave, a.S - k0);
+                    plan.issue_rows(vbase + (size_t)k0 * ld, st + j * 2 * TILE + TILE, wave, a.S - k0);
+                    continue;
+                }
                 plan.issue(kbase + (size_t)k0 * ld, st + j * 2 * TILE, wave);
                 plan.issue(vbase + (size_t)k0 * ld, st + j * 2 * TILE + TILE, wave);
             }
@@ -309,6 +333,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
 #pragma unroll
             for (int v = 0; v < 16; ++v) ot[t2][v] += other[(t2 * 16 + v) * 64 + lane] * aj;
     }
+    if (RAG && q_lane >= a.S) return;
     const float inv = 1.f / l;
     bf16_t* out = (bf16_t*)a.ctx + ((size_t)b * a.S + q_lane) * H + head * dr;
 #pragma unroll
@@ -329,7 +354,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
 //   dQ^T (D x 32) += K^T dS^T         (K tile read plainly for S^T and transposed for dQ^T)
 // The two halves' partial dQ^T are added through LDS at the end.
 // =====================================================================================
-template <int D, int DR>
+template <int D, int DR, bool RAG>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, float scale) {
     constexpr int NW = 4, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE;
@@ -340,7 +365,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
     const int qg = wave >> 1, kh = wave & 1;
     const int h = lane >> 5;
     int qblk, head, b;
-    block_coords(a.S / 64, a.heads, a.causal != 0, true, true, qblk, head, b);
+    block_coords((a.S + 63) / 64, a.heads, a.causal != 0, true, true, qblk, head, b);
     // real head dimension: the tile width (no padding, every guard below folds away), a fixed narrower
     // width (the guards fold to constants), or with DR = 0 whatever the call says
     constexpr bool PAD = DR != D;
@@ -352,24 +377,25 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
     const int q_wave = qblk * 64 + qg * 32;
     const int q_lane = q_wave + (lane & 31);
     const int klen = a.causal ? a.S : (a.lens ? a.lens[b] : a.S);
-    const int kend = a.causal ? qblk * 64 + 64 : klen;
+    const int kend = a.causal ? (RAG ? min(qblk * 64 + 64, a.S) : qblk * 64 + 64) : klen;
     const int nt = (kend + 63) / 64;
     const float c = scale * kLog2e;
 
-    const bf16_t* dob = (const bf16_t*)a.dctx + ((size_t)b * a.S + q_lane) * H + head * dr;
+    const int q_src = RAG ? min(q_lane, a.S - 1) : q_lane;     // row this lane reads
+    const bf16_t* dob = (const bf16_t*)a.dctx + ((size_t)b * a.S + q_src) * H + head * dr;
     bf16x8 qf[KS], dof[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-        qf[s] = load_frag(qkv + (size_t)q_lane * ld, 16 * s + 8 * h, dr);
+        qf[s] = load_frag(qkv + (size_t)q_src * ld, 16 * s + 8 * h, dr);
         dof[s] = load_frag(dob, 16 * s + 8 * h, dr);
     }
-    const size_t li = ((size_t)b * a.heads + head) * a.S + q_lane;
+    const size_t li = ((size_t)b * a.heads + head) * a.S + q_src;
     const float lse2 = a.lse[li] * kLog2e;
     // delta[q] = sum_d dO[q][d] O[q][d]: each lane holds half of its query's dO row already; the
     // value is also left in a.delta for the dK/dV kernel, which runs after this one
     float delta = 0.f;
     {
-        const bf16_t* ob = (const bf16_t*)a.ctx + ((size_t)b * a.S + q_lane) * H + head * dr;
+        const bf16_t* ob = (const bf16_t*)a.ctx + ((size_t)b * a.S + q_src) * H + head * dr;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const bf16x8 of = load_frag(ob, 16 * s + 8 * h, dr);
@@ -377,7 +403,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
             for (int e = 0; e < 8; ++e) delta += (float)of[e] * (float)dof[s][e];
         }
         delta = halves_sum(delta);
-        if (kh == 0 && h == 0) a.delta[li] = delta;
+        if (kh == 0 && h == 0 && (!RAG || q_lane < a.S)) a.delta[li] = delta;
     }
 
     f32x16 dq[DT];
@@ -388,18 +414,22 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
 
     TilePlan<D, NW, PAD> plan;
     plan.init(wave, lane, ld, dr);
-    plan.issue(kbase, smem, wave);
-    plan.issue(vbase, smem + TILE, wave);
+    auto request = [&](int k0, char* st) {
+        if (RAG && k0 + 64 > a.S) {
+            plan.issue_rows(kbase + (size_t)k0 * ld, st, wave, a.S - k0);
+            plan.issue_rows(vbase + (size_t)k0 * ld, st + TILE, wave, a.S - k0);
+            return;
+        }
+        plan.issue(kbase + (size_t)k0 * ld, st, wave);
+        plan.issue(vbase + (size_t)k0 * ld, st + TILE, wave);
+    };
+    request(0, smem);
 
     for (int t = 0; t < nt; ++t) {
         const int k0 = t * 64;
         BP_WAIT_VMCNT(0);
         __syncthreads();
-        if (t + 1 < nt) {
-            char* st = smem + ((t + 1) & 1) * STAGE;
-            plan.issue(kbase + (size_t)(k0 + 64) * ld, st, wave);
-            plan.issue(vbase + (size_t)(k0 + 64) * ld, st + TILE, wave);
-        }
+        if (t + 1 < nt) request(k0 + 64, smem + ((t + 1) & 1) * STAGE);
         const int kw = k0 + 32 * kh;
         if ((a.causal && kw > q_wave + 31) || kw >= klen) continue;
         const char* sk = smem + (t & 1) * STAGE;
@@ -442,7 +472,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
             for (int v = 0; v < 16; ++v) xo[(t2 * 16 + v) * 64 + lane] = dq[t2][v];
     }
     __syncthreads();
-    if (kh == 1) return;
+    if (kh == 1 || (RAG && q_lane >= a.S)) return;
     bf16_t* out = (bf16_t*)a.dqkv + ((size_t)b * a.S + q_lane) * ld + head * dr;
 #pragma unroll
     for (int t2 = 0; t2 < DT; ++t2)
@@ -466,7 +496,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
 //   dV^T (D x 32 keys) += dO^T P,   dK^T (D x 32 keys) += Q^T dS
 // The two query halves' partial sums are added through LDS at the end.
 // =====================================================================================
-template <int D, int DR>
+template <int D, int DR, bool RAG>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, float scale) {
     constexpr int NW = 4, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE + 512;   // Q, dO, then lse[64], delta[64]
@@ -477,7 +507,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
     const int kg = wave >> 1, qh = wave & 1;
     const int h = lane >> 5;
     int kblk, head, b;
-    block_coords(a.S / 64, a.heads, a.causal != 0, false, true, kblk, head, b);   // key block 0 is the heaviest
+    block_coords((a.S + 63) / 64, a.heads, a.causal != 0, false, true, kblk, head, b);   // key block 0 is the heaviest
     // real head dimension: the tile width (no padding, every guard below folds away), a fixed narrower
     // width (the guards fold to constants), or with DR = 0 whatever the call says
     constexpr bool PAD = DR != D;
@@ -491,7 +521,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
     bf16_t* dk_out = (bf16_t*)a.dqkv + ((size_t)b * a.S + k_lane) * ld + H + head * dr;
     bf16_t* dv_out = dk_out + H;
     if (kblk * 64 >= klen) {      // the whole block of keys is padding: no query attends it
-        if (qh == 0) {
+        if (qh == 0 && (!RAG || k_lane < a.S)) {
             const uint2 z = make_uint2(0u, 0u);
 #pragma unroll
             for (int t2 = 0; t2 < DT; ++t2)
@@ -508,11 +538,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
     const float* lse = a.lse + ((size_t)b * a.heads + head) * a.S;
     const float* dlt = a.delta + ((size_t)b * a.heads + head) * a.S;
 
+    const int k_src = RAG ? min(k_lane, a.S - 1) : k_lane;     // row this lane reads
     bf16x8 kf[KS], vf[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-        kf[s] = load_frag(qkv + H + (size_t)k_lane * ld, 16 * s + 8 * h, dr);
-        vf[s] = load_frag(qkv + 2 * H + (size_t)k_lane * ld, 16 * s + 8 * h, dr);
+        kf[s] = load_frag(qkv + H + (size_t)k_src * ld, 16 * s + 8 * h, dr);
+        vf[s] = load_frag(qkv + 2 * H + (size_t)k_src * ld, 16 * s + 8 * h, dr);
     }
     f32x16 dk[DT], dv[DT];
 #pragma unroll
@@ -522,23 +553,30 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
 
     const bool pad_in_block = kblk * 64 + 64 > klen;   // some of this block's keys are padding
     const int t0 = a.causal ? kblk : 0;        // first 64-query tile that can see this block's keys
-    const int nt = a.S / 64;
+    const int nt = (a.S + 63) / 64;
 
     TilePlan<D, NW, PAD> plan_q, plan_do;
     plan_q.init(wave, lane, ld, dr);
     plan_do.init(wave, lane, H, dr);
     auto load_stage = [&](int t, char* st) {
         const int q0 = t * 64;
-        plan_q.issue(qkv + (size_t)q0 * ld, st, wave);
-        plan_do.issue(dobase + (size_t)q0 * H, st + TILE, wave);
+        int q_stat = q0 + lane;                     // row whose statistics this lane fetches
+        if (RAG && q0 + 64 > a.S) {
+            plan_q.issue_rows(qkv + (size_t)q0 * ld, st, wave, a.S - q0);
+            plan_do.issue_rows(dobase + (size_t)q0 * H, st + TILE, wave, a.S - q0);
+            q_stat = min(q_stat, a.S - 1);
+        } else {
+            plan_q.issue(qkv + (size_t)q0 * ld, st, wave);
+            plan_do.issue(dobase + (size_t)q0 * H, st + TILE, wave);
+        }
         // the tile's 64 log-sum-exp values and 64 deltas travel the same way (4 bytes per lane): a load
         // into registers followed by an LDS store would make these waves wait for the tile loads
         // issued just before it, i.e. for the whole memory latency, in every step
         if (wave == 0)
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(lse + q0 + lane),
+            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(lse + q_stat),
                                              (void __attribute__((address_space(3)))*)(st + 2 * TILE), 4, 0, 0);
         else if (wave == 1)
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(dlt + q0 + lane),
+            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(dlt + q_stat),
                                              (void __attribute__((address_space(3)))*)(st + 2 * TILE + 256), 4, 0, 0);
     };
     load_stage(t0, smem + (t0 & 1) * STAGE);
@@ -570,6 +608,11 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 if (k_lane > qw + acc_row(v, h)) sacc[v] = -INFINITY;
+        }
+        if (RAG && q0 + 64 > a.S) {                      // queries past the end: p = 0
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (qw + acc_row(v, h) >= a.S) sacc[v] = -INFINITY;
         }
         if (pad_in_block && k_lane >= klen) {
 #pragma unroll
@@ -608,7 +651,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             }
     }
     __syncthreads();
-    if (qh == 1) return;
+    if (qh == 1 || (RAG && k_lane >= a.S)) return;
 #pragma unroll
     for (int t2 = 0; t2 < DT; ++t2)
 #pragma unroll
@@ -634,7 +677,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
 bool attn_mfma_supported(const AttnArgs& a) {
     auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
     if (a.d % 8 || a.d < 8 || a.d > 128) return false;      // tile width 64 or 128, narrower heads are padded
-    if (a.S % 64) return false;
+    if (a.S < 1) return false;
     return al16(a.qkv) && al16(a.ctx) && (!a.dctx || al16(a.dctx)) && (!a.dqkv || al16(a.dqkv));
 }
 
@@ -657,29 +700,31 @@ static int tiles_per_step(const AttnArgs& a) {
             n_cu = 256;
         n_cu_cached.store(n_cu, std::memory_order_relaxed);
     }
-    const long blocks = (long)(a.S / 64) * a.heads * a.B;
+    const long blocks = (long)((a.S + 63) / 64) * a.heads * a.B;
     return (a.S >= 512 && blocks <= 2L * n_cu) ? 2 : 1;
 }
 
-template <int D, int DR, int NT>
+template <int D, int DR, int NT, bool RAG>
 static hipError_t launch_fwd_nt(const AttnArgs& a, hipStream_t s) {
     const float scale = 1.f / sqrtf((float)a.d);
-    const dim3 grid((a.S / 64) * a.heads * a.B), block(256 * NT);
+    const dim3 grid(((a.S + 63) / 64) * a.heads * a.B), block(256 * NT);
     const size_t stages = (size_t)2 * NT * 2 * 64 * D * 2;
     const size_t merge = (size_t)2 * (2 * NT - 1) * ((D / 32) * 16 * 64 + 128) * sizeof(float);
     const size_t smem = stages > merge ? stages : merge;
     static std::atomic<bool> set{false};   // several host threads may launch at once
     if (!set.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_fwd_mfma_kernel<D, DR, NT>, smem);
+        hipError_t e = set_smem(attn_fwd_mfma_kernel<D, DR, NT, RAG>, smem);
         if (e != hipSuccess) return e;
         set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, DR, NT>), grid, block, smem, s, a, scale);
+    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, DR, NT, RAG>), grid, block, smem, s, a, scale);
     return hipGetLastError();
 }
 template <int D, int DR>
 static hipError_t launch_fwd_t(const AttnArgs& a, hipStream_t s) {
-    return tiles_per_step(a) == 2 ? launch_fwd_nt<D, DR, 2>(a, s) : launch_fwd_nt<D, DR, 1>(a, s);
+    if (a.S % 64)
+        return tiles_per_step(a) == 2 ? launch_fwd_nt<D, DR, 2, true>(a, s) : launch_fwd_nt<D, DR, 1, true>(a, s);
+    return tiles_per_step(a) == 2 ? launch_fwd_nt<D, DR, 2, false>(a, s) : launch_fwd_nt<D, DR, 1, false>(a, s);
 }
 
 hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) {
@@ -691,21 +736,26 @@ hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) {
     return a.d > 64 ? launch_fwd_t<128, 0>(a, s) : launch_fwd_t<64, 0>(a, s);
 }
 
-template <int D, int DR>
-static hipError_t launch_bwd_t(const AttnArgs& a, hipStream_t s) {
+template <int D, int DR, bool RAG>
+static hipError_t launch_bwd_rag(const AttnArgs& a, hipStream_t s) {
     const float scale = 1.f / sqrtf((float)a.d);
-    const dim3 grid((a.S / 64) * a.heads * a.B), block(256);
+    const dim3 grid(((a.S + 63) / 64) * a.heads * a.B), block(256);
     const size_t smem = 2 * 2 * 64 * D * 2, smem2 = 2 * (2 * 64 * D * 2 + 512);
     static std::atomic<bool> set{false};   // several host threads may launch at once
     if (!set.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_bwd_dq_mfma_kernel<D, DR>, smem);
-        if (e == hipSuccess) e = set_smem(attn_bwd_dkv_mfma_kernel<D, DR>, smem2);
+        hipError_t e = set_smem(attn_bwd_dq_mfma_kernel<D, DR, RAG>, smem);
+        if (e == hipSuccess) e = set_smem(attn_bwd_dkv_mfma_kernel<D, DR, RAG>, smem2);
         if (e != hipSuccess) return e;
         set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<D, DR>), grid, block, smem, s, a, scale);
-    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<D, DR>), grid, block, smem2, s, a, scale);
+    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<D, DR, RAG>), grid, block, smem, s, a, scale);
+    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<D, DR, RAG>), grid, block, smem2, s, a, scale);
     return hipGetLastError();
+}
+
+template <int D, int DR>
+static hipError_t launch_bwd_t(const AttnArgs& a, hipStream_t s) {
+    return a.S % 64 ? launch_bwd_rag<D, DR, true>(a, s) : launch_bwd_rag<D, DR, false>(a, s);
 }
 
 hipError_t launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t s) {

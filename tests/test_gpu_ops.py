@@ -212,6 +212,16 @@ def test_attention_fwd_bwd(B, S, heads, d, causal, lens, dtype):
         assert err <= (2e-2 if dtype == "bf16" else 5e-5), (name, err)
 
 
+# Sequence lengths around the 64-row tiles and the 32-row halves, one and two tiles per forward step
+@pytest.mark.parametrize("B,S,heads,d,causal,lens", [
+    (2, 1, 2, 64, True, None), (2, 31, 2, 64, True, None), (1, 33, 3, 128, True, None), (2, 63, 2, 40, True, None),
+    (3, 65, 2, 64, False, [65, 1, 64]), (1, 97, 2, 96, False, [33]), (2, 127, 2, 128, True, None),
+    (1, 513, 2, 64, True, None), (1, 545, 2, 128, False, [544]), (1, 1000, 1, 64, True, None), (2, 333, 2, 64, False, [100, 333]),
+])
+def test_attention_ragged_lengths(B, S, heads, d, causal, lens):
+    test_attention_fwd_bwd(B, S, heads, d, causal, lens, "bf16")
+
+
 @pytest.mark.parametrize("B,S,heads,d,causal", [(1, 512, 2, 128, True), (2, 256, 2, 64, False), (1, 1024, 1, 128, True)])
 def test_attention_wide_score_range(B, S, heads, d, causal):
     """Scores whose magnitude grows along the key axis (std up to ~16, maxima tens of binary orders
