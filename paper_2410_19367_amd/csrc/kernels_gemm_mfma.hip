@@ -12,9 +12,10 @@
 //     [k][rows] and read back with the LDS transpose read ds_read_b64_tr_b16, which hands each
 //     lane four consecutive k of one row.
 // Both layouts XOR-swizzle the chunk index so fragment reads spread over all LDS banks.
-// Two kernels: gemm_mfma_kernel stages slices through registers with predication (ragged shapes);
-// gemm_dma_kernel (further down) loads them straight into LDS and carries the fused epilogues,
-// split-K and multi-segment contractions.  Slices land in LDS while earlier ones feed the MFMAs,
+// Two kernels: gemm_mfma_kernel stages slices through registers with predication and stores element by
+// element (outputs whose rows are no multiple of 8 elements or not 16-byte aligned); gemm_dma_kernel
+// (further down) loads slices straight into LDS, for any shape with 16-byte rows, and carries the
+// fused epilogues, split-K and multi-segment contractions.  Slices land in LDS while earlier ones feed the MFMAs,
 // one barrier per slice: two LDS stages in gemm_mfma_kernel and in the large tiles of
 // gemm_dma_kernel, three in its 128 x 128 forward / data-gradient form, a ring of five half-slices
 // in its weight-gradient form.
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_kernel(GemmArgs g, int 
 }
 
 // =====================================================================================
-// Second kernel: aligned shapes.  Slices go global -> LDS directly (global_load_lds, 16 bytes per
+// Second kernel.  Slices go global -> LDS directly (global_load_lds, 16 bytes per
 // lane, one wave instruction fills 1 KiB of consecutive LDS), so no registers or ds_write issue
 // slots are spent on staging; NS LDS stages let the loads run NS-1 slices ahead of the MFMAs.
 // Because the hardware fixes the LDS position of each lane's 16 bytes, the swizzled layouts
@@ -259,9 +260,10 @@ template <int BKT> __device__ __forceinline__ int kmaj_off(int row, int c) {
 // The global address is a buffer descriptor (wave-uniform tile origin) plus a per-lane 32-bit byte
 // offset plus a wave-uniform byte offset (the K slice), so issuing a load costs no vector ALU work.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
-__device__ __forceinline__ rsrc_t make_rsrc(const void* base) {
-    // raw buffer, stride 0, no bounds clamp below 4 GiB - 1; dword 3 as for untyped 32-bit data on gfx9
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)0xffffffffu, 0x00020000);
+__device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes = 0xffffffffu) {
+    // raw buffer, stride 0, loads at or beyond `bytes` give zeros (default: no bounds clamp below
+    // 4 GiB - 1); dword 3 as for untyped 32-bit data on gfx9
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 __device__ __forceinline__ void dma16(rsrc_t rsrc, uint32_t lane_off, uint32_t slice_off, char* lds_wave_base) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (void __attribute__((address_space(3)))*)lds_wave_base, 16,
@@ -271,12 +273,30 @@ __device__ __forceinline__ void dma16(rsrc_t rsrc, uint32_t lane_off, uint32_t s
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
 #define BP_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
 
+constexpr uint32_t kOutside = 0xffffff00u;          // beyond the size of every ragged operand's descriptor
+
 // Per-lane byte offsets (relative to the slice base) of the chunks this lane fetches: 32 bits, so
 // that the load takes the wave-uniform slice base from scalar registers plus this one vector register.
 template <int R, int BKT, int NW, bool RMAJOR>
 struct DmaPlan {
     static constexpr int NI = R * BKT / 512 / NW;   // wave instructions per wave per slice
     uint32_t boff[NI];                              // byte offset from the slice base
+    uint32_t tail[NI];                              // the same in a slice that is cut short (init_tail)
+    // k-major operand whose K is no multiple of BKT: in the last slice the chunks at and beyond k_valid
+    // would read the next row; they get an offset that lies outside every buffer instead (zeros)
+    __device__ __forceinline__ void init_tail(int wave, int lane, int k_valid) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int P = (wave + NW * i) * 64 + lane;
+            const int row = P / (BKT / 8), c = (P % (BKT / 8)) ^ kmaj_swz<BKT>(row);
+            tail[i] = c * 8 < k_valid ? boff[i] : kOutside;
+        }
+    }
+    __device__ __forceinline__ void issue_rag(rsrc_t tile, bool last, char* lds_tile, int wave) const {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            dma16(tile, !RMAJOR && last ? tail[i] : boff[i], 0, lds_tile + (wave + NW * i) * 1024);
+    }
     __device__ __forceinline__ void init(int wave, int lane, int ld) {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
@@ -392,7 +412,16 @@ struct SchedRounds {
     }
 };
 
-template <int BM, int BN, int WM, int WN, int BKT, int NS, bool A_RMAJOR, bool B_RMAJOR, bool MI16 = false, bool RING = false>
+// RAG: shapes that are no multiples of the tile.  The descriptor of an operand then starts at the next
+// slice to request and ends with the operand, so that rows (k-major) or k (r-major) past the end
+// arrive as zeros; it moves on from slice to slice with three scalar additions.  A k-major operand's
+// last slice is cut by the per-lane offsets (DmaPlan::init_tail); the columns past the end of an
+// r-major operand hold the next k-row's elements and only reach outputs that are not stored.
+// Measured against the register-staged kernel with separate GELU kernels, the only one for such
+// shapes before: 1000 x 1600..6400 products 170 -> 41 us on average; weight gradients over 1998 tokens
+// (fp32 generic kernel before, one launch per micro-batch) 546 us each -> 153 us for a group of eight.
+template <int BM, int BN, int WM, int WN, int BKT, int NS, bool A_RMAJOR, bool B_RMAJOR, bool MI16 = false,
+          bool RING = false, bool RAG = false>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int tiles_m, int tiles_n, int splits,
                                                                int n_full) {
     constexpr int NW = WM * WN;
@@ -420,7 +449,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     // The contraction runs over g.nseg operand pairs of g.K each; this block owns steps
     // [k_first, k_first + nk) of the concatenation.  (seg, kl) is the position of the next slice
     // to request.
-    const int nk_seg = g.K / BKT;
+    const int nk_seg = RAG ? (g.K + BKT - 1) / BKT : g.K / BKT;
     const int nk_all = nk_seg * g.nseg;
     // K slices of a split tile differ by at most one step: the first nk_all % splits get one more
     const int nk = nk_all / eff_splits + (sp < nk_all % eff_splits ? 1 : 0);
@@ -428,18 +457,39 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     // byte step of one K slice inside a segment
     const uint32_t a_step = 2u * (uint32_t)(A_RMAJOR ? BKT * g.lda : BKT);
     const uint32_t b_step = 2u * (uint32_t)(B_RMAJOR ? BKT * g.ldb : BKT);
-    auto a_origin = [&](int sgm) {
+    auto a_base = [&](int sgm) {
         const bf16_t* A = (const bf16_t*)(sgm == 0 ? g.A : g.A_more[sgm - 1]);
-        return make_rsrc(A_RMAJOR ? A + m0 : A + (size_t)m0 * g.lda);
+        return A_RMAJOR ? A + m0 : A + (size_t)m0 * g.lda;
     };
-    auto b_origin = [&](int sgm) {
+    auto b_base = [&](int sgm) {
         const bf16_t* Bp = (const bf16_t*)(sgm == 0 ? g.B : g.B_more[sgm - 1]);
-        return make_rsrc(B_RMAJOR ? Bp + n0 : Bp + (size_t)n0 * g.ldb);
+        return B_RMAJOR ? Bp + n0 : Bp + (size_t)n0 * g.ldb;
     };
+    auto a_origin = [&](int sgm) { return make_rsrc(a_base(sgm)); };
+    auto b_origin = [&](int sgm) { return make_rsrc(b_base(sgm)); };
     // the next slice to request: segment, slice inside it, tile origins of that segment, byte offsets
     int seg = k_first / nk_seg, kl = k_first % nk_seg;
     rsrc_t a_tile = a_origin(seg), b_tile = b_origin(seg);
     uint32_t a_off = kl * a_step, b_off = kl * b_step;
+    // RAG: address of the next slice, bytes from there to the operand's end
+    const char *a_at = nullptr, *b_at = nullptr;
+    long a_left = 0, b_left = 0;
+    auto rag_origin = [&](int sgm, uint32_t a_skip, uint32_t b_skip) {
+        const long a_rows = A_RMAJOR ? g.K : g.M - m0, a_cols = A_RMAJOR ? g.M - m0 : g.K;
+        const long b_rows = B_RMAJOR ? g.K : g.N - n0, b_cols = B_RMAJOR ? g.N - n0 : g.K;
+        a_at = (const char*)a_base(sgm) + a_skip;
+        b_at = (const char*)b_base(sgm) + b_skip;
+        a_left = 2 * ((a_rows - 1) * g.lda + a_cols) - (long)a_skip;
+        b_left = 2 * ((b_rows - 1) * g.ldb + b_cols) - (long)b_skip;
+    };
+    auto rag_rsrc = [&](const char* at, long left) {
+        return make_rsrc(at, left <= 0 ? 0u : left < (long)kOutside ? (uint32_t)left : kOutside);
+    };
+    if constexpr (RAG) rag_origin(seg, a_off, b_off);
+    auto rag_move = [&](uint32_t da, uint32_t db) {
+        a_at += da; a_left -= da;
+        b_at += db; b_left -= db;
+    };
     int issued = 0;                                     // slices requested so far
     // move on to the next slice, unless the last one has just been requested: then stay on it
     auto advance = [&]() {
@@ -447,12 +497,14 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
         if (issued >= nk) return;
         a_off += a_step;
         b_off += b_step;
+        if constexpr (RAG) rag_move(a_step, b_step);
         if (++kl == nk_seg) {
             kl = 0;
             ++seg;
             a_tile = a_origin(seg);
             b_tile = b_origin(seg);
             a_off = b_off = 0;
+            if constexpr (RAG) rag_origin(seg, 0, 0);
         }
     };
 
@@ -460,6 +512,18 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     DmaPlan<BN, BKT, NW, B_RMAJOR> pb;
     pa.init(wave, lane, g.lda);
     pb.init(wave, lane, g.ldb);
+    if constexpr (RAG && !A_RMAJOR) pa.init_tail(wave, lane, g.K - (nk_seg - 1) * BKT);
+    if constexpr (RAG && !B_RMAJOR) pb.init_tail(wave, lane, g.K - (nk_seg - 1) * BKT);
+    // request slice kl_ of the current segment into LDS stage `st`
+    auto issue_slice = [&](char* st, int kl_) {
+        if constexpr (RAG) {
+            pa.issue_rag(rag_rsrc(a_at, a_left), kl_ == nk_seg - 1, st, wave);
+            pb.issue_rag(rag_rsrc(b_at, b_left), kl_ == nk_seg - 1, st + A_BYTES, wave);
+        } else {
+            pa.issue(a_tile, a_off, st, wave);
+            pb.issue(b_tile, b_off, st + A_BYTES, wave);
+        }
+    };
     constexpr int LPT = decltype(pa)::NI + decltype(pb)::NI;   // loads per slice per wave
 
     // MI16: the tile is made of 16x16x32 MFMAs instead of 32x32x16 ones, and a "k step" below is 32
@@ -582,12 +646,18 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
         const int nq = 2 * nk;                                      // slots this block walks through
         const uint32_t a_step32 = a_step / 2, b_step32 = b_step / 2;
         auto request = [&](int slot) {
-            ra.issue(a_tile, a_off, smem + slot * SLOT, wave);
-            rb.issue(b_tile, b_off, smem + slot * SLOT + BM * 64, wave);
+            if constexpr (RAG) {
+                ra.issue_rag(rag_rsrc(a_at, a_left), false, smem + slot * SLOT, wave);
+                rb.issue_rag(rag_rsrc(b_at, b_left), false, smem + slot * SLOT + BM * 64, wave);
+            } else {
+                ra.issue(a_tile, a_off, smem + slot * SLOT, wave);
+                rb.issue(b_tile, b_off, smem + slot * SLOT + BM * 64, wave);
+            }
             // (no branch) past the end the last slot is requested again, into slots nobody reads any more
             ++issued;
             a_off += issued < nq ? a_step32 : 0u;
             b_off += issued < nq ? b_step32 : 0u;
+            if constexpr (RAG) rag_move(issued < nq ? a_step32 : 0u, issued < nq ? b_step32 : 0u);
         };
         auto interleave_l = [&]() { SchedRounds<0, NMFMA, NREAD, L32>::apply(); };
         // The requests walk through the contraction segments 32 deep at a time; a segment holds an even
@@ -602,6 +672,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
                 a_tile = a_origin(seg);
                 b_tile = b_origin(seg);
                 a_off = b_off = 0;
+                if constexpr (RAG) rag_origin(seg, 0, 0);
             }
         };
         a_off = (uint32_t)kl32 * a_step32;
@@ -647,16 +718,14 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s) {
         if (s < nk) {
-            pa.issue(a_tile, a_off, smem + s * STAGE, wave);
-            pb.issue(b_tile, b_off, smem + s * STAGE + A_BYTES, wave);
+            issue_slice(smem + s * STAGE, kl);
             advance();
         }
     }
     wait_slices(min(nk, NS - 1) - 1);                   // slice 0 has landed
     __syncthreads();
     if (NS - 1 < nk) {
-        pa.issue(a_tile, a_off, smem + (NS - 1) * STAGE, wave);
-        pb.issue(b_tile, b_off, smem + (NS - 1) * STAGE + A_BYTES, wave);
+        issue_slice(smem + (NS - 1) * STAGE, kl);
         advance();
     }
     read_step(smem, 0, 0);
@@ -685,14 +754,13 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
             __builtin_amdgcn_sched_barrier(0);
             const int nxt = cur + 1 == NS ? 0 : cur + 1;
             if constexpr (LF == 0) read_step(smem + nxt * STAGE, 0, 0);
-            char* st = smem + cur * STAGE;
-            pa.issue(a_tile, a_off, st, wave);
-            pb.issue(b_tile, b_off, st + A_BYTES, wave);
+            issue_slice(smem + cur * STAGE, min(kl + it, nk_seg - 1));
             if constexpr (LF > 0) read_step(smem + nxt * STAGE, 0, 0);
             // (no branch) the offsets stop moving once the last slice has been requested
             ++issued;
             a_off += issued < nk ? a_step : 0u;
             b_off += issued < nk ? b_step : 0u;
+            if constexpr (RAG) rag_move(issued < nk ? a_step : 0u, issued < nk ? b_step : 0u);
             mfma_step((KK - 1) & 1);
             interleave_boundary();
             cur = nxt;
@@ -705,6 +773,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
             a_tile = a_origin(seg);
             b_tile = b_origin(seg);
             a_off = b_off = 0;
+            if constexpr (RAG) rag_origin(seg, 0, 0);
         }
     }
     }
@@ -733,6 +802,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
             for (int r = 0; r < ENR; ++r) {
                 const int row = r * ERPI + lane / ELPR;
                 if (ELPR * ERPI < 64 && lane >= ELPR * ERPI) continue;
+                if (RAG && (m_base + row >= g.M || n_base + (lane % ELPR) * 8 >= g.N)) continue;
                 upre[r] = *reinterpret_cast<const u32x4*>((const bf16_t*)g.U + (size_t)(m_base + row) * g.ldc +
                                                           n_base + (lane % ELPR) * 8);
             }
@@ -774,6 +844,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
             for (int r = 0; r < 32; r += RPI) {
                 const int row = r + lane / LPR;
                 if (LPR * RPI < 64 && lane >= LPR * RPI) continue;
+                if (RAG && (m_base + row >= g.M || n_base + col >= g.N)) continue;
                 const f32x4 v = *reinterpret_cast<const f32x4*>(ep + row * PITCH + col);
                 f32x4* c = reinterpret_cast<f32x4*>((float*)g.C + (size_t)(m_base + row) * g.ldc + n_base + col);
                 if (g.accumulate == 2) *c = v;      // first contribution after a clear: no read
@@ -784,12 +855,13 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
             const int col = (lane % LPR) * 8;
             float bias[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) bias[e] = g.bias ? g.bias[n_base + col + e] : 0.f;
+            for (int e = 0; e < 8; ++e) bias[e] = g.bias && (!RAG || n_base + col < g.N) ? g.bias[n_base + col + e] : 0.f;
             float csum[8] = {0, 0, 0, 0, 0, 0, 0, 0};      // EPI_GELU_BWD: column sums of this slab
 #pragma unroll
             for (int r = 0; r < 32; r += RPI) {
                 const int row = r + lane / LPR;
                 if (LPR * RPI < 64 && lane >= LPR * RPI) continue;
+                if (RAG && (m_base + row >= g.M || n_base + col >= g.N)) continue;
                 const f32x4 v0 = *reinterpret_cast<const f32x4*>(ep + row * PITCH + col);
                 const f32x4 v1 = *reinterpret_cast<const f32x4*>(ep + row * PITCH + col + 4);
                 float o[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
@@ -830,7 +902,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
                 for (int e = 0; e < 8; ++e)
 #pragma unroll
                     for (int o2 = LPR; o2 < 64; o2 <<= 1) csum[e] += __shfl_xor(csum[e], o2, 64);
-                if (lane < LPR) store8(g.colpart + (size_t)(m_base >> 5) * g.N + n_base + col, csum);
+                if (lane < LPR && (!RAG || (m_base < g.M && n_base + col < g.N))) store8(g.colpart + (size_t)(m_base >> 5) * g.N + n_base + col, csum);
             }
         }
     }
@@ -864,7 +936,7 @@ static hipError_t launch_cfg(const GemmArgs& g, hipStream_t s) {
 
 // Sum the K-slice partials of the tail tiles in slice order and apply the epilogue; 8 outputs per
 // thread, BM * BN / 2048 blocks per tile.
-template <int BM, int BN>
+template <int BM, int BN, bool RAG>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, int splits, int tiles_m, int tiles_n,
                                                             int n_full) {
     constexpr int BPT = BM * BN / 2048;                 // blocks per tile
@@ -874,6 +946,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, int spli
     const int v = (blockIdx.x % BPT) * 256 + threadIdx.x;      // 8-element vector inside the tile
     const int r = v / (BN / 8), c = (v % (BN / 8)) * 8;
     const int m = tm * BM + r, n = tn * BN + c;
+    if (RAG && (m >= g.M || n >= g.N)) return;
     const float* slab = g.split_ws + (size_t)tail_idx * splits * (BM * BN) + (size_t)r * BN + c;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int sp = 0; sp < splits; ++sp) {
@@ -908,9 +981,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, int spli
     }
 }
 
-template <int BM, int BN, int WM, int WN, int NS, int BKT = 64, bool MI16 = false, bool RING = false>
-static hipError_t launch_dma(const GemmArgs& g, hipStream_t s, int splits = 1, int n_full = -1) {
-    const int tiles_m = g.M / BM, tiles_n = g.N / BN;
+template <int BM, int BN, int WM, int WN, int NS, int BKT, bool MI16, bool RING, bool RAG>
+static hipError_t launch_dma_rag(const GemmArgs& g, hipStream_t s, int splits, int n_full) {
+    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     const int nblk = tiles_m * tiles_n;
     if (splits <= 1) { splits = 1; n_full = nblk; }
     else if (n_full < 0) n_full = 0;                    // every tile is cut along K
@@ -921,7 +994,7 @@ static hipError_t launch_dma(const GemmArgs& g, hipStream_t s, int splits = 1, i
     const size_t smem = stages > epilogue ? stages : epilogue;
 #define BP_GEMM_LAUNCH(AR, BR)                                                                   \
     do {                                                                                         \
-        auto kern = gemm_dma_kernel<BM, BN, WM, WN, BKT, NS, AR, BR, MI16, RING>;                         \
+        auto kern = gemm_dma_kernel<BM, BN, WM, WN, BKT, NS, AR, BR, MI16, RING, RAG>;                    \
         static std::atomic<bool> attr_set{false};   /* once per instantiation; host threads may race */ \
         if (smem > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {                                                     \
             hipError_t e = hipFuncSetAttribute((const void*)kern,                                \
@@ -938,14 +1011,22 @@ static hipError_t launch_dma(const GemmArgs& g, hipStream_t s, int splits = 1, i
 #undef BP_GEMM_LAUNCH
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n_tail == 0) return e;
-    hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN>), dim3((unsigned)(n_tail * (BM * BN / 2048))), dim3(256), 0, s,
+    hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, RAG>), dim3((unsigned)(n_tail * (BM * BN / 2048))), dim3(256), 0, s,
                        g, splits, tiles_m, tiles_n, n_full);
     return hipGetLastError();
 }
 
+template <int BM, int BN, int WM, int WN, int NS, int BKT = 64, bool MI16 = false, bool RING = false>
+static hipError_t launch_dma(const GemmArgs& g, hipStream_t s, int splits = 1, int n_full = -1) {
+    if (g.M % BM || g.N % BN || g.K % BKT)
+        return launch_dma_rag<BM, BN, WM, WN, NS, BKT, MI16, RING, true>(g, s, splits, n_full);
+    return launch_dma_rag<BM, BN, WM, WN, NS, BKT, MI16, RING, false>(g, s, splits, n_full);
+}
+
 bool gemm_mfma_supported(const GemmArgs& g) {
     auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-    if (g.K % 8 || g.lda % 8 || g.ldb % 8) return false;
+    // k-major operands are read in 8-element chunks along k
+    if (g.lda % 8 || g.ldb % 8 || ((!g.a_t || g.b_t) && g.K % 8)) return false;
     if (!al16(g.A) || !al16(g.B)) return false;
     for (int i = 0; i + 1 < g.nseg; ++i)
         if (!al16(g.A_more[i]) || !al16(g.B_more[i])) return false;
@@ -955,9 +1036,10 @@ bool gemm_mfma_supported(const GemmArgs& g) {
     return true;
 }
 
+// rows of C (and of the residual) in 16-byte pieces; everything else gemm_mfma_supported has checked
 static bool dma_path_ok(const GemmArgs& g) {
     auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-    bool ok = g.M % 128 == 0 && g.N % 128 == 0 && g.K % BK == 0 && g.ldc % 8 == 0 && al16(g.C) &&
+    bool ok = g.N % 8 == 0 && g.ldc % 8 == 0 && al16(g.C) &&
               (!g.residual || al16(g.residual));
     for (int i = 0; i + 1 < g.nseg; ++i) ok = ok && al16(g.A_more[i]) && al16(g.B_more[i]);
     return ok;
@@ -987,9 +1069,9 @@ static int cu_count() {
 
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-    const bool aligned128 = dma_path_ok(g);
+    const bool dma = dma_path_ok(g);
     if (g.epi != EPI_NONE && !gemm_can_fuse_epilogue(BF16, g)) return hipErrorInvalidValue;
-    if (!aligned128) {
+    if (!dma) {
         if (g.nseg == 1) return launch_cfg<128, 128, 2, 2, true>(g, s);
         return launch_gemm_per_segment(g, s, [](const GemmArgs& h, hipStream_t st) {
             return launch_cfg<128, 128, 2, 2, true>(h, st);
@@ -999,12 +1081,15 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     const long k_total = (long)g.K * g.nseg;
     const long most = 3L * ncu / 4;       // a launch with at least this many blocks is taken to fill the chip
     // 256 x 256 tiles (8 waves) once they fill at least three quarters of the CUs
+    // (of what their edge tiles compute at most 15 % may be padding)
+    auto tiles = [&](int bm, int bn) { return (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+    auto useful = [&](int bm, int bn) { return (double)g.M * g.N / ((double)tiles(bm, bn) * bm * bn); };
     const bool aligned256 = g.M % 256 == 0 && g.N % 256 == 0;
-    const long t256 = aligned256 ? (long)(g.M / 256) * (g.N / 256) : 0;
+    const long t256 = useful(256, 256) >= 0.85 ? tiles(256, 256) : 0;
     // 256 x 192 tiles when they fill the CUs better: e.g. N = 6144 gives 24 columns of 256 (192 tiles
     // for M = 2048, a quarter of the CUs idle) but 32 columns of 192 (256 tiles)
     auto fill = [&](long t) { return t <= 0 ? 0.0 : (double)t / (double)(((t + ncu - 1) / ncu) * ncu); };
-    const long t192 = (g.M % 256 == 0 && g.N % 192 == 0) ? (long)(g.M / 256) * (g.N / 192) : 0;
+    const long t192 = g.N % 192 == 0 || (!aligned256 && useful(256, 192) >= 0.85) ? tiles(256, 192) : 0;
     // (the fused GELU-backward epilogue folds column sums over power-of-two lane groups: not 96 wide)
     // The 192-wide tile has fewer MFMAs per LDS read and per barrier: measured against the 256-wide
     // one at equal fill it runs at about 0.85 of its rate for weight gradients with a long contraction
@@ -1013,7 +1098,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     // 543 us against 494 us at a fill of 0.94), else within 5 %.
     const bool nt = !g.a_t && g.b_t;
     const double rate192 = ((g.a_t && !g.b_t && (long)g.K * g.nseg >= 4096) || nt) ? 0.85 : 0.95;
-    if (g.epi == EPI_NONE && t192 >= most && rate192 * fill(t192) > fill(t256)) {
+    if (g.epi == EPI_NONE && t192 >= most && rate192 * fill(t192) * useful(256, 192) > fill(t256) * useful(256, 256)) {
         if (nt) return launch_dma<256, 192, 2, 4, 2, 64, true>(g, s);
         return launch_dma<256, 192, 4, 2, 2>(g, s);
     }
@@ -1048,11 +1133,12 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     // 229 us against 115 us).
     // Not for weight gradients either: with both operands read through the transpose path the small
     // tiles lose more than the partials cost (2560 x 2560 x 16384: 334 us against 272 us).
-    const long t128 = (long)(g.M / 128) * (g.N / 128);
+    const long t128 = tiles(128, 128);
+    const bool deep = g.K % 128 == 0 || (g.K % BK != 0 && g.K > 512);   // slices of 128 along K
     const bool small_fill = t128 >= most && (k_total <= 4096 || (nt && k_total <= 8192 && fill(t128) >= 0.95));
     if (small_fill && !(g.a_t && !g.b_t)) {
         if (nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s);
-        if (g.K % 128 == 0) return launch_dma<128, 128, 2, 4, 2, 128>(g, s);
+        if (deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s);
         return launch_dma<128, 128, 2, 4, 2>(g, s);
     }
     // Fewer tiles than that but a long K: 256 x 256 tiles on K slices keep the operand traffic per
@@ -1067,12 +1153,11 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     // Small outputs (128 x 128 tiles on fewer than three quarters of the CUs) with a long K: the same split, on the small
     // tiles (slices at least 1024 deep: below that the second kernel costs what the split gains)
     if (g.split_ws && g.epi == EPI_NONE) {
-        const int bk = g.K % 128 == 0 ? 128 : BK;
         int splits = (int)(ncu / t128);
         if (splits > 4) splits = 4;
-        while (splits > 1 && (k_total / splits < 1024 || (size_t)splits * g.M * g.N > g.split_ws_elems)) --splits;
+        while (splits > 1 && (k_total / splits < 1024 || (size_t)splits * t128 * 16384 > g.split_ws_elems)) --splits;
         if (splits > 1 && nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s, splits, 0);
-        if (splits > 1 && bk == 128) return launch_dma<128, 128, 2, 4, 2, 128>(g, s, splits, 0);
+        if (splits > 1 && deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s, splits, 0);
         if (splits > 1) return launch_dma<128, 128, 2, 4, 2>(g, s, splits, 0);
     }
     // 8 waves (2 per SIMD) hide the LDS and load latencies better than 4 on these small tiles.
@@ -1082,7 +1167,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     // 4096 27.9 us against 31.8 us).  The other forms: slices of 128 along K (two stages of 64 KB),
     // which halve the number of barriers per MFMA.
     if (nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s);
-    if (g.K % 128 == 0) return launch_dma<128, 128, 2, 4, 2, 128>(g, s);
+    if (deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s);
     return launch_dma<128, 128, 2, 4, 2>(g, s);
 }
 

@@ -67,6 +67,19 @@ def test_gemm_forms(M, N, K, form, dtype):
     assert err <= tol, (form, M, N, K, err)
 
 
+# Edge tiles of the direct-to-LDS kernel: one row / column / chunk, one past a tile, K (a token count in
+# the weight-gradient form) that is no multiple of anything, each tile shape.  Tolerances as above: the
+# same products with the same roundings.
+@pytest.mark.parametrize("form,M,N,K", [
+    ("dgrad", 1, 8, 8), ("dgrad", 129, 136, 72), ("dgrad", 255, 264, 200), ("dgrad", 1000, 9600, 72),
+    ("dgrad", 4000, 3200, 136), ("fwd", 257, 136, 72), ("fwd", 1, 264, 64),
+    ("wgrad", 8, 8, 1), ("wgrad", 136, 264, 77), ("wgrad", 520, 136, 333), ("wgrad", 4000, 3200, 97),
+    ("wgrad", 1000, 9600, 65), ("wgrad", 264, 520, 1999),
+])
+def test_gemm_edge_tiles(form, M, N, K):
+    test_gemm_forms(M, N, K, form, "bf16")
+
+
 @pytest.mark.parametrize("T,H", [(64, 128), (300, 1024), (260, 2048), (77, 5120), (33, 8192), (5, 8)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_layernorm_fwd_bwd(T, H, dtype):
@@ -279,6 +292,9 @@ def test_attention_wide_score_range(B, S, heads, d, causal):
     (2048, 2560, 1664, 2),     # with a workspace: 80 tiles x 3 token slices of 18, 17, 17 steps
     (512, 768, 1600, 2),       # with a workspace: 24 small tiles x 3 token slices of 17, 17, 16 steps
     (2048, 1152, 2048, 2),     # with a workspace, N a multiple of 128 and 192 but not of 256
+    (264, 520, 77, 3),         # ragged everywhere, segments of an odd number of tokens
+    (264, 520, 1025, 3),       # the same with a workspace: token slices that end inside segments
+    (4000, 3200, 33, 2),       # 256x256 tiles with edges, segments shorter than a slice
 ])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("overwrite", [0, 1])

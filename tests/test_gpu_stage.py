@@ -281,3 +281,14 @@ def test_random_small_stage_configs(idx, kw, group, lean):
     errs = hz.run_fwd_bwd_parity(cfg, ln_jitter=0.1, wgrad_group=group, stash_recompute=lean, seed=idx)
     worst = max(errs.items(), key=lambda kv: kv[1])
     print(idx, kw, "group", group, "lean", lean, "worst", worst)
+
+
+@pytest.mark.parametrize("kw,group,lean", [
+    # T = 231 tokens (odd), width a multiple of 8 only, MLP deep enough for K slices: edge tiles in every GEMM form
+    # with the fused GELU epilogues, token segments that end inside a slice
+    (dict(layers=2, hidden=520, heads=13, seq=77, microbatch=3, causal=True, n_micro=4), 3, 0),
+    (dict(layers=1, hidden=320, heads=5, seq=333, microbatch=2, causal=False, n_micro=2, len_lo=20, len_hi=333), 0, 1),
+])
+def test_ragged_stage(kw, group, lean):
+    cfg = si.scaled(si.CONFIGS[1], name="small_ragged_edges", **kw)
+    hz.run_fwd_bwd_parity(cfg, ln_jitter=0.1, wgrad_group=group, stash_recompute=lean)
