@@ -1,7 +1,22 @@
 // Kernel selection: which implementation serves a given GEMM / attention shape.
 #include "bp_kernels.h"
 
+#include <atomic>
+
 namespace bp {
+
+int cu_count() {
+    static std::atomic<int> cached{0};
+    int n = cached.load(std::memory_order_relaxed);
+    if (!n) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+            n = 256;
+        cached.store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
 
 // one launch per contraction segment, for kernels that take a single operand pair
 hipError_t launch_gemm_per_segment(const GemmArgs& g, hipStream_t stream,
@@ -24,6 +39,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
     if (g.nseg < 1 || g.nseg > kMaxGemmSegments || (g.nseg > 1 && !g.accumulate)) return hipErrorInvalidValue;
     if (g.epi != EPI_NONE && !gemm_can_fuse_epilogue(dtype, g)) return hipErrorInvalidValue;
     if (dtype == BF16 && gemm_mfma_supported(g)) return launch_gemm_mfma(g, stream);
+    if (dtype == F32 && gemm_f32_supported(g)) return launch_gemm_f32(g, stream);
     if (g.nseg == 1) return launch_gemm_generic(dtype, g, stream);
     if (dtype == BF16)
         return launch_gemm_per_segment(g, stream, [](const GemmArgs& h, hipStream_t s) {

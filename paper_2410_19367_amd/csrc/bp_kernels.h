@@ -13,6 +13,8 @@ inline size_t dtype_size(int dt) { return dt == BF16 ? 2 : 4; }
 
 constexpr int kMaxGemmSegments = 8;
 
+int cu_count();          // compute units of the device (256 if it cannot be asked)
+
 // C = op(A) op(B) (+bias) (+residual)  or  C(fp32) += op(A) op(B).
 //   op(A)[m,k] = a_t ? A[k*lda + m] : A[m*lda + k]
 //   op(B)[k,n] = b_t ? B[n*ldb + k] : B[k*ldb + n]
@@ -57,6 +59,8 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t stream);
 hipError_t launch_gemm_generic(int dtype, const GemmArgs& g, hipStream_t stream);
 bool gemm_mfma_supported(const GemmArgs& g);                       // bf16 only
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t stream);
+bool gemm_f32_supported(const GemmArgs& g);                        // fp32 only
+hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t stream);
 hipError_t launch_gemm_per_segment(const GemmArgs& g, hipStream_t stream,
                                    hipError_t (*one)(const GemmArgs&, hipStream_t));
 

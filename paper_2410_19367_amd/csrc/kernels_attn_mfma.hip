@@ -691,17 +691,8 @@ static hipError_t set_smem(K kern, size_t smem) {
 // heaviest causal block, which is what bounds a launch with only a couple of blocks per CU; with
 // many blocks per CU the 4-wave form with two co-resident blocks is faster.
 static int tiles_per_step(const AttnArgs& a) {
-    static std::atomic<int> n_cu_cached{0};
-    int n_cu = n_cu_cached.load(std::memory_order_relaxed);
-    if (!n_cu) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
-            n_cu = 256;
-        n_cu_cached.store(n_cu, std::memory_order_relaxed);
-    }
     const long blocks = (long)((a.S + 63) / 64) * a.heads * a.B;
-    return (a.S >= 512 && blocks <= 2L * n_cu) ? 2 : 1;
+    return (a.S >= 512 && blocks <= 2L * cu_count()) ? 2 : 1;
 }
 
 template <int D, int DR, int NT, bool RAG>

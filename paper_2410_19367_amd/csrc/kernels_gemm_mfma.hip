@@ -26,6 +26,7 @@
 
 #include "bp_kernels.h"
 #include "bp_device.h"
+#include "bp_tile.h"
 
 namespace bp {
 
@@ -246,35 +247,6 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_kernel(GemmArgs g, int 
 // are produced by choosing which global chunk each lane fetches.
 // =====================================================================================
 
-// (a 16-byte fragment read serves 16 lanes = 16 consecutive rows per cycle: the XOR has to give
-// those rows 16 different chunk positions modulo the 256-byte bank period)
-template <int BKT> __device__ __forceinline__ int kmaj_swz(int row) {
-    return BKT == 128 ? (row & 15) : BKT == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3);
-}
-// byte offset of logical 16-byte chunk c of `row` in a k-major tile [R][BKT]
-template <int BKT> __device__ __forceinline__ int kmaj_off(int row, int c) {
-    return row * (BKT * 2) + ((c ^ kmaj_swz<BKT>(row)) << 4);
-}
-
-// One wave instruction moves 64 x 16 bytes from global memory straight into 1 KiB of consecutive LDS.
-// The global address is a buffer descriptor (wave-uniform tile origin) plus a per-lane 32-bit byte
-// offset plus a wave-uniform byte offset (the K slice), so issuing a load costs no vector ALU work.
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-__device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes = 0xffffffffu) {
-    // raw buffer, stride 0, loads at or beyond `bytes` give zeros (default: no bounds clamp below
-    // 4 GiB - 1); dword 3 as for untyped 32-bit data on gfx9
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ void dma16(rsrc_t rsrc, uint32_t lane_off, uint32_t slice_off, char* lds_wave_base) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (void __attribute__((address_space(3)))*)lds_wave_base, 16,
-                                             (int)lane_off, (int)slice_off, 0, 0);
-}
-
-// s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
-#define BP_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
-
-constexpr uint32_t kOutside = 0xffffff00u;          // beyond the size of every ragged operand's descriptor
-
 // Per-lane byte offsets (relative to the slice base) of the chunks this lane fetches: 32 bits, so
 // that the load takes the wave-uniform slice base from scalar registers plus this one vector register.
 template <int R, int BKT, int NW, bool RMAJOR>
@@ -364,19 +336,6 @@ constexpr int rows_per_instr(int lanes_per_row) {
     int r = 1;
     while (2 * r * lanes_per_row <= 64 && 2 * r <= 32) r *= 2;
     return r;
-}
-
-// Tile order: each XCD (blocks are dealt round-robin over 8 XCDs) gets a contiguous range of ids,
-// walked in groups of 4 tile rows so that concurrent blocks share A rows and B columns.
-__device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int nblk = tiles_m * tiles_n;
-    if (nblk % 8 == 0) t = (t & 7) * (nblk >> 3) + (t >> 3);
-    constexpr int GM = 4;
-    const int per_group = GM * tiles_n;
-    const int first_m = (t / per_group) * GM;
-    const int gsize = min(tiles_m - first_m, GM);
-    tm = first_m + (t % per_group) % gsize;
-    tn = (t % per_group) / gsize;
 }
 
 // Issue-order groups for one k step of NMFMA MFMAs.  Inside a slice (NLOAD == 0) the step's NREAD
@@ -1047,24 +1006,11 @@ static bool dma_path_ok(const GemmArgs& g) {
 
 bool gemm_can_fuse_epilogue(int dtype, const GemmArgs& g) {
     auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-    if (dtype != BF16 || !gemm_mfma_supported(g) || !dma_path_ok(g)) return false;
+    if (dtype == BF16 ? !gemm_mfma_supported(g) || !dma_path_ok(g) : !gemm_f32_supported(g)) return false;
     if (g.accumulate || g.residual || g.nseg != 1 || !g.bias) return false;
     if (g.epi == EPI_GELU_FWD) return g.C2 && al16(g.C2);
     if (g.epi == EPI_GELU_BWD) return g.U && al16(g.U) && g.colpart && al16(g.colpart) && g.N % 8 == 0;
     return false;
-}
-
-static int cu_count() {
-    static std::atomic<int> cached{0};
-    int n = cached.load(std::memory_order_relaxed);
-    if (!n) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-            n = 256;
-        cached.store(n, std::memory_order_relaxed);
-    }
-    return n;
 }
 
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {

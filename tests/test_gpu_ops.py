@@ -80,6 +80,16 @@ def test_gemm_edge_tiles(form, M, N, K):
     test_gemm_forms(M, N, K, form, "bf16")
 
 
+# fp32 kernel: both tile widths, one element past a tile, the shortest K, K tails of four, unaligned rows
+# (the generic kernel); 1e-5 relative to the largest element bounds fp32 sums of this length
+@pytest.mark.parametrize("form,M,N,K", [
+    ("dgrad", 33, 32, 4), ("dgrad", 1, 36, 68), ("dgrad", 65, 132, 200), ("dgrad", 1030, 1100, 72), ("fwd", 31, 100, 132),
+    ("fwd", 1030, 1100, 36), ("wgrad", 4, 4, 1), ("wgrad", 36, 132, 77), ("wgrad", 1028, 1100, 65), ("fwd", 50, 37, 64),
+])
+def test_gemm_f32_edge_tiles(form, M, N, K):
+    test_gemm_forms(M, N, K, form, "f32")
+
+
 @pytest.mark.parametrize("T,H", [(64, 128), (300, 1024), (260, 2048), (77, 5120), (33, 8192), (5, 8)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_layernorm_fwd_bwd(T, H, dtype):

@@ -288,6 +288,8 @@ def test_random_small_stage_configs(idx, kw, group, lean):
     # with the fused GELU epilogues, token segments that end inside a slice
     (dict(layers=2, hidden=520, heads=13, seq=77, microbatch=3, causal=True, n_micro=4), 3, 0),
     (dict(layers=1, hidden=320, heads=5, seq=333, microbatch=2, causal=False, n_micro=2, len_lo=20, len_hi=333), 0, 1),
+    # fp32: fused GELU epilogues with edge tiles
+    (dict(layers=2, hidden=200, heads=5, seq=77, microbatch=3, causal=True, n_micro=4, dtype="f32"), 3, 0),
 ])
 def test_ragged_stage(kw, group, lean):
     cfg = si.scaled(si.CONFIGS[1], name="small_ragged_edges", **kw)
