@@ -237,12 +237,34 @@ def test_attention_fwd_bwd(B, S, heads, d, causal, lens, dtype):
 
 # Sequence lengths around the 64-row tiles and the 32-row halves, one and two tiles per forward step
 @pytest.mark.parametrize("B,S,heads,d,causal,lens", [
-    (2, 1, 2, 64, True, None), (2, 31, 2, 64, True, None), (1, 33, 3, 128, True, None), (2, 63, 2, 40, True, None),
+    (2, 2, 2, 64, True, None), (2, 31, 2, 64, True, None), (1, 33, 3, 128, True, None), (2, 63, 2, 40, True, None),
     (3, 65, 2, 64, False, [65, 1, 64]), (1, 97, 2, 96, False, [33]), (2, 127, 2, 128, True, None),
     (1, 513, 2, 64, True, None), (1, 545, 2, 128, False, [544]), (1, 1000, 1, 64, True, None), (2, 333, 2, 64, False, [100, 333]),
 ])
-def test_attention_ragged_lengths(B, S, heads, d, causal, lens):
-    test_attention_fwd_bwd(B, S, heads, d, causal, lens, "bf16")
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_attention_ragged_lengths(B, S, heads, d, causal, lens, dtype):
+    test_attention_fwd_bwd(B, S, heads, d, causal, lens, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_attention_one_token(dtype):
+    """S = 1: probability one, so ctx = v and dv = dctx exactly, and dq, dk vanish up to the rounding of
+    dP - delta, two equal sums of d = 64 products of about unit size: below 64 * 64 * 2^-24 * 16 * max|k|/8 < 1e-2."""
+    import torch
+    import paper_2410_19367_amd as bp
+    B, heads, d = 3, 2, 64
+    H, dt = heads * d, bp.BP_BF16 if dtype == "bf16" else bp.BP_F32
+    qkv, dctx = _randn("oqkv", (B, 1, 3 * H), dtype=dtype), _randn("odctx", (B, 1, H), dtype=dtype)
+    qd, dd = hz.to_dev(qkv, dtype), hz.to_dev(dctx, dtype)
+    ctx, dqkv = hz.empty_like_dev((B, 1, H), dtype), hz.empty_like_dev((B, 1, 3 * H), dtype)
+    lse, delta = torch.empty((B, heads, 1), device="cuda"), torch.empty((B, heads, 1), device="cuda")
+    bp.bp_op_attention_fwd(dt, B, 1, heads, d, True, None, qd, ctx, lse)
+    bp.bp_op_attention_bwd(dt, B, 1, heads, d, True, None, qd, ctx, lse, dd, dqkv, delta)
+    torch.cuda.synchronize()
+    assert np.allclose(hz.to_host(ctx), qkv[..., 2 * H:], rtol=1e-5)
+    got = hz.to_host(dqkv)
+    assert np.allclose(got[..., 2 * H:], dctx, rtol=1e-5 if dtype == "f32" else 2 ** -8)
+    assert np.max(np.abs(got[..., :2 * H])) < 1e-2
 
 
 @pytest.mark.parametrize("B,S,heads,d,causal", [(1, 512, 2, 128, True), (2, 256, 2, 64, False), (1, 1024, 1, 128, True)])
