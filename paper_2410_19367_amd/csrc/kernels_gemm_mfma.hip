@@ -16,9 +16,9 @@
 // element (outputs whose rows are no multiple of 8 elements or not 16-byte aligned); gemm_dma_kernel
 // (further down) loads slices straight into LDS, for any shape with 16-byte rows, and carries the
 // fused epilogues, split-K and multi-segment contractions.  Slices land in LDS while earlier ones feed the MFMAs,
-// one barrier per slice: two LDS stages in gemm_mfma_kernel and in the large tiles of
-// gemm_dma_kernel, three in its 128 x 128 forward / data-gradient form, a ring of five half-slices
-// in its weight-gradient form.
+// one barrier per slice: two LDS stages in gemm_mfma_kernel; in gemm_dma_kernel three of A and two of B
+// in the large tiles of the forward / data-gradient form, three in its 128 x 128 tiles, a ring of five
+// half-slices in the weight-gradient form, two elsewhere.
 #include <cstdlib>
 #include <type_traits>
 
@@ -332,6 +332,10 @@ __device__ __forceinline__ bf16x8 read_frag16(const char* lds, int row0, int kk,
     }
 }
 
+// the forward / data-gradient form of the large tiles: its operands have LDS stages of their own
+template <int NS, bool MI16, bool RING>
+constexpr bool staggered(bool a_rmajor, bool b_rmajor) { return NS == 2 && MI16 && !RING && !a_rmajor && !b_rmajor; }
+
 constexpr int rows_per_instr(int lanes_per_row) {
     int r = 1;
     while (2 * r * lanes_per_row <= 64 && 2 * r <= 32) r *= 2;
@@ -386,6 +390,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     constexpr int NW = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int A_BYTES = BM * BKT * 2, B_BYTES = BN * BKT * 2, STAGE = A_BYTES + B_BYTES;
+    constexpr bool AHEAD = staggered<NS, MI16, RING>(A_RMAJOR, B_RMAJOR);
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     // Blocks 0 .. n_full-1 compute whole tiles.  The remaining tiles (the tail of the launch, which
@@ -520,9 +525,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     bf16x8 fa[2][FM], fb[2][FN];
     // program order = issue order of the reads: the fragments the step's first MFMAs need (A row
     // block 0 and every B column block) before the other A row blocks
-    auto read_step = [&](const char* sa, int kk, int buf) {
+    auto read_step2 = [&](const char* sa, const char* sb, int kk, int buf) {
         constexpr int LBK = RING ? 32 : BKT;            // K depth of one LDS tile (ring: slots of 32)
-        const char* sb = sa + BM * LBK * 2;
         if constexpr (MI16) {
             fa[buf][0] = read_frag16<BM, LBK, A_RMAJOR>(sa, wm * (BM / WM), kk, lane);
 #pragma unroll
@@ -537,6 +541,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
         for (int i = 1; i < TM; ++i) fa[buf][i] = read_frag2<BM, BKT, A_RMAJOR>(sa, wm * (BM / WM) + i * 32, kk, lane);
         }
     };
+    auto read_step = [&](const char* sa, int kk, int buf) { read_step2(sa, sa + BM * (RING ? 32 : BKT) * 2, kk, buf); };
     auto mfma_step = [&](int buf) {
         if constexpr (MI16) {
 #pragma unroll
@@ -672,6 +677,62 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
             it += run;
             kl32 += 2 * run;
             next_segment();
+        }
+    } else if constexpr (AHEAD) {
+        // Both operands contraction-major, one segment: three LDS stages of A and two of B (160 KB for a
+        // 256 x 256 tile, the whole LDS).  The kernel is bound by how late a slice's loads land (issue
+        // of 64 KB plus one L2 miss is longer than a slice's MFMAs), so the two operands are requested
+        // half a slice apart: A of slice kt + 2 before the barrier of slice kt, into the stage that the
+        // barrier before has freed, B of slice kt + 2 right after it.  The barrier then waits for the older
+        // half only, and A has one and a half slices to land instead of one.  (Five slots along K, as in
+        // the ring, would fetch half cache lines here.)  Against two stages of both, same bits:
+        // 4096 x 20480 x 5120 654 -> 629 us, 4096 x 5120 x 20480 889 -> 819 us, 4096 x 15360 x 5120
+        // 512 -> 489 us, 8192^3 790 -> 775 us; launches of one round of tiles (2048 x 8192 x 2048, 55 us)
+        // stay where they were.  Both requests after the barrier: 2 % slower.
+        constexpr int LA = decltype(pa)::NI, LB = decltype(pb)::NI;
+        char* const b_stages = smem + 3 * A_BYTES;
+        int qa = 0, qb = 0;                                         // slices requested of either operand
+        // (no branch) past the end the last slice is requested again, into stages nobody reads any more
+        auto request_a = [&](int st) {
+            if constexpr (RAG) pa.issue_rag(rag_rsrc(a_at, a_left), kl + min(qa, nk - 1) == nk_seg - 1, smem + st * A_BYTES, wave);
+            else pa.issue(a_tile, a_off, smem + st * A_BYTES, wave);
+            ++qa;
+            a_off += qa < nk ? a_step : 0u;
+            if constexpr (RAG) rag_move(qa < nk ? a_step : 0u, 0);
+        };
+        auto request_b = [&](int st) {
+            if constexpr (RAG) pb.issue_rag(rag_rsrc(b_at, b_left), kl + min(qb, nk - 1) == nk_seg - 1, b_stages + st * B_BYTES, wave);
+            else pb.issue(b_tile, b_off, b_stages + st * B_BYTES, wave);
+            ++qb;
+            b_off += qb < nk ? b_step : 0u;
+            if constexpr (RAG) rag_move(0, qb < nk ? b_step : 0u);
+        };
+        request_a(0);
+        request_b(0);
+        request_a(1);
+        request_b(1);
+        BP_WAIT_VMCNT(LA + LB);                                     // slice 0 has landed
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        read_step2(smem, b_stages, 0, 0);
+        int ca = 0, cb = 0;                                         // stages of slice kt
+        for (int kt = 0; kt < nk; ++kt) {
+            const int na = ca == 2 ? 0 : ca + 1;
+            request_a(ca == 0 ? 2 : ca - 1);
+            read_step2(smem + ca * A_BYTES, b_stages + cb * B_BYTES, 1, 1);
+            mfma_step(0);
+            SchedRounds<0, NMFMA, NREAD, LA, LA>::apply();
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0)
+            BP_WAIT_VMCNT(LA);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            request_b(cb);
+            read_step2(smem + na * A_BYTES, b_stages + (cb ^ 1) * B_BYTES, 0, 0);
+            mfma_step(1);
+            SchedRounds<0, NMFMA, NREAD, LB, LB>::apply();
+            ca = na;
+            cb ^= 1;
         }
     } else {
 #pragma unroll
@@ -948,11 +1009,13 @@ static hipError_t launch_dma_rag(const GemmArgs& g, hipStream_t s, int splits, i
     else if (n_full < 0) n_full = 0;                    // every tile is cut along K
     const int n_tail = nblk - n_full;
     const dim3 grid(n_full + n_tail * splits), block(WM * WN * 64);
-    const size_t stages = RING ? (size_t)5 * (BM + BN) * 32 * 2 : (size_t)NS * (BM + BN) * BKT * 2;
-    const size_t epilogue = (size_t)WM * WN * 32 * (BN / WN + 8) * sizeof(float);
-    const size_t smem = stages > epilogue ? stages : epilogue;
+    constexpr size_t epilogue = (size_t)WM * WN * 32 * (BN / WN + 8) * sizeof(float);
 #define BP_GEMM_LAUNCH(AR, BR)                                                                   \
     do {                                                                                         \
+        constexpr size_t stages = RING ? (size_t)5 * (BM + BN) * 32 * 2                          \
+                                  : staggered<NS, MI16, RING>(AR, BR) ? (size_t)(3 * BM + 2 * BN) * BKT * 2 \
+                                                                      : (size_t)NS * (BM + BN) * BKT * 2;   \
+        constexpr size_t smem = stages > epilogue ? stages : epilogue;                           \
         auto kern = gemm_dma_kernel<BM, BN, WM, WN, BKT, NS, AR, BR, MI16, RING, RAG>;                    \
         static std::atomic<bool> attr_set{false};   /* once per instantiation; host threads may race */ \
         if (smem > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {                                                     \
@@ -1017,12 +1080,10 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
     const bool dma = dma_path_ok(g);
     if (g.epi != EPI_NONE && !gemm_can_fuse_epilogue(BF16, g)) return hipErrorInvalidValue;
-    if (!dma) {
-        if (g.nseg == 1) return launch_cfg<128, 128, 2, 2, true>(g, s);
-        return launch_gemm_per_segment(g, s, [](const GemmArgs& h, hipStream_t st) {
-            return launch_cfg<128, 128, 2, 2, true>(h, st);
-        });
-    }
+    // (several segments come as weight gradients; the forward form's large tiles walk through one)
+    if (g.nseg > 1 && (!dma || (!g.a_t && g.b_t)))
+        return launch_gemm_per_segment(g, s, [](const GemmArgs& h, hipStream_t st) { return launch_gemm_mfma(h, st); });
+    if (!dma) return launch_cfg<128, 128, 2, 2, true>(g, s);
     const int ncu = cu_count();
     const long k_total = (long)g.K * g.nseg;
     const long most = 3L * ncu / 4;       // a launch with at least this many blocks is taken to fill the chip

@@ -80,6 +80,16 @@ def test_gemm_edge_tiles(form, M, N, K):
     test_gemm_forms(M, N, K, form, "bf16")
 
 
+# Large forward-form tiles (256 x 256 and 256 x 192 wide), whose operands are requested half a slice apart
+# into three and two LDS stages: fewer slices than stages, every phase of the 3 x 2 stage cycle at the end.
+@pytest.mark.parametrize("M,N,K", [
+    (1024, 12288, 64), (1024, 12288, 128), (1024, 12288, 192), (1024, 12288, 256), (1024, 12288, 448),
+    (2048, 6144, 64), (2048, 6144, 320), (2048, 6144, 384), (4000, 3200, 8), (4000, 3200, 264), (1000, 9600, 328),
+])
+def test_gemm_large_tiles_few_slices(M, N, K):
+    test_gemm_forms(M, N, K, "dgrad", "bf16")
+
+
 # fp32 kernel: both tile widths, one element past a tile, the shortest K, K tails of four, unaligned rows
 # (the generic kernel); 1e-5 relative to the largest element bounds fp32 sums of this length
 @pytest.mark.parametrize("form,M,N,K", [
