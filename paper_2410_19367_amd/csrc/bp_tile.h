@@ -42,10 +42,16 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
     if (nblk % 8 == 0) t = (t & 7) * (nblk >> 3) + (t >> 3);
     constexpr int GM = 4;
     const int per_group = GM * tiles_n;
-    const int first_m = (t / per_group) * GM;
-    const int gsize = min(tiles_m - first_m, GM);
-    tm = first_m + (t % per_group) % gsize;
-    tn = (t % per_group) / gsize;
+    const int group = t / per_group, in_group = t - group * per_group;
+    const int first_m = group * GM;
+    const int gsize = tiles_m - first_m;
+    if (gsize >= GM) {          // a full group: no second division on the way to a block's first load
+        tm = first_m + in_group % GM;
+        tn = in_group / GM;
+    } else {
+        tn = in_group / gsize;
+        tm = first_m + in_group - tn * gsize;
+    }
 }
 
 }  // namespace bp
