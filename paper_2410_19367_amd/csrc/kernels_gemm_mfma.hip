@@ -762,7 +762,10 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     wait_slices(min(nk, NS - 1) - 1);                   // slice 0 has landed
     __builtin_amdgcn_s_barrier();                       // (bare: __syncthreads() would wait for the others too)
     __builtin_amdgcn_sched_barrier(0);
-    if (NS - 1 < nk) {
+    // (with nk == NS - 1 the last slice again, into a stage nobody reads: the waits below count on NS - 2
+    // younger requests behind the slice they need)
+    static_assert(RING || AHEAD || NS <= 3, "one request behind the barrier keeps the count for up to three stages");
+    if (nk > 1) {
         issue_slice(smem + (NS - 1) * STAGE, kl);
         advance();
     }
