@@ -90,6 +90,18 @@ def test_gemm_large_tiles_few_slices(M, N, K):
     test_gemm_forms(M, N, K, "dgrad", "bf16")
 
 
+# Small outputs: 64 x 64 tiles (slices of 128 along K), 128 x 64 and 128 x 128 tiles (slices of 64), each with one
+# slice, fewer slices than LDS stages, and one more; the limits between the tiles; edges of 64.
+@pytest.mark.parametrize("form,M,N,K", [
+    ("dgrad", 384, 256, 128), ("dgrad", 384, 256, 256), ("dgrad", 384, 768, 384), ("dgrad", 1024, 1024, 512),
+    ("dgrad", 1024, 1088, 64), ("dgrad", 1024, 2048, 128), ("dgrad", 1024, 2048, 192), ("dgrad", 1024, 2112, 128),
+    ("dgrad", 1000, 4800, 136), ("dgrad", 63, 72, 136), ("dgrad", 65, 136, 264), ("dgrad", 1001, 1608, 72),
+    ("wgrad", 256, 192, 384), ("wgrad", 72, 328, 129), ("wgrad", 1024, 1024, 250),
+])
+def test_gemm_small_tiles(form, M, N, K):
+    test_gemm_forms(M, N, K, form, "bf16")
+
+
 # fp32 kernel: both tile widths, one element past a tile, the shortest K, K tails of four, unaligned rows
 # (the generic kernel); 1e-5 relative to the largest element bounds fp32 sums of this length
 @pytest.mark.parametrize("form,M,N,K", [
