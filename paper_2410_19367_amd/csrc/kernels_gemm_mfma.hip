@@ -333,8 +333,10 @@ __device__ __forceinline__ bf16x8 read_frag16(const char* lds, int row0, int kk,
 }
 
 // the forward / data-gradient form of the large tiles: its operands have LDS stages of their own
-template <int NS, bool MI16, bool RING>
-constexpr bool staggered(bool a_rmajor, bool b_rmajor) { return NS == 2 && MI16 && !RING && !a_rmajor && !b_rmajor; }
+template <int NS, int BKT, bool MI16, bool RING>
+constexpr bool staggered(bool a_rmajor, bool b_rmajor) {
+    return NS == 2 && BKT == 64 && MI16 && !RING && !a_rmajor && !b_rmajor;
+}
 
 constexpr int rows_per_instr(int lanes_per_row) {
     int r = 1;
@@ -390,7 +392,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     constexpr int NW = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int A_BYTES = BM * BKT * 2, B_BYTES = BN * BKT * 2, STAGE = A_BYTES + B_BYTES;
-    constexpr bool AHEAD = staggered<NS, MI16, RING>(A_RMAJOR, B_RMAJOR);
+    constexpr bool AHEAD = staggered<NS, BKT, MI16, RING>(A_RMAJOR, B_RMAJOR);
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     // Every argument in one round trip: they sit in memory that is cold at each launch, and left alone the
@@ -981,6 +983,8 @@ template <int BM, int BN, bool RAG>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, int splits, int tiles_m, int tiles_n,
                                                             int n_full) {
     constexpr int BPT = BM * BN / 2048;                 // blocks per tile
+    asm volatile("" ::"s"(g.M), "s"(g.N), "s"(g.ldc), "s"(g.C), "s"(g.bias), "s"(g.residual), "s"(g.accumulate),
+                 "s"(g.split_ws), "s"(splits), "s"(tiles_m), "s"(tiles_n), "s"(n_full));
     const int tail_idx = blockIdx.x / BPT;
     int tm, tn;
     tile_coords(n_full + tail_idx, tiles_m, tiles_n, tm, tn);
@@ -1034,7 +1038,7 @@ static hipError_t launch_dma_rag(const GemmArgs& g, hipStream_t s, int splits, i
 #define BP_GEMM_LAUNCH(AR, BR)                                                                   \
     do {                                                                                         \
         constexpr size_t stages = RING ? (size_t)5 * (BM + BN) * 32 * 2                          \
-                                  : staggered<NS, MI16, RING>(AR, BR) ? (size_t)(3 * BM + 2 * BN) * BKT * 2 \
+                                  : staggered<NS, BKT, MI16, RING>(AR, BR) ? (size_t)(3 * BM + 2 * BN) * BKT * 2 \
                                                                       : (size_t)NS * (BM + BN) * BKT * 2;   \
         constexpr size_t smem = stages > epilogue ? stages : epilogue;                           \
         auto kern = gemm_dma_kernel<BM, BN, WM, WN, BKT, NS, AR, BR, MI16, RING, RAG>;                    \
@@ -1120,16 +1124,12 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     const long t192 = g.N % 192 == 0 || (!aligned256 && useful(256, 192) >= 0.85) ? tiles(256, 192) : 0;
     // (the fused GELU-backward epilogue folds column sums over power-of-two lane groups: not 96 wide)
     // The 192-wide tile has fewer MFMAs per LDS read and per barrier: measured against the 256-wide
-    // one at equal fill it runs at about 0.85 of its rate for weight gradients with a long contraction
-    // (both operands through the transpose path, no ring) and for the forward / data-gradient form
+    // one at equal fill it runs at about 0.85 of its rate for the forward / data-gradient form
     // (2048 x 6144 x 2048: 44.5 us against 46.0 us on three quarters of the CUs; 4096 x 15360 x 5120:
-    // 543 us against 494 us at a fill of 0.94), else within 5 %.
+    // 543 us against 494 us at a fill of 0.94), else within 5 % (weight gradients with a long contraction:
+    // below).
     const bool nt = !g.a_t && g.b_t;
-    const double rate192 = ((g.a_t && !g.b_t && (long)g.K * g.nseg >= 4096) || nt) ? 0.85 : 0.95;
-    if (g.epi == EPI_NONE && t192 >= most && rate192 * fill(t192) * useful(256, 192) > fill(t256) * useful(256, 256)) {
-        if (nt) return launch_dma<256, 192, 2, 4, 2, 64, true>(g, s);
-        return launch_dma<256, 192, 4, 2, 2>(g, s);
-    }
+    const double rate192 = nt ? 0.85 : 0.95;
     // How many K slices the last, partly filled round of 256 x 256 tiles is cut into so that it fills
     // the chip too (at most 4, each at least 1024 deep so that the fp32 partials stay a small part of
     // the traffic; the slices need not be equal).  With fewer tiles than CUs this is plain split-K.
@@ -1139,6 +1139,28 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
         while (splits > 1 && (k_total / splits < 1024 || (size_t)splits * tail * 65536 > g.split_ws_elems)) --splits;
         return splits;
     };
+    // Weight gradients with a long contraction: the five-slot ring on 256 x 256 tiles wherever it occupies
+    // half of the CUs, cut along K or not, and of what its edge tiles compute at most a quarter is
+    // padding.  It is so much faster than the 256 x 192 tile (no ring) that the latter, which fills
+    // the chip better at 133 .. 192 tiles, loses even there: a round of it takes 0.75 / 0.69 of a
+    // round of whole tiles (1600 x 4800 x 8000 185 -> 160 us, 2048 x 6144 x 16384 425 -> 391 us,
+    // 1920 x 5760 x 8192 181 -> 166 us); and half the chip of large tiles on K slices beats twice as many
+    // 128 x 128 tiles (3072 x 768 x 15984 167 -> 96 us, 1600 x 1600 x 8000 89 -> 70 us).
+    const bool wgrad = g.a_t && !g.b_t;
+    if (wgrad && k_total >= 4096 && useful(256, 256) >= 0.75) {
+        const long all = tiles(256, 256), full = all / ncu * ncu, tail = all - full;
+        const int splits = g.split_ws ? tail_splits(tail) : 1;
+        const double rounds = (double)(full / ncu) + (tail ? 1.0 / splits : 0.0);
+        const double rounds192 = t192 >= most ? (double)((t192 + ncu - 1) / ncu) * 0.75 / 0.69 : 1e9;
+        if ((full || 2 * tail * splits >= ncu) && rounds <= rounds192) {
+            if (splits > 1) return launch_dma<256, 256, 2, 4, 5, 64, true, true>(g, s, splits, (int)full);
+            return launch_dma<256, 256, 2, 4, 5, 64, true, true>(g, s);
+        }
+    }
+    if (g.epi == EPI_NONE && t192 >= most && rate192 * fill(t192) * useful(256, 192) > fill(t256) * useful(256, 256)) {
+        if (nt) return launch_dma<256, 192, 2, 4, 2, 64, true>(g, s);
+        return launch_dma<256, 192, 4, 2, 2>(g, s);
+    }
     if (t256 >= most) {
         const long full = (t256 / ncu) * ncu, tail = t256 - full;
         const int splits =
@@ -1161,10 +1183,25 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     // 229 us against 115 us).
     // Not for weight gradients either: with both operands read through the transpose path the small
     // tiles lose more than the partials cost (2560 x 2560 x 16384: 334 us against 272 us).
-    const long t128 = tiles(128, 128);
+    const long t128 = tiles(128, 128), t64 = tiles(64, 64);
+    // Small outputs.  What a block takes there is its chain of slices, each a barrier and a load latency, so
+    // smaller tiles (fewer MFMAs per slice, more blocks) win although they move more operand bytes.
+    // Forward / data-gradient form, 128 x 128 tiles (cut along K where that applied) against
+    //   64 x 64, three stages of 128 along K, while every CU gets at most one block:
+    //     384 x 768 x 256 5.8 -> 4.0 us, 1024^3 10.1 -> 6.6 us, 1024 x 1024 x 4096 27.4 -> 16.0 us;
+    //   128 x 64, three stages of 64 (72 KB: two blocks per CU), while two of 64 x 64 would fit a CU:
+    //     1000 x 1600 x 6400 45.4 -> 34.8 us, 1024 x 2048 x 8192 49.6 -> 41.8 us.
+    // Not beyond: 768 x 3072 x 768 9.2 -> 10.2 us; and where 128 x 128 tiles start a second round that stays
+    // less than half full a warm loop gains 5 % (6144 x 1024 x 1024), the stage loses 1 %.
+    // Weight gradients with a short contraction, 128 x 128 against 64 x 64 tiles: 256 x 1024 x 1536
+    // 15.7 -> 9.7 us, 1024 x 1024 x 2048 20.4 -> 12.5 us; longer ones are better off cut along K.
+    if (nt && t64 <= ncu) return launch_dma<64, 64, 2, 2, 3, 128, true>(g, s);
+    if (nt && t64 <= 2L * ncu)
+        return launch_dma<128, 64, 2, 2, 3, 64, true>(g, s);
+    if (wgrad && t64 <= ncu && k_total <= 2048) return launch_dma<64, 64, 2, 2, 3, 128, true>(g, s);
     const bool deep = g.K % 128 == 0 || (g.K % BK != 0 && g.K > 512);   // slices of 128 along K
     const bool small_fill = t128 >= most && (k_total <= 4096 || (nt && k_total <= 8192 && fill(t128) >= 0.95));
-    if (small_fill && !(g.a_t && !g.b_t)) {
+    if (small_fill && !wgrad) {
         if (nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s);
         if (deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s);
         return launch_dma<128, 128, 2, 4, 2>(g, s);
@@ -1184,15 +1221,13 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
         int splits = (int)(ncu / t128);
         if (splits > 4) splits = 4;
         while (splits > 1 && (k_total / splits < 1024 || (size_t)splits * t128 * 16384 > g.split_ws_elems)) --splits;
-        if (splits > 1 && nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s, splits, 0);
         if (splits > 1 && deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s, splits, 0);
         if (splits > 1) return launch_dma<128, 128, 2, 4, 2>(g, s, splits, 0);
     }
-    // 8 waves (2 per SIMD) hide the LDS and load latencies better than 4 on these small tiles.
+    // 8 waves (2 per SIMD) hide the LDS and load latencies better than 4 on 128 x 128 tiles.
     // Forward / data-gradient form: 16x16x32 MFMAs and loads first, as on the large tiles, and three
     // stages of 64 along K (96 KB), so that a slice has two barriers to land (against two stages of
-    // 128: 2048^3 20.7 us against 21.9 us, 2048 x 2048 x 8192 63.7 us against 67.9 us, 1024 x 1024 x
-    // 4096 27.9 us against 31.8 us).  The other forms: slices of 128 along K (two stages of 64 KB),
+    // 128: 2048^3 20.7 us against 21.9 us, 2048 x 2048 x 8192 63.7 us against 67.9 us).  The other forms: slices of 128 along K (two stages of 64 KB),
     // which halve the number of barriers per MFMA.
     if (nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s);
     if (deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s);
