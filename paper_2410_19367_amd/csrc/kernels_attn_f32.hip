@@ -132,6 +132,7 @@ __device__ __forceinline__ void f32_block(const AttnArgs& a, bool last_is_heavy,
 
 template <int D, int DC>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(AttnArgs a, float scale) {
+    attn_args_now(a, scale);
     constexpr int KS = DC / 8, DT = DC / 32, TILE = 64 * D * 4, STAGE = 2 * TILE;    // K then V
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, h = lane >> 5;
@@ -244,6 +245,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
 // dQ, and delta[q] = sum_d dO[q][d] O[q][d] for the dK/dV kernel
 template <int D, int DC>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(AttnArgs a, float scale) {
+    attn_args_now(a, scale);
     constexpr int KS = DC / 8, DT = DC / 32, TILE = 64 * D * 4, STAGE = 2 * TILE;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, h = lane >> 5;
@@ -332,6 +334,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(A
 // dK and dV: 32 keys per wave, one half of every 64-query tile of Q and dO that streams by
 template <int D, int DC>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(AttnArgs a, float scale) {
+    attn_args_now(a, scale);
     constexpr int KS = DC / 8, DT = DC / 32, TILE = 64 * D * 4, STAGE = 2 * TILE + 512;   // Q, dO, lse[64], delta[64]
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, h = lane >> 5;

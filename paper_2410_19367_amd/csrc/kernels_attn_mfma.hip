@@ -174,6 +174,7 @@ __device__ __forceinline__ void block_coords(int nblk, int heads, bool causal, b
 // one row per block: 8 micro-batches of 2 layers with H = 1600, S = 1000, B = 1: 46.7 ms, now 16.0 ms.)
 template <int D, int DR, int NT, bool RAG>
 __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kernel(AttnArgs a, float scale) {
+    attn_args_now(a, scale);
     constexpr int NW = 4 * NT, NSUB = 2 * NT, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = NT * 2 * TILE;   // per tile: K then V
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -356,6 +357,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
 // =====================================================================================
 template <int D, int DR, bool RAG>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, float scale) {
+    attn_args_now(a, scale);
     constexpr int NW = 4, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -498,6 +500,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
 // =====================================================================================
 template <int D, int DR, bool RAG>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, float scale) {
+    attn_args_now(a, scale);
     constexpr int NW = 4, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE + 512;   // Q, dO, then lse[64], delta[64]
     extern __shared__ __attribute__((aligned(16))) char smem[];

@@ -65,6 +65,11 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
     constexpr int A_BYTES = BM * BK * 4, STAGE = (BM + BN) * BK * 4;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
+    const void *A0 = g.A, *B0 = g.B;        // every argument in one round trip
+    asm volatile("" : "+s"(A0), "+s"(B0)
+                 : "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc), "s"(g.nseg), "s"(g.C),
+                   "s"(g.bias), "s"(g.residual), "s"(g.accumulate), "s"(g.epi), "s"(g.C2), "s"(g.U), "s"(g.colpart),
+                   "s"(tiles_m), "s"(tiles_n));
     int tm, tn;
     tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
@@ -86,8 +91,10 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
     long a_left, b_left;                    // bytes from there to the operand's end
     int seg = 0, kl = 0;
     auto origin = [&]() {
-        a_at = (const char*)((const float*)(seg == 0 ? g.A : g.A_more[seg - 1]) + (A_RMAJOR ? m0 : (size_t)m0 * g.lda));
-        b_at = (const char*)((const float*)(seg == 0 ? g.B : g.B_more[seg - 1]) + (B_RMAJOR ? n0 : (size_t)n0 * g.ldb));
+        const void *A = A0, *B = B0;
+        if (seg > 0) { A = g.A_more[seg - 1]; B = g.B_more[seg - 1]; }
+        a_at = (const char*)((const float*)A + (A_RMAJOR ? m0 : (size_t)m0 * g.lda));
+        b_at = (const char*)((const float*)B + (B_RMAJOR ? n0 : (size_t)n0 * g.ldb));
         a_left = 4L * (A_RMAJOR ? (g.K - 1) * (long)g.lda + g.M - m0 : (g.M - m0 - 1) * (long)g.lda + g.K);
         b_left = 4L * (B_RMAJOR ? (g.K - 1) * (long)g.ldb + g.N - n0 : (g.N - n0 - 1) * (long)g.ldb + g.K);
     };

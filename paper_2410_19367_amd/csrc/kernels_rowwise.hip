@@ -7,6 +7,12 @@
 
 namespace bp {
 
+// The LayerNorm kernels last a few microseconds, most of it one memory latency after another, so they ask
+// for everything at once: the arguments (an empty asm that names them: the compiler otherwise loads each
+// where it is used, and they are cold at every launch), and the row vectors up to this many passes
+// (H <= 2048; beyond that the registers cost more than the latency).
+constexpr int kEarlyPasses = 4;
+
 // ------------------------------------------------------------------ LayerNorm forward
 // One 64-lane wave per row; the row lives in registers (NP passes of 64 lanes x 8 columns).
 template <typename T, int NP>
@@ -16,17 +22,25 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x,
                                                      T* __restrict__ out, float* __restrict__ mean,
                                                      float* __restrict__ rstd, T* __restrict__ xcopy,
                                                      int rows, int H, float eps) {
+    asm volatile("" ::"s"(x), "s"(gamma), "s"(beta), "s"(out), "s"(mean), "s"(rstd), "s"(xcopy), "s"(rows), "s"(H),
+                 "s"(eps));
     const int lane = threadIdx.x & 63;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
     const T* xr = x + (size_t)row * H;
     float v[NP][8];
+    constexpr bool EARLY = NP <= kEarlyPasses;
+    float ge[EARLY ? NP : 1][8], be[EARLY ? NP : 1][8];
     float s = 0.f;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const int col = (p * 64 + lane) * 8;
         if (col < H) {
             load8(xr + col, v[p]);
+            if constexpr (EARLY) {
+                load8(gamma + col, ge[p]);
+                load8(beta + col, be[p]);
+            }
             if (xcopy) store8(xcopy + (size_t)row * H + col, v[p]);
 #pragma unroll
             for (int i = 0; i < 8; ++i) s += v[p][i];
@@ -52,10 +66,13 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x,
         const int col = (p * 64 + lane) * 8;
         if (col < H) {
             float g[8], b[8], o[8];
-            load8(gamma + col, g);
-            load8(beta + col, b);
+            if constexpr (!EARLY) {
+                load8(gamma + col, g);
+                load8(beta + col, b);
+            }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) o[i] = (v[p][i] - mu) * rs * g[i] + b[i];
+            for (int i = 0; i < 8; ++i)
+                o[i] = (v[p][i] - mu) * rs * (EARLY ? ge[EARLY ? p : 0][i] : g[i]) + (EARLY ? be[EARLY ? p : 0][i] : b[i]);
             store8(out + (size_t)row * H + col, o);
         }
     }
@@ -71,6 +88,7 @@ __global__ __launch_bounds__(256) void ln_bwd_rows_kernel(const T* __restrict__ 
                                                           const float* __restrict__ gamma,
                                                           const T* __restrict__ res,
                                                           T* __restrict__ dx, int rows, int H) {
+    asm volatile("" ::"s"(dout), "s"(x), "s"(mean), "s"(rstd), "s"(gamma), "s"(res), "s"(dx), "s"(rows), "s"(H));
     const int lane = threadIdx.x & 63;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
@@ -196,29 +214,41 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(ColsumBatch batch, 
 
 // out_k[c] += (or =, for a batch marked overwrite) sum over chunks of part[chunk][k][c].  Block = 64 columns x 4 chunk slices.
 __global__ __launch_bounds__(256) void colsum_final_kernel(ColsumBatch batch, int chunks) {
-    __shared__ float red[4][64];
+    __shared__ float red[2][4][64];
     const ColsumJob job = batch.jobs[blockIdx.y];
     const int N = job.N;
     if (blockIdx.x * 64 >= N || !job.part) return;
     const int nout = job.out_ax ? 2 : 1;
     const int cl = threadIdx.x & 63, slice = threadIdx.x >> 6;
     const int c = blockIdx.x * 64 + cl;
-    for (int o = 0; o < nout; ++o) {
-        float s = 0.f;
-        if (c < N) {
-            // 16 loads in flight per thread (the additions keep their order): with 4 the kernel
-            // spends its time waiting for one memory latency after the other
-#pragma unroll 16
-            for (int k = slice; k < chunks; k += 4) s += job.part[((size_t)k * nout + o) * N + c];
+    // Both sums at once, 8 chunks of each in flight per thread whatever their number (the additions
+    // keep their order): a loop that waits for one chunk after the other took 10 us for the 32 chunks of
+    // 1024 tokens.
+    float s[2] = {0.f, 0.f};
+    if (c < N) {
+        const float* part = job.part + c;
+        for (int k0 = slice; k0 < chunks; k0 += 32) {
+            float v[2][8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int k = k0 + 4 * j;
+                v[0][j] = k < chunks ? part[(size_t)k * nout * N] : 0.f;
+                v[1][j] = k < chunks && nout == 2 ? part[((size_t)k * 2 + 1) * N] : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                s[0] += v[0][j];
+                s[1] += v[1][j];
+            }
         }
-        red[slice][cl] = s;
-        __syncthreads();
-        if (slice == 0 && c < N) {
-            float* out = o == 0 ? job.out_a : job.out_ax;
-            const float v = (red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl]);
-            out[c] = batch.overwrite ? v : out[c] + v;
-        }
-        __syncthreads();
+    }
+    red[0][slice][cl] = s[0];
+    red[1][slice][cl] = s[1];
+    __syncthreads();
+    if (slice < nout && c < N) {
+        float* out = slice == 0 ? job.out_a : job.out_ax;
+        const float v = (red[slice][0][cl] + red[slice][1][cl]) + (red[slice][2][cl] + red[slice][3][cl]);
+        out[c] = batch.overwrite ? v : out[c] + v;
     }
 }
 
