@@ -133,7 +133,10 @@ int bp_stage_set_param(bp_stage_t* st, int chunk, int layer, int tensor_id,
                        const float* host_f32, size_t n);
 
 /* Copy one fp32 gradient accumulator to the host (n must equal the tensor's size).
- * Synchronises the stream first.  After bp_run_schedule the two directions are already summed. */
+ * Completes the open weight-gradient groups, waits for all forwards and data gradients enqueued so far and for
+ * every contribution to this tensor; weight gradients of other tensors may still be running when it returns
+ * (reading the tensors in the order layer 0 first, ids ascending, overlaps them with the copies best).
+ * After bp_run_schedule the two directions are already summed. */
 int bp_stage_get_grad(bp_stage_t* st, int chunk, int layer, int tensor_id,
                       float* host_f32, size_t n);
 

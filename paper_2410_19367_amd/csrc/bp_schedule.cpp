@@ -442,6 +442,10 @@ int Stage::run_schedule(const Layout& L, const bp_op* order, int n_ops, int D, c
     // an order may keep every (stage, mb) stashed at once; slots get memory only when used
     if (slot_capacity < n_stage * N) slot_capacity = n_stage * N;
 
+    // gradients of earlier stage calls may still be on their way (get_grad waits for one tensor only), and
+    // the lanes write the same buffers from streams of their own
+    if (side && hipStreamSynchronize(side) != hipSuccess) return fail(BP_EHIP, "synchronise before the iteration");
+    forget_ready();
     if ((rc = zero_grad())) return rc;
     // A weight-gradient group that the iteration cannot fill would only be flushed at the end, with
     // nothing left to overlap it: no group larger than the backward calls a (direction, stage) gets.

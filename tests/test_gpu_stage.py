@@ -103,6 +103,36 @@ def test_forward_ahead_any_lead_gives_the_same_bits(seed):
         assert np.array_equal(grads_a[k], grads_b[k]), k
 
 
+@pytest.mark.parametrize("n_micro,wgrad_group,stash_recompute", [(4, 4, 0), (8, 4, 0), (5, 2, 0), (3, 1, 0), (4, 4, 1)])
+@pytest.mark.parametrize("backwards", [False, True])
+def test_gradients_read_while_others_are_computed(n_micro, wgrad_group, stash_recompute, backwards):
+    """bp_stage_get_grad waits for the tensor it copies and not for the weight-gradient GEMMs behind it: read
+    right after the last call, in either order of the tensors, on two chunks and two iterations, every
+    gradient has the bits that it has after a device synchronisation."""
+    import torch
+    cfg = si.scaled(si.CONFIGS[1], name="read_early", layers=2, hidden=1024, heads=8, seq=256, microbatch=4, causal=True,
+                    n_chunks=2, n_micro=n_micro)
+    params = si.make_params(cfg, 0, 0.1)
+    xs = [hz.to_dev(si.make_activation(cfg, "act_in", mb, 0), cfg.dtype) for mb in range(n_micro)]
+    gs = [hz.to_dev(si.make_activation(cfg, "grad_out", mb, 0), cfg.dtype) for mb in range(n_micro)]
+    names = [(c, l, n) for c in range(2) for l in range(cfg.layers) for n in si.PARAM_NAMES]
+    if backwards:
+        names = names[::-1]
+    with hz.GpuStage(cfg, max_inflight=2, wgrad_group=wgrad_group, stash_recompute=stash_recompute) as g:
+        g.load_params(params)
+        for it in range(2):
+            g.bp.bp_stage_zero_grad(g.h)
+            for mb in range(n_micro):
+                for c in (0, 1):
+                    g.forward(c, mb, xs[mb])
+                for c in (0, 1):
+                    g.backward(c, mb, gs[mb])
+            early = {k: g.grad(*k) for k in names}
+            torch.cuda.synchronize()
+            for k in names:
+                assert np.array_equal(early[k], g.grad(*k)), (it, k)
+
+
 def test_small_fp32_bert_padded():
     cfg = si.scaled(si.CONFIGS[0], name="small_f32_bert", causal=False, len_lo=10, len_hi=64,
                     microbatch=3, n_micro=2)
