@@ -1,4 +1,5 @@
-// Fused attention on the gfx950 matrix cores (bf16 inputs, fp32 softmax and accumulation):
+// Fused attention on the gfx950 matrix cores (bf16 inputs, fp32 softmax and accumulation; P and dS enter their
+// second product in bf16 where the sequence length is a multiple of 64, else in fp32):
 // forward with online softmax, and the backward as two deterministic kernels (dQ; dK and dV).
 //
 // All three kernels stream [64 rows][D] tiles of the packed qkv / dctx tensors through LDS with
@@ -133,6 +134,56 @@ __device__ __forceinline__ bf16x8 acc_to_b(const f32x16& a, int half) {
     return r;
 }
 
+// The same registers as three bf16 operands whose sum they are: 24 significant bits cut into 8 + 8 + 8.
+struct Split8 { bf16x8 part[3]; };
+__device__ __forceinline__ Split8 acc_to_b3(const f32x16& a, int half) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    float r[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = a[8 * half + e];
+    Split8 o;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        u32x4 w;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const uint32_t u0 = __builtin_bit_cast(uint32_t, r[e]), u1 = __builtin_bit_cast(uint32_t, r[e + 1]);
+            w[e / 2] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);      // the upper halves of both
+            r[e] -= __builtin_bit_cast(float, u0 & 0xffff0000u);        // exact
+            r[e + 1] -= __builtin_bit_cast(float, u1 & 0xffff0000u);
+        }
+        o.part[i] = __builtin_bit_cast(bf16x8, w);
+    }
+    return o;
+}
+
+// out^T (D x 32) += tile[row0 .. row0 + 31]^T x, x as a score accumulator holds it (P or dS).  EXACT keeps x in
+// fp32: three products with its bf16 parts, the smallest first, in place of one with its rounded value.
+template <int D, int DT, bool EXACT>
+__device__ __forceinline__ void contract(const char* tile, int row0, int lane, int dr, const f32x16& x, f32x16 (&out)[DT]) {
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+        if constexpr (EXACT) {
+            const Split8 xb = acc_to_b3(x, s2);
+#pragma unroll
+            for (int t2 = 0; t2 < DT; ++t2) {
+                if (32 * t2 >= dr) continue;
+                const bf16x8 f = frag_cols<D>(tile, row0 + 16 * s2, t2 * 32, lane);
+#pragma unroll
+                for (int i = 2; i >= 0; --i)
+                    out[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, xb.part[i], out[t2], 0, 0, 0);
+            }
+        } else {
+            const bf16x8 xb = acc_to_b(x, s2);
+#pragma unroll
+            for (int t2 = 0; t2 < DT; ++t2)
+                if (32 * t2 < dr)
+                    out[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        frag_cols<D>(tile, row0 + 16 * s2, t2 * 32, lane), xb, out[t2], 0, 0, 0);
+        }
+    }
+}
+
 // row index inside a 32-row accumulator tile held in register v by a lane of half h
 __device__ __forceinline__ int acc_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
 
@@ -171,7 +222,11 @@ __device__ __forceinline__ void block_coords(int nblk, int heads, bool causal, b
 // then partly filled: tile rows past the end are zeros, keys past the end are masked like padded
 // ones, queries past the end repeat the last one and are not stored.  (The guards cost a branch per
 // tile, so multiples of 64 keep kernels without them.  Before, such lengths went to the kernels of
-// one row per block: 8 micro-batches of 2 layers with H = 1600, S = 1000, B = 1: 46.7 ms, now 16.0 ms.)
+// one row per block: 8 micro-batches of 2 layers with H = 1600, S = 1000, B = 1: 46.7 ms, now 16.0 ms.
+// Those kernels kept P and dS in fp32, and these lengths still do: each goes into the second product as three
+// bf16 parts that add up to it exactly.  Against one product with the rounded value: forward B 3, S 2550,
+// 12 heads of 64, causal 55 -> 79 us, backward B 2, S 1058, 32 heads of 128 237 -> 340 us, 5 - 20 % below S 300;
+// the kernels of one row per block take ten times as long.)
 template <int D, int DR, int NT, bool RAG>
 __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kernel(AttnArgs a, float scale) {
     attn_args_now(a, scale);
@@ -288,15 +343,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
         }
         lsum += ps;
         // O^T (D x 32 queries) += V^T P^T over this wave's 32 keys
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            const bf16x8 pb = acc_to_b(st2, s2);
-#pragma unroll
-            for (int t2 = 0; t2 < DT; ++t2)
-                if (32 * t2 < dr)
-                    ot[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        frag_cols<D>(sv, 32 * kh + 16 * s2, t2 * 32, lane), pb, ot[t2], 0, 0, 0);
-        }
+        contract<D, DT, RAG>(sv, 32 * kh, lane, dr, st2, ot);
     }
 
     // merge the key sub-ranges: waves 1 .. NSUB-1 of a query group hand (m, l, O^T) to wave 0 through LDS
@@ -455,15 +502,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
             }
             dp[v] = p * (dp[v] - delta);            // dS^T
         }
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            const bf16x8 db = acc_to_b(dp, s2);
-#pragma unroll
-            for (int t2 = 0; t2 < DT; ++t2)
-                if (32 * t2 < dr)
-                    dq[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        frag_cols<D>(sk, 32 * kh + 16 * s2, t2 * 32, lane), db, dq[t2], 0, 0, 0);
-        }
+        contract<D, DT, RAG>(sk, 32 * kh, lane, dr, dp, dq);
     }
     __syncthreads();
     float* xo = (float*)smem + qg * (DT * 16 * 64);
@@ -628,6 +667,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             sacc[v] = p;                                 // P
             dp[v] = p * (dp[v] - s_dlt[qi]);             // dS
         }
+        if constexpr (RAG) {
+            contract<D, DT, true>(sdo, 32 * qh, lane, dr, sacc, dv);
+            contract<D, DT, true>(sq, 32 * qh, lane, dr, dp, dk);
+        } else {
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
             const bf16x8 pb = acc_to_b(sacc, s2);
@@ -640,6 +683,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
                 dk[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     frag_cols<D>(sq, 32 * qh + 16 * s2, t2 * 32, lane), db, dk[t2], 0, 0, 0);
             }
+        }
         }
     }
     __syncthreads();
