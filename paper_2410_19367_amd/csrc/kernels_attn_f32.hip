@@ -31,7 +31,8 @@ template <int D> __device__ __forceinline__ int f32_tile_off(int row, int chunk)
     return row * (D * 4) + ((chunk ^ (row & 15)) << 4);
 }
 
-// Direct global->LDS copy of the first `rows` rows of a [64][D] tile by four waves; the other rows and
+// Direct global->LDS copy of the first `rows` rows of a [64][D] tile by four waves (keys: up to the valid
+// length, since what padding holds must not reach the products: zero times NaN); the other rows and
 // the columns at and beyond the head width dr lie outside the buffer descriptor's range: zeros.
 template <int D>
 struct F32Tile {
@@ -159,10 +160,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
     plan.init(wave, lane, ld, dr);
     auto request = [&](int t) {
         char* st = smem + (t & 1) * STAGE;
-        plan.issue(qkv + H + (size_t)t * 64 * ld, ld, dr, S - t * 64, st, wave);
-        plan.issue(qkv + 2 * H + (size_t)t * 64 * ld, ld, dr, S - t * 64, st + TILE, wave);
+        plan.issue(qkv + H + (size_t)t * 64 * ld, ld, dr, klen - t * 64, st, wave);
+        plan.issue(qkv + 2 * H + (size_t)t * 64 * ld, ld, dr, klen - t * 64, st + TILE, wave);
     };
-    request(0);
+    if (nt > 0) request(0);
     for (int t = 0; t < nt; ++t) {
         BP_WAIT_VMCNT(0);
         __syncthreads();
@@ -283,10 +284,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(A
     plan.init(wave, lane, ld, dr);
     auto request = [&](int t) {
         char* st = smem + (t & 1) * STAGE;
-        plan.issue(qkv + H + (size_t)t * 64 * ld, ld, dr, S - t * 64, st, wave);
-        plan.issue(qkv + 2 * H + (size_t)t * 64 * ld, ld, dr, S - t * 64, st + TILE, wave);
+        plan.issue(qkv + H + (size_t)t * 64 * ld, ld, dr, klen - t * 64, st, wave);
+        plan.issue(qkv + 2 * H + (size_t)t * 64 * ld, ld, dr, klen - t * 64, st + TILE, wave);
     };
-    request(0);
+    if (nt > 0) request(0);
     for (int t = 0; t < nt; ++t) {
         BP_WAIT_VMCNT(0);
         __syncthreads();
@@ -345,8 +346,9 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(
     const int dr = a.d, H = a.heads * dr, ld = 3 * H, S = a.S;
     const float* qkv = (const float*)a.qkv + (size_t)b * S * ld + head * dr;
     const float* dobase = (const float*)a.dctx + (size_t)b * S * H + head * dr;
-    const int k_wave = kblk * 64 + kg * 32, k_lane = k_wave + (lane & 31), k_src = min(k_lane, S - 1);
+    const int k_wave = kblk * 64 + kg * 32, k_lane = k_wave + (lane & 31);
     const int klen = a.causal ? S : (a.lens ? a.lens[b] : S);
+    const int k_src = max(min(k_lane, klen - 1), 0);     // row this lane reads (its own, unless it is padding)
     float* dk_out = (float*)a.dqkv + ((size_t)b * S + k_lane) * ld + H + head * dr;
     float* dv_out = dk_out + H;
     const float c = scale * kLog2e;

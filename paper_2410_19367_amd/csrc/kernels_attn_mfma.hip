@@ -219,8 +219,9 @@ __device__ __forceinline__ void block_coords(int nblk, int heads, bool causal, b
 // as CUs become free the tail of the launch stays short.
 // =====================================================================================
 // RAG: the sequence length is not a multiple of 64.  The last query block and the last key tile are
-// then partly filled: tile rows past the end are zeros, keys past the end are masked like padded
-// ones, queries past the end repeat the last one and are not stored.  (The guards cost a branch per
+// then partly filled: tile rows of keys past the end, or past the sequence's valid length, are zeros
+// (what padding holds must not reach the products: zero times NaN), such keys are masked, queries past
+// the end repeat the last one and are not stored.  (The guards cost a branch per
 // tile, so multiples of 64 keep kernels without them.  Before, such lengths went to the kernels of
 // one row per block: 8 micro-batches of 2 layers with H = 1600, S = 1000, B = 1: 46.7 ms, now 16.0 ms.
 // Those kernels kept P and dS in fp32, and these lengths still do: each goes into the second product as three
@@ -276,9 +277,9 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
         for (int j = 0; j < NT; ++j) {
             const int k0 = (step * NT + j) * 64;
             if (step * NT + j < nt) {
-                if (RAG && k0 + 64 > a.S) {
-                    plan.issue_rows(kbase + (size_t)k0 * ld, st + j * 2 * TILE, wave, a.S - k0);
-                    plan.issue_rows(vbase + (size_t)k0 * ld, st + j * 2 * TILE + TILE, wave, a.S - k0);
+                if (RAG && k0 + 64 > klen) {
+                    plan.issue_rows(kbase + (size_t)k0 * ld, st + j * 2 * TILE, wave, klen - k0);
+                    plan.issue_rows(vbase + (size_t)k0 * ld, st + j * 2 * TILE + TILE, wave, klen - k0);
                     continue;
                 }
                 plan.issue(kbase + (size_t)k0 * ld, st + j * 2 * TILE, wave);
@@ -464,15 +465,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
     TilePlan<D, NW, PAD> plan;
     plan.init(wave, lane, ld, dr);
     auto request = [&](int k0, char* st) {
-        if (RAG && k0 + 64 > a.S) {
-            plan.issue_rows(kbase + (size_t)k0 * ld, st, wave, a.S - k0);
-            plan.issue_rows(vbase + (size_t)k0 * ld, st + TILE, wave, a.S - k0);
+        if (RAG && k0 + 64 > klen) {
+            plan.issue_rows(kbase + (size_t)k0 * ld, st, wave, klen - k0);
+            plan.issue_rows(vbase + (size_t)k0 * ld, st + TILE, wave, klen - k0);
             return;
         }
         plan.issue(kbase + (size_t)k0 * ld, st, wave);
         plan.issue(vbase + (size_t)k0 * ld, st + TILE, wave);
     };
-    request(0, smem);
+    if (nt > 0) request(0, smem);
 
     for (int t = 0; t < nt; ++t) {
         const int k0 = t * 64;
@@ -580,7 +581,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
     const float* lse = a.lse + ((size_t)b * a.heads + head) * a.S;
     const float* dlt = a.delta + ((size_t)b * a.heads + head) * a.S;
 
-    const int k_src = RAG ? min(k_lane, a.S - 1) : k_lane;     // row this lane reads
+    const int k_src = RAG ? min(k_lane, klen - 1) : k_lane;     // row this lane reads (its own, unless it is padding)
     bf16x8 kf[KS], vf[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {

@@ -309,6 +309,38 @@ def test_attention_ragged_lengths_keep_probabilities_in_fp32(S, heads, d):
         assert err <= 2.0 ** -8, (name, err)
 
 
+@pytest.mark.parametrize("S,heads,d,lens,dtype", [
+    (77, 2, 64, [50, 77], "bf16"), (333, 1, 128, [100, 333], "bf16"), (577, 2, 40, [1, 560], "bf16"), (70, 1, 24, [65, 3], "bf16"),
+    (64, 2, 64, [50, 64], "f32"), (77, 2, 96, [64, 33], "f32"), (333, 1, 128, [100, 1], "f32"), (128, 2, 24, [127, 96], "f32"),
+])
+def test_attention_padding_may_hold_anything(S, heads, d, lens, dtype):
+    """Keys and values beyond a sequence's valid length take no part: NaN and infinities there leave every bit
+    of the outputs as zeros there do, and their own gradients are zeros."""
+    import torch
+    import paper_2410_19367_amd as bp
+    dt = bp.BP_BF16 if dtype == "bf16" else bp.BP_F32
+    B, H = len(lens), heads * d
+    qkv = _randn("nqkv", (B, S, 3 * H), 1.0, dtype=dtype)
+    dd = hz.to_dev(_randn("ndctx", (B, S, H), dtype=dtype), dtype)
+    lens_d = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    results = []
+    for fill in (0.0, float("nan"), float("inf")):
+        qd = hz.to_dev(qkv, dtype)
+        for b, n in enumerate(lens):
+            qd[b, n:, H:] = fill
+        ctx, dqkv = hz.empty_like_dev((B, S, H), dtype), hz.empty_like_dev((B, S, 3 * H), dtype)
+        lse, delta = torch.empty((B, heads, S), device="cuda"), torch.empty((B, heads, S), device="cuda")
+        bp.bp_op_attention_fwd(dt, B, S, heads, d, False, lens_d, qd, ctx, lse)
+        bp.bp_op_attention_bwd(dt, B, S, heads, d, False, lens_d, qd, ctx, lse, dd, dqkv, delta)
+        torch.cuda.synchronize()
+        results.append([hz.to_host(t) for t in (ctx, lse, delta, dqkv)])
+    for r in results:
+        for b, n in enumerate(lens):
+            assert not np.any(r[3][b, n:, H:])
+        for a, ref in zip(r, results[0]):
+            assert np.all(np.isfinite(a)) and np.array_equal(a, ref)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_attention_one_token(dtype):
     """S = 1: probability one, so ctx = v and dv = dctx exactly, and dq, dk vanish up to the rounding of
