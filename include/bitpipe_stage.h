@@ -326,7 +326,8 @@ int bp_op_gemm(int dtype, int a_t, int b_t, int M, int N, int K,
  * workspace: optional dev fp32 scratch of workspace_elems floats (NULL / 0: none).  With it, the
  * output tiles that do not fill the chip (all of them for a small dW, else those of the last,
  * partly filled round) are cut into up to 4 slices of a long token axis that run on different
- * CUs; their partial sums go through the workspace (4*M*N floats always suffice) and are added
+ * CUs; their partial sums go through the workspace (4*M*N floats with M and N
+ * rounded up to multiples of 256 always suffice; with less there are fewer slices) and are added
  * in a fixed order.  Asynchronous on `stream`. */
 int bp_op_wgrad_group(int dtype, int M, int N, int T, int n, const void* const* X,
                       const void* const* dY, float* dW, int overwrite, float* workspace,

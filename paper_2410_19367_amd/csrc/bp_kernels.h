@@ -31,7 +31,7 @@ struct GemmArgs {
     // filled last round) may have K cut into up to 4 slices computed by different blocks, each
     // writing an fp32 partial of its tile there; a second kernel adds the partials in a fixed
     // order and applies the epilogue.  splits * tiles * tile size floats are needed; 4 * M * N
-    // always suffice.  Null: never split.
+    // with both rounded up to multiples of 256 always suffice, with less there are fewer slices.  Null: never split.
     float* split_ws = nullptr;
     size_t split_ws_elems = 0;
     // Optional further contraction segments: the product runs over nseg operand pairs

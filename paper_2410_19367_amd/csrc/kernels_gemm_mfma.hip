@@ -457,18 +457,18 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     // RAG: address of the next slice, bytes from there to the operand's end
     const char *a_at = nullptr, *b_at = nullptr;
     long a_left = 0, b_left = 0;
-    auto rag_origin = [&](int sgm, uint32_t a_skip, uint32_t b_skip) {
+    auto rag_origin = [&](int sgm, long a_skip, long b_skip) {
         const long a_rows = A_RMAJOR ? g.K : g.M - m0, a_cols = A_RMAJOR ? g.M - m0 : g.K;
         const long b_rows = B_RMAJOR ? g.K : g.N - n0, b_cols = B_RMAJOR ? g.N - n0 : g.K;
         a_at = (const char*)a_base(sgm) + a_skip;
         b_at = (const char*)b_base(sgm) + b_skip;
-        a_left = 2 * ((a_rows - 1) * g.lda + a_cols) - (long)a_skip;
-        b_left = 2 * ((b_rows - 1) * g.ldb + b_cols) - (long)b_skip;
+        a_left = 2 * ((a_rows - 1) * g.lda + a_cols) - a_skip;
+        b_left = 2 * ((b_rows - 1) * g.ldb + b_cols) - b_skip;
     };
     auto rag_rsrc = [&](const char* at, long left) {
         return make_rsrc(at, left <= 0 ? 0u : left < (long)kOutside ? (uint32_t)left : kOutside);
     };
-    if constexpr (RAG) rag_origin(seg, a_off, b_off);
+    if constexpr (RAG) rag_origin(seg, (long)kl * a_step, (long)kl * b_step);     // (beyond 32 bits in long operands)
     auto rag_move = [&](uint32_t da, uint32_t db) {
         a_at += da; a_left -= da;
         b_at += db; b_left -= db;
@@ -1065,7 +1065,9 @@ static hipError_t launch_dma_rag(const GemmArgs& g, hipStream_t s, int splits, i
 
 template <int BM, int BN, int WM, int WN, int NS, int BKT = 64, bool MI16 = false, bool RING = false>
 static hipError_t launch_dma(const GemmArgs& g, hipStream_t s, int splits = 1, int n_full = -1) {
-    if (g.M % BM || g.N % BN || g.K % BKT)
+    // (slices of the other variant are addressed by 32-bit byte offsets from the tile's first row)
+    const bool beyond = (g.a_t && 2L * g.K * g.lda > 0xffffffffL) || (!g.b_t && 2L * g.K * g.ldb > 0xffffffffL);
+    if (g.M % BM || g.N % BN || g.K % BKT || beyond)
         return launch_dma_rag<BM, BN, WM, WN, NS, BKT, MI16, RING, true>(g, s, splits, n_full);
     return launch_dma_rag<BM, BN, WM, WN, NS, BKT, MI16, RING, false>(g, s, splits, n_full);
 }

@@ -446,3 +446,26 @@ def test_wgrad_group(M, N, T, n, dtype, overwrite):
     torch.cuda.synchronize()
     err = hz.rel_err(wd.cpu().numpy().astype(np.float64), ref)
     assert err <= (2e-3 if dtype == "bf16" else 1e-5), err
+
+
+@pytest.mark.parametrize("M,N,T", [(8192, 8, 370001), (8192, 128, 371200), (32768, 8, 80000)])
+def test_wgrad_operand_beyond_4_gib(M, N, T):
+    """X of 5 to 6 GB: K slices (and, in the last case, one walk over all tokens) that reach offsets no 32-bit
+    number holds; a wrapped offset reads other tokens, an error of the size of the result.  fp32 sums of T products
+    of about unit size in another order: below 1e-4 of the largest element."""
+    import torch
+    import paper_2410_19367_amd as bp
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.randn(T, M, device="cuda", generator=g, dtype=torch.bfloat16)
+    y = torch.randn(T, N, device="cuda", generator=g, dtype=torch.bfloat16)
+    assert x.numel() * 2 > 2 ** 32
+    ref = torch.zeros(M, N, device="cuda", dtype=torch.float64)
+    for t in range(0, T, 8192):
+        ref += (x[t:t + 8192].float().t().contiguous() @ y[t:t + 8192].float()).double()
+    w = torch.empty(M, N, device="cuda")
+    ws = torch.empty(4 * M * max(N, 128), device="cuda")         # whole 128 x 128 tiles
+    bp.bp_op_wgrad_group(bp.BP_BF16, M, N, T, [x], [y], w, 1, ws, ws.numel())
+    torch.cuda.synchronize()
+    err = float((w.double() - ref).abs().max() / ref.abs().max())
+    assert err <= 1e-4, err
