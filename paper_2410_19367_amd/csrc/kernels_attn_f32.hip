@@ -16,6 +16,7 @@
 
 #include "bp_kernels.h"
 #include "bp_device.h"
+#include "bp_attn_rows.h"
 #include "bp_tile.h"
 
 namespace bp {
@@ -117,6 +118,18 @@ __device__ __forceinline__ void scores(const char* tile_a, const char* tile_c, i
                          }
                      });
 }
+// no NaN and no infinity in rows row0 .. row0 + 31 of a tile (the same answer in every lane)
+template <int D, int DC>
+__device__ __forceinline__ bool rows_finite(const char* tile, int row0, int lane) {
+    float z = 0.f;
+#pragma unroll
+    for (int j = 0; j < DC / 8; ++j) {
+        const f32x4 f = rows4<D>(tile, row0, j, lane);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z = __builtin_fmaf(0.f, f[e], z);
+    }
+    return __builtin_amdgcn_ballot_w64(z != 0.f) == 0;
+}
 __device__ __forceinline__ f32x16 zero16() {
     f32x16 z;
 #pragma unroll
@@ -155,6 +168,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
 #pragma unroll
     for (int t = 0; t < DT; ++t) ot[t] = zero16();
     float m = -INFINITY, lsum = 0.f;
+    bool by_rows = false;       // a value on the diagonal is not finite: see bp_attn_rows.h
 
     F32Tile<D> plan;
     plan.init(wave, lane, ld, dr);
@@ -206,7 +220,12 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
             st2[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(st2[v], c, -m_use));
             lsum += st2[v];
         }
+        if (a.causal && kw + 31 > q_wave && !rows_finite<D, DC>(sv, 32 * kh, lane)) by_rows = true;
         contract<D, DC>(sv, 32 * kh, lane, st2, ot);
+    }
+    if (a.causal && any_wave(by_rows, smem)) {
+        for (int q = qblk * 64; q < min(qblk * 64 + 64, S); ++q) attn_fwd_row<float>(a, scale, q, head, b, (float*)smem);
+        return;
     }
 
     // merge the two key halves through LDS; half 0 has seen key 0, so its m is finite
@@ -280,6 +299,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(A
     f32x16 dq[DT];
 #pragma unroll
     for (int t = 0; t < DT; ++t) dq[t] = zero16();
+    bool by_rows = false;       // a key or value on the diagonal is not finite
     F32Tile<D> plan;
     plan.init(wave, lane, ld, dr);
     auto request = [&](int t) {
@@ -296,6 +316,9 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(A
         if ((a.causal && kw > q_wave + 31) || kw >= klen) continue;
         const char* sk = smem + (t & 1) * STAGE;
         const char* sv = sk + TILE;
+        // (a value that is not finite makes dP of the queries that do not attend it NaN)
+        if (a.causal && kw + 31 > q_wave && (!rows_finite<D, DC>(sk, 32 * kh, lane) || !rows_finite<D, DC>(sv, 32 * kh, lane)))
+            by_rows = true;
         f32x16 sacc = zero16(), dp = zero16();
         scores<D, DC>(sk, sv, 32 * kh, lane, qf, dof, sacc, dp);
         const bool need_mask = (a.causal && kw + 31 > q_wave) || kw + 32 > klen;
@@ -307,6 +330,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(A
             dp[v] = p * (dp[v] - delta);                // dS^T
         }
         contract<D, DC>(sk, 32 * kh, lane, dp, dq);
+    }
+    if (a.causal && any_wave(by_rows, smem)) {
+        for (int q = qblk * 64; q < min(qblk * 64 + 64, S); ++q) attn_bwd_dq_row<float>(a, scale, q, head, b, (float*)smem);
+        return;
     }
     __syncthreads();
     float* xo = (float*)smem + qg * (DT * 16 * 64);
@@ -364,6 +391,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(
     f32x16 dk[DT], dv[DT];
 #pragma unroll
     for (int t = 0; t < DT; ++t) { dk[t] = zero16(); dv[t] = zero16(); }
+    bool by_rows = false;       // a query on the diagonal is not finite
     // a block of padding keys that no query attends skips the loop and stores zeros
     const int t0 = a.causal ? kblk : 0, nt = kblk * 64 >= klen ? t0 : (S + 63) / 64;
 
@@ -393,6 +421,9 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(
         const char* sdo = sq + TILE;
         const float* s_lse = (const float*)(sq + 2 * TILE) + 32 * qh;
         const float* s_dlt = s_lse + 64;
+        if (a.causal && qw < k_wave + 31 && (!rows_finite<D, DC>(sq, 32 * qh, lane) || !rows_finite<D, DC>(sdo, 32 * qh, lane) ||
+                                             !stats_finite(s_lse, s_dlt, lane)))
+            by_rows = true;
         f32x16 sacc = zero16(), dp = zero16();
         scores<D, DC>(sq, sdo, 32 * qh, lane, kf, vf, sacc, dp);
         const bool need_mask = (a.causal && qw < k_wave + 31) || qw + 32 > S || k_wave + 32 > klen;
@@ -406,6 +437,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(
         }
         contract<D, DC>(sdo, 32 * qh, lane, sacc, dv);
         contract<D, DC>(sq, 32 * qh, lane, dp, dk);
+    }
+    if (a.causal && any_wave(by_rows, smem)) {
+        for (int k = kblk * 64; k < min(kblk * 64 + 64, S); ++k) attn_bwd_dkv_row<float>(a, scale, k, head, b, (float*)smem);
+        return;
     }
     __syncthreads();
     float* xo = (float*)smem + kg * (2 * DT * 16 * 64);
@@ -449,6 +484,7 @@ static hipError_t launch_f32_attn(const AttnArgs& a, bool bwd, hipStream_t s) {
     const float scale = 1.f / sqrtf((float)a.d);
     const dim3 grid(((a.S + 63) / 64) * a.heads * a.B), block(256);
     // two stages; the merges fit in them (forward: (D/32*1024 + 128) floats twice, dK/dV: D/32*4096 floats)
+    // (more than the rows by themselves take: 60000 bytes at most)
     const int smem = 2 * 2 * 64 * D * 4, smem2 = smem + 1024;
     static std::atomic<bool> set{false};
     if (!set.load(std::memory_order_acquire)) {

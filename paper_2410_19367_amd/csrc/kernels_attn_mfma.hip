@@ -16,10 +16,12 @@
 // One swizzle serves plain 16-byte fragment reads and transpose reads of the same tile:
 // chunk c of row r is stored at c ^ f(r), f chosen so that 16 consecutive rows (plain reads) and
 // 4 consecutive rows x 64 bytes (transpose reads) both cover all banks.
+#include <algorithm>
 #include <atomic>
 
 #include "bp_kernels.h"
 #include "bp_device.h"
+#include "bp_attn_rows.h"
 
 namespace bp {
 
@@ -187,6 +189,22 @@ __device__ __forceinline__ void contract(const char* tile, int row0, int lane, i
 // row index inside a 32-row accumulator tile held in register v by a lane of half h
 __device__ __forceinline__ int acc_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
 
+// no NaN and no infinity in rows row0 .. row0 + 31 of a tile (the same answer in every lane)
+template <int D>
+__device__ __forceinline__ bool rows_finite(const char* tile, int row0, int lane, int dr) {
+    typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+    u16x8 top = (u16x8)(unsigned short)0;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s)
+        if (16 * s < dr)
+            top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x8, frag_rows<D>(tile, row0, s, lane)) &
+                                                     (u16x8)(unsigned short)0x7fff);
+    bool ok = true;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ok = ok && top[e] < 0x7f80;
+    return __builtin_amdgcn_ballot_w64(!ok) == 0;
+}
+
 // Heavy-first, then light-last block order for causal masks: the first half of the grid walks the
 // query (or key) blocks from the most expensive down, the second half from the cheapest up, so the
 // two blocks that share a CU's two slots add up to roughly the same work everywhere.
@@ -269,6 +287,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
 #pragma unroll
         for (int v = 0; v < 16; ++v) ot[t][v] = 0.f;
     float m = -INFINITY, lsum = 0.f;
+    bool by_rows = false;       // a value on the diagonal is not finite: see bp_attn_rows.h
 
     TilePlan<D, NW, PAD> plan;
     plan.init(wave, lane, ld, dr);
@@ -344,7 +363,12 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
         }
         lsum += ps;
         // O^T (D x 32 queries) += V^T P^T over this wave's 32 keys
+        if (RAG && a.causal && kw + 31 > q_wave && !rows_finite<D>(sv, 32 * kh, lane, dr)) by_rows = true;
         contract<D, DT, RAG>(sv, 32 * kh, lane, dr, st2, ot);
+    }
+    if (RAG && a.causal && any_wave(by_rows, smem)) {
+        for (int q = qblk * 64; q < min(qblk * 64 + 64, a.S); ++q) attn_fwd_row<bf16_t>(a, scale, q, head, b, (float*)smem);
+        return;
     }
 
     // merge the key sub-ranges: waves 1 .. NSUB-1 of a query group hand (m, l, O^T) to wave 0 through LDS
@@ -461,6 +485,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
     for (int t = 0; t < DT; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) dq[t][v] = 0.f;
+    bool by_rows = false;       // a key or value on the diagonal is not finite
 
     TilePlan<D, NW, PAD> plan;
     plan.init(wave, lane, ld, dr);
@@ -484,6 +509,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
         if ((a.causal && kw > q_wave + 31) || kw >= klen) continue;
         const char* sk = smem + (t & 1) * STAGE;
         const char* sv = sk + TILE;
+        // (a value that is not finite makes dP of the queries that do not attend it NaN)
+        if (RAG && a.causal && kw + 31 > q_wave &&
+            (!rows_finite<D>(sk, 32 * kh, lane, dr) || !rows_finite<D>(sv, 32 * kh, lane, dr))) by_rows = true;
         const bool need_mask = (a.causal && kw + 31 > q_wave) || (kw + 32 > klen);
         f32x16 sacc, dp;
 #pragma unroll
@@ -504,6 +532,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
             dp[v] = p * (dp[v] - delta);            // dS^T
         }
         contract<D, DT, RAG>(sk, 32 * kh, lane, dr, dp, dq);
+    }
+    if (RAG && a.causal && any_wave(by_rows, smem)) {
+        for (int q = qblk * 64; q < min(qblk * 64 + 64, a.S); ++q) attn_bwd_dq_row<bf16_t>(a, scale, q, head, b, (float*)smem);
+        return;
     }
     __syncthreads();
     float* xo = (float*)smem + qg * (DT * 16 * 64);
@@ -594,6 +626,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
 #pragma unroll
         for (int v = 0; v < 16; ++v) { dk[t][v] = 0.f; dv[t][v] = 0.f; }
 
+    bool by_rows = false;       // a query on the diagonal is not finite
     const bool pad_in_block = kblk * 64 + 64 > klen;   // some of this block's keys are padding
     const int t0 = a.causal ? kblk : 0;        // first 64-query tile that can see this block's keys
     const int nt = (a.S + 63) / 64;
@@ -636,6 +669,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
         const float* s_lse = (const float*)(sq + 2 * TILE) + 32 * qh;
         const float* s_dlt = (const float*)(sq + 2 * TILE) + 64 + 32 * qh;
         const bool need_mask = a.causal && qw < k_wave + 31;
+        if (RAG && need_mask && (!rows_finite<D>(sq, 32 * qh, lane, dr) || !rows_finite<D>(sdo, 32 * qh, lane, dr) ||
+                                 !stats_finite(s_lse, s_dlt, lane))) by_rows = true;
         f32x16 sacc, dp;
 #pragma unroll
         for (int v = 0; v < 16; ++v) { sacc[v] = 0.f; dp[v] = 0.f; }
@@ -686,6 +721,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             }
         }
         }
+    }
+    if (RAG && a.causal && any_wave(by_rows, smem)) {
+        for (int k = kblk * 64; k < min(kblk * 64 + 64, a.S); ++k) attn_bwd_dkv_row<bf16_t>(a, scale, k, head, b, (float*)smem);
+        return;
     }
     __syncthreads();
     float* xo = (float*)smem + kg * (2 * DT * 16 * 64);
@@ -749,10 +788,10 @@ static hipError_t launch_fwd_nt(const AttnArgs& a, hipStream_t s) {
     const dim3 grid(((a.S + 63) / 64) * a.heads * a.B), block(256 * NT);
     const size_t stages = (size_t)2 * NT * 2 * 64 * D * 2;
     const size_t merge = (size_t)2 * (2 * NT - 1) * ((D / 32) * 16 * 64 + 128) * sizeof(float);
-    const size_t smem = stages > merge ? stages : merge;
+    const size_t smem = std::max(std::max(stages, merge), RAG && a.causal ? attn_row_lds_fwd(a) : 0);
     static std::atomic<bool> set{false};   // several host threads may launch at once
     if (!set.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_fwd_mfma_kernel<D, DR, NT, RAG>, smem);
+        hipError_t e = set_smem(attn_fwd_mfma_kernel<D, DR, NT, RAG>, std::max(std::max(stages, merge), kMaxAttnRowLds));
         if (e != hipSuccess) return e;
         set.store(true, std::memory_order_release);
     }
@@ -779,11 +818,13 @@ template <int D, int DR, bool RAG>
 static hipError_t launch_bwd_rag(const AttnArgs& a, hipStream_t s) {
     const float scale = 1.f / sqrtf((float)a.d);
     const dim3 grid(((a.S + 63) / 64) * a.heads * a.B), block(256);
-    const size_t smem = 2 * 2 * 64 * D * 2, smem2 = 2 * (2 * 64 * D * 2 + 512);
+    constexpr size_t stages = 2 * 2 * 64 * D * 2, stages2 = 2 * (2 * 64 * D * 2 + 512);
+    const bool rows = RAG && a.causal;
+    const size_t smem = std::max(stages, rows ? attn_row_lds_dq(a) : 0), smem2 = std::max(stages2, rows ? attn_row_lds_dkv(a) : 0);
     static std::atomic<bool> set{false};   // several host threads may launch at once
     if (!set.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_bwd_dq_mfma_kernel<D, DR, RAG>, smem);
-        if (e == hipSuccess) e = set_smem(attn_bwd_dkv_mfma_kernel<D, DR, RAG>, smem2);
+        hipError_t e = set_smem(attn_bwd_dq_mfma_kernel<D, DR, RAG>, std::max(stages, kMaxAttnRowLds));
+        if (e == hipSuccess) e = set_smem(attn_bwd_dkv_mfma_kernel<D, DR, RAG>, std::max(stages2, kMaxAttnRowLds));
         if (e != hipSuccess) return e;
         set.store(true, std::memory_order_release);
     }

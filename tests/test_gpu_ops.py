@@ -341,6 +341,50 @@ def test_attention_padding_may_hold_anything(S, heads, d, lens, dtype):
             assert np.all(np.isfinite(a)) and np.array_equal(a, ref)
 
 
+@pytest.mark.parametrize("S,heads,d,t,dtype", [
+    (100, 2, 64, 40, "bf16"), (333, 1, 128, 331, "bf16"), (545, 1, 40, 100, "bf16"), (70, 2, 96, 65, "bf16"), (3001, 1, 64, 1500, "bf16"),
+    (64, 2, 64, 1, "f32"), (100, 2, 96, 40, "f32"), (333, 1, 128, 331, "f32"), (128, 1, 24, 70, "f32"),
+])
+@pytest.mark.parametrize("where", ["q", "k", "v", "dctx"])
+def test_attention_causal_token_that_is_not_finite(S, heads, d, t, dtype, where):
+    """A causal mask keeps token t from those before it, whatever it holds: what does not depend on it stays as
+    it is without it (to the rounding of either path), in fp32 and at lengths that are no multiple of 64."""
+    import torch
+    import paper_2410_19367_amd as bp
+    dt = bp.BP_BF16 if dtype == "bf16" else bp.BP_F32
+    H = heads * d
+    runs = []
+    for fill in (None, float("nan"), float("inf")):
+        qd = hz.to_dev(_randn("cqkv", (1, S, 3 * H), 1.0, dtype=dtype), dtype)
+        dd = hz.to_dev(_randn("cdctx", (1, S, H), dtype=dtype), dtype)
+        if fill is not None:
+            if where == "dctx":
+                dd[0, t] = fill
+            else:
+                k = "qkv".index(where)
+                qd[0, t, k * H:(k + 1) * H] = fill
+        ctx, dqkv = hz.empty_like_dev((1, S, H), dtype), hz.empty_like_dev((1, S, 3 * H), dtype)
+        lse, delta = torch.empty((1, heads, S), device="cuda"), torch.empty((1, heads, S), device="cuda")
+        bp.bp_op_attention_fwd(dt, 1, S, heads, d, True, None, qd, ctx, lse)
+        bp.bp_op_attention_bwd(dt, 1, S, heads, d, True, None, qd, ctx, lse, dd, dqkv, delta)
+        torch.cuda.synchronize()
+        g = hz.to_host(dqkv)[0]
+        runs.append({"ctx": hz.to_host(ctx)[0], "dq": g[:, :H], "dk": g[:, H:2 * H], "dv": g[:, 2 * H:]})
+    rows = np.arange(S)
+    before, others, after, every, none = rows < t, rows != t, rows > t, rows >= 0, rows < 0
+    clean = {"q": {"ctx": others, "dq": others, "dk": after, "dv": after},
+             "k": {"ctx": before, "dq": before, "dk": none, "dv": none},
+             "v": {"ctx": before, "dq": before, "dk": none, "dv": every},
+             "dctx": {"ctx": every, "dq": others, "dk": after, "dv": after}}[where]
+    for r in runs[1:]:
+        for name, ok in clean.items():
+            ref, got = runs[0][name], r[name][ok]
+            assert np.all(np.isfinite(got)), (name, rows[ok][~np.all(np.isfinite(got), axis=-1)])
+            if got.size:
+                err = np.max(np.abs(got - ref[ok])) / np.max(np.abs(ref))
+                assert err <= (1e-2 if dtype == "bf16" else 5e-5), (name, err)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_attention_one_token(dtype):
     """S = 1: probability one, so ctx = v and dv = dctx exactly, and dq, dk vanish up to the rounding of
