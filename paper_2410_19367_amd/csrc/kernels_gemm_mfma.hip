@@ -1187,18 +1187,35 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     // tiles lose more than the partials cost (2560 x 2560 x 16384: 334 us against 272 us).
     const long t128 = tiles(128, 128), t64 = tiles(64, 64);
     // Small outputs.  What a block takes there is its chain of slices, each a barrier and a load latency, so
-    // smaller tiles (fewer MFMAs per slice, more blocks) win although they move more operand bytes.
+    // smaller tiles (fewer MFMAs per slice, more blocks) win although they move more operand bytes, until the chain
+    // is so long that cutting K between several 128 x 128 blocks and adding their partials takes less.
     // Forward / data-gradient form, 128 x 128 tiles (cut along K where that applied) against
     //   64 x 64, three stages of 128 along K, while every CU gets at most one block:
-    //     384 x 768 x 256 5.8 -> 4.0 us, 1024^3 10.1 -> 6.6 us, 1024 x 1024 x 4096 27.4 -> 16.0 us;
+    //     384 x 768 x 256 5.8 -> 4.0 us, 1024^3 10.1 -> 6.6 us, 1024 x 1024 x 4096 18.0 -> 16.0 us;
     //   128 x 64, three stages of 64 (72 KB: two blocks per CU), while two of 64 x 64 would fit a CU:
-    //     1000 x 1600 x 6400 45.4 -> 34.8 us, 1024 x 2048 x 8192 49.6 -> 41.8 us.
-    // Not beyond: 768 x 3072 x 768 9.2 -> 10.2 us; and where 128 x 128 tiles start a second round that stays
+    //     1000 x 1600 x 3072 20.6 -> 19.8 us, 1024 x 2048 x 4096 24.3 -> 22.8 us.
+    // Against K slices (which need a workspace) the limits in depth are, at
+    //   64 tiles of 64 x 64 or fewer   K 3072 13.3 / 12.2, 4096 14.2 / 15.2 us (512 x 512)
+    //   128                            K 3072 14.2 / 12.2, 4096 14.6 / 15.3 us (512 x 1024)
+    //   256                            K 6144 21.9 / 21.7, 8192 25.1 / 28.1 us (1024 x 1024)
+    //   512 (128 x 64)                 K 5120 28.0 / 27.4, 6144 31.2 / 32.2 us (1024 x 2048)
+    //   the same with edge tiles       K 3072 20.6 / 19.8, 4096 23.7 / 24.3 us (1000 x 1600)
+    // (slices / small tiles).  That is with four slices (two for the last two); 64 x 64 tiles win against three up to twice that depth
+    // (320 x 960 x 3776 16.8 / 15.5 us), against two (944 x 176 x 17080 80 / 62 us) and without any
+    // (512 x 512 x 8192 48.8 / 26.9 us) always.
+    // Not beyond 512: 768 x 3072 x 768 9.2 -> 10.2 us; and where 128 x 128 tiles start a second round that stays
     // less than half full a warm loop gains 5 % (6144 x 1024 x 1024), the stage loses 1 %.
     // Weight gradients with a short contraction, 128 x 128 against 64 x 64 tiles: 256 x 1024 x 1536
     // 15.7 -> 9.7 us, 1024 x 1024 x 2048 20.4 -> 12.5 us; longer ones are better off cut along K.
-    if (nt && t64 <= ncu) return launch_dma<64, 64, 2, 2, 3, 128, true>(g, s);
-    if (nt && t64 <= 2L * ncu)
+    int slices = g.split_ws && g.epi == EPI_NONE ? (int)(ncu / t128) : 1;       // of 128 x 128 tiles, each at least 1024 deep
+    if (slices > 4) slices = 4;
+    while (slices > 1 && (k_total / slices < 1024 || (size_t)slices * t128 * 16384 > g.split_ws_elems)) --slices;
+    const bool edges = g.M % 128 != 0 || g.N % 64 != 0 || g.K % BK != 0;
+    const long small_depth = slices <= 1 || (slices == 2 && t64 <= ncu) ? k_total :
+                             t64 > ncu ? (edges ? 3584 : 5120) :
+                             slices == 3 || t64 > ncu / 2 ? 6144 : t64 > ncu / 4 ? 3584 : 3072;
+    if (nt && t64 <= ncu && k_total <= small_depth) return launch_dma<64, 64, 2, 2, 3, 128, true>(g, s);
+    if (nt && t64 <= 2L * ncu && k_total <= small_depth)
         return launch_dma<128, 64, 2, 2, 3, 64, true>(g, s);
     if (wgrad && t64 <= ncu && k_total <= 2048) return launch_dma<64, 64, 2, 2, 3, 128, true>(g, s);
     const bool deep = g.K % 128 == 0 || (g.K % BK != 0 && g.K > 512);   // slices of 128 along K
@@ -1219,12 +1236,10 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     }
     // Small outputs (128 x 128 tiles on fewer than three quarters of the CUs) with a long K: the same split, on the small
     // tiles (slices at least 1024 deep: below that the second kernel costs what the split gains)
-    if (g.split_ws && g.epi == EPI_NONE) {
-        int splits = (int)(ncu / t128);
-        if (splits > 4) splits = 4;
-        while (splits > 1 && (k_total / splits < 1024 || (size_t)splits * t128 * 16384 > g.split_ws_elems)) --splits;
-        if (splits > 1 && deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s, splits, 0);
-        if (splits > 1) return launch_dma<128, 128, 2, 4, 2>(g, s, splits, 0);
+    if (slices > 1) {
+        if (nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s, slices, 0);
+        if (deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s, slices, 0);
+        return launch_dma<128, 128, 2, 4, 2>(g, s, slices, 0);
     }
     // 8 waves (2 per SIMD) hide the LDS and load latencies better than 4 on 128 x 128 tiles.
     // Forward / data-gradient form: 16x16x32 MFMAs and loads first, as on the large tiles, and three

@@ -318,6 +318,9 @@ def test_random_small_stage_configs(idx, kw, group, lean):
     # with the fused GELU epilogues, token segments that end inside a slice
     (dict(layers=2, hidden=520, heads=13, seq=77, microbatch=3, causal=True, n_micro=4), 3, 0),
     (dict(layers=1, hidden=320, heads=5, seq=333, microbatch=2, causal=False, n_micro=2, len_lo=20, len_hi=333), 0, 1),
+    # MLP so deep that the data-side products of its second matrix are cut along K, aligned and not
+    (dict(layers=1, hidden=256, heads=4, seq=77, microbatch=3, causal=True, n_micro=2, mlp=4104), 2, 0),
+    (dict(layers=1, hidden=256, heads=4, seq=128, microbatch=2, causal=True, n_micro=2, mlp=6144), 2, 0),
     # fp32: fused GELU epilogues with edge tiles
     (dict(layers=2, hidden=200, heads=5, seq=77, microbatch=3, causal=True, n_micro=4, dtype="f32"), 3, 0),
 ])
