@@ -50,15 +50,42 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
     });
 }
 
+// Short sequences: the kernels of one row per block beat the matrix-core ones, whose tiles of 64 rows are then mostly
+// padding and whose time is one chain of latencies whatever the length.  What decides is the work of all rows, heads
+// times S^2, and how soon the rows are more than the chip holds at once (rows / matrix cores, us):
+//   fp32, heads wider than 64: 16 of 96, backward, S 63 (63504) 28.4 / 27.7, 256 of 96, S 12 (36864) 21.5 / 24.2, S 16
+//     34.7 / 24.3; 4 of 104, backward, S 128 (512 rows, 65536) 31.0 / 49.9;
+//   33 to 64 wide: 64 of 64, backward, S 24 (36864) 14.6 / 17.0, S 32 20.1 / 17.2; 16, forward, S 48 6.1 / 6.5, S 63 7.4 / 6.7;
+//   narrower: 16 of 24, backward, S 32 10.2 / 11.4, S 48 13.7 / 11.8; 2 of 24, forward, S 24 4.3 / 4.5, S 32 4.6 / 4.1;
+//   bf16 backward: 16 of 64, S 16 9.0 / 9.2, 64 of 64 10.4 / 9.3; 2 of 128, S 48 15.6 / 16.8; widths above 64 without a kernel
+//     of their own spill registers: 1 of 80, S 76 16.6 / 24.5;
+//   bf16 forward: 16 of 64, S 4 4.2 / 4.1 (causal 4.2 / 4.6); 16 of 128, S 12 5.4 / 5.5 (causal 5.4 / 6.1).
+// (bf16 at multiples of 64 has always been on the matrix cores.)
+static bool rows_are_faster(int dtype, const AttnArgs& a, bool bwd) {
+    const long rows = (long)a.B * a.heads * a.S, work = rows * a.S;
+    if (dtype == F32) {
+        if (a.d > 32 && rows > 3072) return work <= 40000;
+        if (a.d > 32 && rows <= 512) return work <= (a.d > 64 ? 120000 : 80000);
+        if (a.d > 32) return work <= (a.d > 64 ? 64000 : bwd ? 50000 : 40000);
+        return a.S <= (bwd ? 48 : 24) && work <= 20000;
+    }
+    if (a.S % 64 == 0) return false;
+    if (bwd && a.d > 64 && a.d != 96) return a.d == 128 ? a.S <= 48 && work <= 16384 : work <= 40000;
+    if (bwd) return a.S <= (a.d == 96 ? 24 : 16) && work <= 8192;
+    return a.d > 32 && a.d <= 64 ? a.S <= 4 && work <= 2048 : a.S <= 12 && work <= 4096;
+}
+
 hipError_t launch_attn_fwd(int dtype, const AttnArgs& a, hipStream_t stream) {
-    if (dtype == BF16 && attn_mfma_supported(a)) return launch_attn_fwd_mfma(a, stream);
-    if (dtype == F32 && attn_f32_supported(a)) return launch_attn_fwd_f32(a, stream);
+    const bool rows = rows_are_faster(dtype, a, false);
+    if (dtype == BF16 && !rows && attn_mfma_supported(a)) return launch_attn_fwd_mfma(a, stream);
+    if (dtype == F32 && !rows && attn_f32_supported(a)) return launch_attn_fwd_f32(a, stream);
     return launch_attn_fwd_generic(dtype, a, stream);
 }
 
 hipError_t launch_attn_bwd(int dtype, const AttnArgs& a, hipStream_t stream) {
-    if (dtype == BF16 && attn_mfma_supported(a)) return launch_attn_bwd_mfma(a, stream);
-    if (dtype == F32 && attn_f32_supported(a)) return launch_attn_bwd_f32(a, stream);
+    const bool rows = rows_are_faster(dtype, a, true);
+    if (dtype == BF16 && !rows && attn_mfma_supported(a)) return launch_attn_bwd_mfma(a, stream);
+    if (dtype == F32 && !rows && attn_f32_supported(a)) return launch_attn_bwd_f32(a, stream);
     return launch_attn_bwd_generic(dtype, a, stream);
 }
 

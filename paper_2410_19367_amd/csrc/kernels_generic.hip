@@ -1,6 +1,6 @@
 // Shape-generic kernels: a tiled GEMM with fp32 accumulation and a row-at-a-time attention
-// forward/backward.  They serve any shape or alignment the matrix-core kernels do not cover;
-// correctness first, no tuning.
+// forward/backward.  They serve any shape or alignment the matrix-core kernels do not cover, and short
+// sequences; correctness first, no tuning.
 #include "bp_kernels.h"
 #include "bp_device.h"
 #include "bp_attn_rows.h"

@@ -268,6 +268,18 @@ def test_attention_ragged_lengths(B, S, heads, d, causal, lens, dtype):
     test_attention_fwd_bwd(B, S, heads, d, causal, lens, dtype)
 
 
+# Both sides of the limits between the kernels of one row per block and the matrix-core ones
+@pytest.mark.parametrize("B,S,heads,d,causal,lens", [
+    (2, 5, 2, 64, True, None), (8, 3, 32, 64, False, [1, 2, 3, 3, 1, 2, 3, 1]), (2, 12, 2, 128, True, None), (3, 13, 2, 128, False, None),
+    (2, 16, 16, 64, True, None), (3, 16, 16, 64, True, None), (2, 17, 2, 64, False, [17, 9]), (1, 24, 4, 24, True, None), (1, 25, 4, 24, True, None),
+    (2, 32, 16, 64, False, [30, 32]), (3, 37, 16, 40, True, None), (1, 244, 2, 128, False, [70]), (1, 245, 2, 128, True, None), (1, 200, 2, 64, True, None), (1, 201, 2, 64, True, None), (2, 70, 2, 80, True, None), (3, 67, 4, 80, False, [67, 1, 40]),
+    (1, 90, 4, 128, True, None), (1, 127, 2, 128, False, None),
+])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_attention_short_sequences(B, S, heads, d, causal, lens, dtype):
+    test_attention_fwd_bwd(B, S, heads, d, causal, lens, dtype)
+
+
 @pytest.mark.parametrize("S,heads,d", [(77, 2, 64), (333, 1, 128), (333, 2, 40), (577, 1, 96), (545, 1, 128), (130, 2, 24), (100, 1, 112)])
 def test_attention_ragged_lengths_keep_probabilities_in_fp32(S, heads, d):
     """bf16 storage, a length that is no multiple of 64: P and dS stay in fp32.  Keys, values, queries and output
