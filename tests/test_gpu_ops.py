@@ -176,6 +176,14 @@ def test_bias_gelu_fwd_bwd(T, F, dtype):
     assert hz.rel_err(hz.to_host(dbd), db0 + du_ref.sum(0)) <= (2e-3 if dtype == "bf16" else 1e-5)
 
 
+# Column sums over 1, 8, 9 chunks of 32 rows and around the rounds of 64 chunks, the last chunk whole and cut
+@pytest.mark.parametrize("T,N", [(1, 8), (256, 8), (257, 16), (1920, 8), (1953, 8), (2043, 16), (2048, 8), (2049, 72), (4127, 24), (13082, 8)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_column_sums_many_chunks(T, N, dtype):
+    test_layernorm_fwd_bwd(T, N, dtype)
+    test_bias_gelu_fwd_bwd(T, N, dtype)
+
+
 ATTN_CASES = [
     # B, S, heads, d, causal, lens
     (2, 64, 2, 64, True, None),
