@@ -1038,11 +1038,8 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         slots[slot].held = true;
         grp.items.push_back(PendingMb{slot, qbuf});
         qbuf = nullptr;                         // owned by the group now
-        if (completes) {
-            if ((rc = flush_group(dir, chunk))) return rc;
-        } else {
-            note_held();
-        }
+        note_held();                            // (before the flush: a complete group holds the most)
+        if (completes && (rc = flush_group(dir, chunk))) return rc;
     } else {
         if ((rc = release_group(grp, ss))) return rc;
         if (two) {

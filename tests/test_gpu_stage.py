@@ -133,6 +133,27 @@ def test_gradients_read_while_others_are_computed(n_micro, wgrad_group, stash_re
                 assert np.array_equal(early[k], g.grad(*k)), (it, k)
 
 
+@pytest.mark.parametrize("hidden,group,early", [(1024, 4, True), (1024, 2, True), (256, 4, False)])
+def test_peak_of_held_memory_counts_the_complete_group(hidden, group, early):
+    """With gradients worth reading early (16 MB and more in a chunk) the call that completes a weight-gradient
+    group writes into a group buffer like the others: at the peak the object holds `group` stashes and as many
+    buffers of dz, du, dy, dqkv; else the last micro-batch has its stash only."""
+    import paper_2410_19367_amd as bp
+    cfg = si.scaled(si.CONFIGS[1], name="held", layers=2, hidden=hidden, heads=4, seq=128, microbatch=2, causal=True, n_micro=group)
+    assert early == (cfg.layers * 12 * hidden * hidden * 4 >= 16 << 20)
+    with hz.GpuStage(cfg, max_inflight=2, wgrad_group=group) as g:
+        g.load_params(si.make_params(cfg, 0, 0.1))
+        bp.bp_stage_reset_peak_bytes(g.h)
+        stash = bp.bp_stage_stash_bytes(g.h)
+        buffer = cfg.layers * cfg.T * (cfg.F + 5 * hidden) * 2
+        for mb in range(group):
+            g.forward(0, mb, hz.to_dev(si.make_activation(cfg, "act_in", mb, 0), cfg.dtype))
+            g.backward(0, mb, hz.to_dev(si.make_activation(cfg, "grad_out", mb, 0), cfg.dtype))
+        held = bp.bp_stage_held_bytes(g.h)
+        assert (held["live_stash"], held["group_stash"], held["group_grads"]) == (0, 0, 0)
+        assert held["peak_total"] == group * stash + (group if early else group - 1) * buffer
+
+
 def test_small_fp32_bert_padded():
     cfg = si.scaled(si.CONFIGS[0], name="small_f32_bert", causal=False, len_lo=10, len_hi=64,
                     microbatch=3, n_micro=2)
