@@ -126,10 +126,10 @@ struct Stage : LaneState {
     bool lean = false;                   // stash without LN outputs and GELU output: recomputed for the weight gradients
     bool fuse_gelu = true;               // GELU forward/backward inside the GEMM epilogues when possible
     std::vector<PendGroup> pend[2];
-    // Reading gradients while the last group's GEMMs still run: flush_group leaves an event behind every
-    // weight gradient of direction 0 ([chunk][layer][k], k as in wgrad_one) and one in front of them all, behind
-    // which the side stream holds no column reduction that came before.  "ready" says that the event was
-    // recorded after the tensor's last writer; whoever writes in another way takes it back.
+    // Reading gradients while others are still computed: wgrad_one leaves an event behind every weight gradient of
+    // direction 0 ([chunk][layer][k]), flush_group one in front of a group's GEMMs, behind which the side stream
+    // holds no column reduction that came before.  "ready" says that the event was recorded after the tensor's last
+    // writer; whoever writes in another way takes it back.
     std::vector<hipEvent_t> ev_matrix;
     std::vector<uint8_t> matrix_ready;
     hipEvent_t ev_vectors = nullptr;
@@ -138,6 +138,7 @@ struct Stage : LaneState {
     // and the extra copy of grad_out cost more than they give (H 128, two layers, 2 MB: 1.63 -> 1.70 ms an
     // iteration; H 768, two layers, 57 MB: fp32 6.63 -> 5.62 ms).
     bool reads_early() const { return !is_view && (size_t)L * g_layer_bytes >= ((size_t)16 << 20); }
+    bool leaves_events(hipStream_t on) const { return on != stream && wgrad_group > 1 && reads_early(); }
     void forget_ready() { matrix_ready.assign(matrix_ready.size(), 0); vectors_ready = false; }
     size_t q_dz = 0, q_du = 0, q_dy = 0, q_dqkv = 0, q_layer_bytes = 0;
     int slot_capacity = 8;                           // most live stashes (held ones come on top)

@@ -556,6 +556,17 @@ int Stage::wgrad_one(int dir, int chunk, int l, int k, const void* cur_x, const 
     Scoped sc(this, BP_K_GEMM, 2.0 * Mk[k] * Nk[k] * (double)T * n, 0);
     hipError_t e = launch_gemm(dtype, g, ss);
     if (e != hipSuccess) return fail(BP_EHIP, "weight-gradient GEMM: %s", hipGetErrorString(e));
+    if (dir == 0 && leaves_events(ss)) {        // get_grad waits for this one only
+        const size_t i = ((size_t)chunk * L + l) * 4 + k;
+        if (matrix_ready.empty()) {
+            ev_matrix.assign((size_t)n_chunks * L * 4, nullptr);
+            matrix_ready.assign(ev_matrix.size(), 0);
+        }
+        e = ev_matrix[i] ? hipSuccess : hipEventCreateWithFlags(&ev_matrix[i], hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventRecord(ev_matrix[i], ss);
+        if (e != hipSuccess) return fail(BP_EHIP, "weight-gradient event: %s", hipGetErrorString(e));
+        matrix_ready[i] = 1;
+    }
     return BP_OK;
 }
 
@@ -586,31 +597,19 @@ int Stage::flush_group(int dir, int chunk) {
         if (e == hipSuccess) e = hipStreamWaitEvent(ss, ev_ready[0], 0);
         if (e != hipSuccess) return fail(BP_EHIP, "flush_group: %s", hipGetErrorString(e));
     }
-    // in the order in which the gradients are usually read (see get_grad), an event behind each
-    const bool events = ss != stream && dir == 0 && reads_early();
-    if (!events && dir == 0) forget_ready();
-    if (events) {
-        if (matrix_ready.empty()) {
-            ev_matrix.assign((size_t)n_chunks * L * 4, nullptr);
-            matrix_ready.assign(ev_matrix.size(), 0);
-        }
+    if (leaves_events(ss)) {
         hipError_t e = ev_vectors ? hipSuccess : hipEventCreateWithFlags(&ev_vectors, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventRecord(ev_vectors, ss);
         if (e != hipSuccess) return fail(BP_EHIP, "flush_group: %s", hipGetErrorString(e));
         vectors_ready = true;
+    } else {
+        forget_ready();
     }
     int rc;
-    for (int l = 0; l < L; ++l) {
+    for (int l = 0; l < L; ++l) {       // the order in which the gradients are usually read
         uint8_t& clean = grad_clean[dir][(size_t)chunk * L + l];
-        for (int k = 3; k >= 0; --k) {
+        for (int k = 3; k >= 0; --k)
             if ((rc = wgrad_one(dir, chunk, l, k, nullptr, nullptr, (clean & 1) ? 2 : 1, ss))) return rc;
-            if (!events) continue;
-            const size_t i = ((size_t)chunk * L + l) * 4 + k;
-            hipError_t e = ev_matrix[i] ? hipSuccess : hipEventCreateWithFlags(&ev_matrix[i], hipEventDisableTiming);
-            if (e == hipSuccess) e = hipEventRecord(ev_matrix[i], ss);
-            if (e != hipSuccess) return fail(BP_EHIP, "flush_group: %s", hipGetErrorString(e));
-            matrix_ready[i] = 1;
-        }
         clean &= ~1;
     }
     if ((rc = release_group(grp, ss))) return rc;
@@ -891,14 +890,18 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
     // GEMMs of every layer are postponed; the tensors they need (dz, du, dy, dqkv) are then
     // produced straight into a buffer that lives until the group is complete, and the stash stays
     // held.  The call that completes the group multiplies over all waiting micro-batches at once.
-    // With a side stream (and enough to read), the completing call too writes into such a buffer and multiplies at its end,
-    // in the order in which get_grad is usually called: behind the last backward of an iteration the
-    // gradients are then read one by one while the GEMMs run.
+    // With a side stream (and enough to read), the completing call too writes into such a buffer and multiplies at
+    // its end, in the order in which get_grad is usually called, if no other stash is live: behind the last backward of an
+    // iteration the gradients are then read one by one while the GEMMs run.  While others are live more backwards
+    // follow, and the GEMMs start as soon as their operands exist, beside the rest of this call's chain (two groups
+    // an iteration, forwards one ahead: H 1024 677 -> 691 TFLOP/s with nothing read, 15.19 -> 15.09 ms with all
+    // read, H 2560 45.7 -> 45.5 ms).  A stream of their own and spare buffers, so that the next backward need
+    // not wait for the GEMMs, gave nothing over this, and 1 % less at H 5120, where single products fill the chip.
     PendGroup& grp = pend[dir][chunk];
     const bool completes = (int)grp.items.size() + 1 >= wgrad_group;
-    const bool defer = !completes || (wgrad_group > 1 && two && reads_early());
-    vectors_ready = false;                  // column reductions and, without grouping, GEMMs are on their way
-    if (!defer) forget_ready();
+    const bool defer = !completes || (leaves_events(ss) && live_slots() == 1);
+    vectors_ready = false;                  // column reductions are on their way
+    if (!leaves_events(ss)) forget_ready(); // ... and GEMMs without events behind them
     char* qbuf = nullptr;
     if (defer) {
         if (!pend_pool.empty()) {

@@ -154,6 +154,27 @@ def test_peak_of_held_memory_counts_the_complete_group(hidden, group, early):
         assert held["peak_total"] == group * stash + (group if early else group - 1) * buffer
 
 
+def test_group_completed_while_a_stash_is_live_multiplies_at_once():
+    """F0 F1 B0 F2 B1 F3 B2 B3 in groups of two: B1 completes a group while the stash of F2 is live, so more backwards
+    follow and its weight gradients start beside its own chain, without a group buffer; B3 is the last one.
+    The most that is held is then at F2: its stash, that of F1, that of the waiting B0 and B0's buffer."""
+    import paper_2410_19367_amd as bp
+    cfg = si.scaled(si.CONFIGS[1], name="held_ahead", layers=2, hidden=1024, heads=4, seq=128, microbatch=2, causal=True, n_micro=4)
+    with hz.GpuStage(cfg, max_inflight=2, wgrad_group=2, forward_ahead=1) as g:
+        g.load_params(si.make_params(cfg, 0, 0.1))
+        bp.bp_stage_reset_peak_bytes(g.h)
+        xs = [hz.to_dev(si.make_activation(cfg, "act_in", mb, 0), cfg.dtype) for mb in range(4)]
+        dys = [hz.to_dev(si.make_activation(cfg, "grad_out", mb, 0), cfg.dtype) for mb in range(4)]
+        g.forward(0, 0, xs[0])
+        for mb in range(4):
+            if mb + 1 < 4:
+                g.forward(0, mb + 1, xs[mb + 1])
+            g.backward(0, mb, dys[mb])
+        bp.bp_stage_wait_forward(g.h)
+        buffer = cfg.layers * cfg.T * (cfg.F + 5 * cfg.hidden) * 2
+        assert bp.bp_stage_held_bytes(g.h)["peak_total"] == 3 * bp.bp_stage_stash_bytes(g.h) + buffer
+
+
 def test_small_fp32_bert_padded():
     cfg = si.scaled(si.CONFIGS[0], name="small_f32_bert", causal=False, len_lo=10, len_hi=64,
                     microbatch=3, n_micro=2)
