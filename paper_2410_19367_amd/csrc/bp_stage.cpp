@@ -899,7 +899,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
     // not wait for the GEMMs, gave nothing over this, and 1 % less at H 5120, where single products fill the chip.
     PendGroup& grp = pend[dir][chunk];
     const bool completes = (int)grp.items.size() + 1 >= wgrad_group;
-    const bool defer = !completes || (leaves_events(ss) && live_slots() == 1);
+    bool defer = !completes || (leaves_events(ss) && live_slots() == 1);
     vectors_ready = false;                  // column reductions are on their way
     if (!leaves_events(ss)) forget_ready(); // ... and GEMMs without events behind them
     char* qbuf = nullptr;
@@ -908,7 +908,9 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             qbuf = (char*)pend_pool.back();
             pend_pool.pop_back();
         } else if ((rc = dev_alloc((void**)&qbuf, (size_t)L * q_layer_bytes))) {
-            return rc;
+            if (!completes) return rc;
+            qbuf = nullptr;             // no room for the one buffer more: multiply along the way
+            defer = false;
         }
     }
     struct PoolGuard {      // hand the buffer back if the call fails half-way
