@@ -103,34 +103,148 @@ def test_forward_ahead_any_lead_gives_the_same_bits(seed):
         assert np.array_equal(grads_a[k], grads_b[k]), k
 
 
-@pytest.mark.parametrize("n_micro,wgrad_group,stash_recompute", [(4, 4, 0), (8, 4, 0), (5, 2, 0), (3, 1, 0), (4, 4, 1)])
-@pytest.mark.parametrize("backwards", [False, True])
-def test_gradients_read_while_others_are_computed(n_micro, wgrad_group, stash_recompute, backwards):
-    """bp_stage_get_grad waits for the tensor it copies and not for the weight-gradient GEMMs behind it: read
-    right after the last call, in either order of the tensors, on two chunks and two iterations, every
-    gradient has the bits that it has after a device synchronisation."""
-    import torch
-    cfg = si.scaled(si.CONFIGS[1], name="read_early", layers=2, hidden=1024, heads=8, seq=256, microbatch=4, causal=True,
-                    n_chunks=2, n_micro=n_micro)
-    params = si.make_params(cfg, 0, 0.1)
-    xs = [hz.to_dev(si.make_activation(cfg, "act_in", mb, 0), cfg.dtype) for mb in range(n_micro)]
-    gs = [hz.to_dev(si.make_activation(cfg, "grad_out", mb, 0), cfg.dtype) for mb in range(n_micro)]
-    names = [(c, l, n) for c in range(2) for l in range(cfg.layers) for n in si.PARAM_NAMES]
-    if backwards:
-        names = names[::-1]
-    with hz.GpuStage(cfg, max_inflight=2, wgrad_group=wgrad_group, stash_recompute=stash_recompute) as g:
-        g.load_params(params)
-        for it in range(2):
-            g.bp.bp_stage_zero_grad(g.h)
-            for mb in range(n_micro):
-                for c in (0, 1):
-                    g.forward(c, mb, xs[mb])
-                for c in (0, 1):
-                    g.backward(c, mb, gs[mb])
-            early = {k: g.grad(*k) for k in names}
+class _EarlyReads:
+    """Iterations on two chunks (four for a schedule) whose gradients are worth reading early, with other inputs in
+    every iteration: what a read right behind the last call gives is compared with what an object gives that is
+    synchronised before every step."""
+
+    def __init__(self, n_micro=4, wgrad_group=4, stash_recompute=0, forward_ahead=0, n_chunks=2, layers=2):
+        self.opts = dict(max_inflight=n_chunks * 2, wgrad_group=wgrad_group, stash_recompute=stash_recompute,
+                         forward_ahead=forward_ahead)
+        self.cfg = si.scaled(si.CONFIGS[1], name="read_early", layers=layers, hidden=1024, heads=8, seq=256, microbatch=4,
+                             causal=True, n_chunks=n_chunks, n_micro=n_micro)
+        self.params = si.make_params(self.cfg, 0, 0.1)
+        self.names = [(c, l, n) for c in range(n_chunks) for l in range(layers) for n in si.PARAM_NAMES]
+
+    def data(self, role, mb, it):
+        return hz.to_dev(si.make_activation(self.cfg, role, mb, it), self.cfg.dtype)
+
+    def stage(self):
+        g = hz.GpuStage(self.cfg, **self.opts)
+        g.load_params(self.params)
+        return g
+
+    def iteration(self, g, it, direction=lambda mb: 0, sync=False):
+        import torch
+        n = self.cfg.n_micro
+        ins = [(self.data("act_in", mb, it), self.data("grad_out", mb, it)) for mb in range(n)]
+        torch.cuda.synchronize()
+        step = torch.cuda.synchronize if sync else (lambda: None)
+        g.bp.bp_stage_zero_grad(g.h)
+        keep = []                                   # (outputs stay allocated until the caller has read)
+        def forward(mb):
+            for c in range(self.cfg.n_chunks):
+                keep.append(g.forward(c, mb, ins[mb][0])); step()
+        lead = 1 if self.opts["forward_ahead"] else 0
+        if lead:
+            forward(0)
+        for mb in range(n):
+            if mb + lead < n:
+                forward(mb + lead)
+            for c in range(self.cfg.n_chunks):
+                keep.append(g.backward(c, mb, ins[mb][1], direction(mb))); step()
+        g.bp.bp_stage_wait_forward(g.h)
+        return ins, keep
+
+    def reference(self, it, **kw):
+        import torch
+        with self.stage() as g:
+            keep = self.iteration(g, it, sync=True, **kw)
+            g.grad(*self.names[-1])                 # completes the open groups
             torch.cuda.synchronize()
-            for k in names:
-                assert np.array_equal(early[k], g.grad(*k)), (it, k)
+            return {k: g.grad(*k) for k in self.names}
+
+
+def _assert_same(got, ref, what):
+    for k in got:
+        assert np.array_equal(got[k], ref[k]), (what, k)
+
+
+@pytest.mark.parametrize("n_micro,wgrad_group,stash_recompute,forward_ahead", [
+    (4, 4, 0, 0), (8, 4, 0, 0), (5, 2, 0, 0), (3, 1, 0, 0), (4, 4, 1, 0), (4, 4, 0, 1), (6, 2, 0, 1), (5, 4, 1, 1)])
+@pytest.mark.parametrize("backwards", [False, True])
+def test_gradients_read_while_others_are_computed(n_micro, wgrad_group, stash_recompute, forward_ahead, backwards):
+    """bp_stage_get_grad waits for the tensor it copies and not for the weight-gradient GEMMs behind it: read
+    right after the last call, in either order of the tensors, on two chunks and in two iterations over different
+    inputs, every gradient has the bits of a synchronised run."""
+    e = _EarlyReads(n_micro, wgrad_group, stash_recompute, forward_ahead)
+    with e.stage() as g:
+        for it in range(2):
+            keep = e.iteration(g, it)
+            got = {k: g.grad(*k) for k in (e.names[::-1] if backwards else e.names)}
+            _assert_same(got, e.reference(it), it)
+
+
+@pytest.mark.parametrize("forward_ahead", [0, 1])
+def test_next_iteration_while_gradients_are_still_computed(forward_ahead):
+    """One tensor read, the gradients cleared and the next iteration issued at once, while weight gradients of the
+    one before still run; then once more with the launches timed (one stream) and once after that."""
+    e = _EarlyReads(forward_ahead=forward_ahead)
+    with e.stage() as g:
+        keep, first = [], []
+        for it in range(4):
+            if it == 2:
+                g.bp.bp_prof_enable(g.h, 1)
+            elif it == 3:
+                g.bp.bp_prof_enable(g.h, 0)
+            keep.append(e.iteration(g, it))
+            first.append({e.names[0]: g.grad(*e.names[0])})
+        last = {k: g.grad(*k) for k in e.names}
+    refs = [e.reference(it) for it in range(4)]
+    for it in range(4):
+        _assert_same(first[it], refs[it], it)
+    _assert_same(last, refs[3], "last")
+
+
+@pytest.mark.parametrize("stash_recompute", [0, 1])
+def test_parameters_set_while_gradients_are_still_computed(stash_recompute):
+    """Parameters set right after the first read: the gradients still to come are those of the old ones (the
+    weight gradients of the reduced stash read LayerNorm parameters and b1 when they run)."""
+    e = _EarlyReads(stash_recompute=stash_recompute)
+    ref = e.reference(0)
+    with e.stage() as g:
+        keep = e.iteration(g, 0)
+        got = {e.names[0]: g.grad(*e.names[0])}
+        for c, l, n in e.names:
+            g.bp.bp_stage_set_param(g.h, c, l, g.bp.TENSOR_IDS[n], np.full(si.param_shape(e.cfg, n), 0.5, np.float32))
+        got.update({k: g.grad(*k) for k in e.names[1:]})
+        _assert_same(got, ref, "old parameters")
+
+
+def test_schedule_while_gradients_are_still_computed():
+    """A whole schedule iteration right after the first read: its gradients are those of an object that has done
+    nothing else."""
+    import torch
+    e = _EarlyReads(n_chunks=4, layers=1)
+    runs = []
+    for before in (False, True):
+        with e.stage() as g:
+            if before:
+                keep = e.iteration(g, 0)
+                g.grad(*e.names[0])
+            order = g.bp.bp_schedule_generate(2, e.cfg.n_micro)
+            x = torch.stack([e.data("act_in", mb, 7) for mb in range(e.cfg.n_micro)])
+            y = torch.stack([e.data("target", mb, 7) for mb in range(e.cfg.n_micro)])
+            g.bp.bp_run_schedule(g.h, order, 2, x, y)
+            runs.append({k: g.grad(*k) for k in e.names})
+    _assert_same(runs[1], runs[0], "schedule")
+
+
+def test_two_directions_read_while_gradients_are_still_computed():
+    """Micro-batches 0, 1, 4, 5 in one direction, the others in the other: a read gives direction 0 alone; after the
+    merge both, as a synchronised object gives them."""
+    import torch
+    e = _EarlyReads(n_micro=8, wgrad_group=2)
+    direction = lambda mb: mb // 2 % 2
+    merged, first = [], []
+    for sync in (True, False):
+        with e.stage() as g:
+            keep = e.iteration(g, 0, direction=direction, sync=sync)
+            first.append({k: g.grad(*k) for k in e.names})
+            g.bp.bp_stage_merge_directions(g.h)
+            merged.append({k: g.grad(*k) for k in e.names})
+    _assert_same(first[1], first[0], "direction 0")
+    _assert_same(merged[1], merged[0], "both")
 
 
 @pytest.mark.parametrize("hidden,group,early", [(1024, 4, True), (1024, 2, True), (256, 4, False)])
