@@ -124,7 +124,6 @@ struct Stage : LaneState {
     // Grouped weight gradients: per (direction, chunk) the micro-batches waiting for their group.
     int wgrad_group = 1;
     bool lean = false;                   // stash without LN outputs and GELU output: recomputed for the weight gradients
-    bool fuse_gelu = true;               // GELU forward/backward inside the GEMM epilogues when possible
     std::vector<PendGroup> pend[2];
     // Reading gradients while others are still computed: wgrad_one leaves an event behind every weight gradient of
     // direction 0 ([chunk][layer][k]), flush_group one in front of a group's GEMMs, behind which the side stream

@@ -317,7 +317,7 @@ int Stage::make_view(Stage** out) {
     v->L = L; v->H = H; v->heads = heads; v->d = d; v->S = S; v->B = B; v->T = T; v->F = F; v->n_chunks = n_chunks;
     v->causal = causal; v->dtype = dtype; v->max_inflight = max_inflight; v->esz = esz; v->eps = eps;
     v->overlap = overlap; v->params = params; v->grads[0] = grads[0]; v->grads[1] = grads[1];
-    v->wgrad_group = wgrad_group; v->lean = lean; v->fuse_gelu = fuse_gelu;
+    v->wgrad_group = wgrad_group; v->lean = lean;
     v->q_dz = q_dz; v->q_du = q_du; v->q_dy = q_dy; v->q_dqkv = q_dqkv; v->q_layer_bytes = q_layer_bytes;
     memcpy(v->p_off, p_off, sizeof p_off); memcpy(v->g_off, g_off, sizeof g_off);
     v->p_layer_bytes = p_layer_bytes; v->g_layer_bytes = g_layer_bytes;
@@ -805,24 +805,16 @@ int Stage::forward(int chunk, int mb, const void* act_in, void* act_out) {
                                     (const float*)param(chunk, l, BP_LN2_B), eps, m_out,
                                     (float*)(sb + s_mean2), (float*)(sb + s_rstd2), nullptr, fs));
         }
-        {   // u = m W1 and g = gelu(u + b1): one kernel when the GEMM can carry the activation
+        {   // u = m W1 and g = gelu(u + b1) in one kernel: every operand is the library's own, with aligned rows
             GemmArgs fg;
             fg.A = m_out; fg.B = param_t(chunk, l, BP_W1); fg.C = sb + s_u;
             fg.bias = (const float*)param(chunk, l, BP_B1); fg.residual = nullptr;
             fg.M = T; fg.N = F; fg.K = H; fg.lda = H; fg.ldb = H; fg.ldc = F;
             fg.a_t = 0; fg.b_t = 1; fg.accumulate = 0;
             fg.epi = EPI_GELU_FWD; fg.C2 = g_out;
-            if (fuse_gelu && gemm_can_fuse_epilogue(dtype, fg)) {
-                prof.tag_gemm(T, F, H, 0, 1, 1, EPI_GELU_FWD);
-                Scoped sc(this, BP_K_GEMM, 2.0 * T * (double)F * H, 0);
-                BP_LAUNCH(launch_gemm(dtype, fg, fs));
-            } else {
-                if ((rc = gemm(m_out, H, 0, param_t(chunk, l, BP_W1), H, 1, sb + s_u, F, T, F, H, nullptr,
-                               nullptr, 0, fs, true))) return rc;
-                Scoped sc(this, BP_K_GELU_FWD, 0, 2.0 * T * F * esz);
-                BP_LAUNCH(launch_gelu_fwd(dtype, T, F, sb + s_u, (const float*)param(chunk, l, BP_B1),
-                                          g_out, fs));
-            }
+            prof.tag_gemm(T, F, H, 0, 1, 1, EPI_GELU_FWD);
+            Scoped sc(this, BP_K_GEMM, 2.0 * T * (double)F * H, 0);
+            BP_LAUNCH(launch_gemm(dtype, fg, fs));
         }
         if ((rc = gemm(g_out, F, 0, param_t(chunk, l, BP_W2), F, 1, z, H, T, H, F,
                        (const float*)param(chunk, l, BP_B2), sb + s_y, 0, fs, true))) return rc;
@@ -958,13 +950,13 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         // z = y + g W2 + b2
         BP_HIP(hand_over(0));                                                                               // dz
         if (!defer && (rc = wgrad_one(dir, chunk, l, 0, sb, dz, acc, ss))) return rc;                 // dW2
-        {   // du = (dz W2^T) * gelu'(u + b1) with the db1 partials: one kernel when the GEMM can carry it
+        {   // du = (dz W2^T) * gelu'(u + b1) with the db1 partials: one kernel unless the caller's gradient is unaligned
             GemmArgs bg;
             bg.A = dz; bg.B = P(BP_W2); bg.C = big1; bg.bias = (const float*)P(BP_B1); bg.residual = nullptr;
             bg.M = T; bg.N = F; bg.K = H; bg.lda = H; bg.ldb = H; bg.ldc = F;
             bg.a_t = 0; bg.b_t = 1; bg.accumulate = 0;
             bg.epi = EPI_GELU_BWD; bg.U = sb + s_u; bg.colpart = p_b1;
-            if (fuse_gelu && gemm_can_fuse_epilogue(dtype, bg)) {
+            if (gemm_can_fuse_epilogue(dtype, bg)) {
                 prof.tag_gemm(T, F, H, 0, 1, 1, EPI_GELU_BWD);
                 Scoped sc(this, BP_K_GEMM, 2.0 * T * (double)F * H, 0);
                 BP_LAUNCH(launch_gemm(dtype, bg, stream));

@@ -63,9 +63,9 @@ template <int R> constexpr int tile_bytes() { return R * BK * 2; }
 
 // ---- global -> registers -> LDS for one operand slice.
 // NT threads copy R*8 chunks of 16 bytes; CH = chunks per thread.
-template <int R, int NT, bool RMAJOR, bool RAGGED>
+template <int R, int NTHREADS, bool RMAJOR>
 struct TileLoader {
-    static constexpr int CH = R * 8 / NT;
+    static constexpr int CH = R * 8 / NTHREADS;
     u32x4 regs[CH];
 
     // rows_valid: number of valid rows of this tile (M or N remainder); k_valid: valid k in slice
@@ -73,25 +73,21 @@ struct TileLoader {
                                          int k_valid) {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            const int q = threadIdx.x + i * NT;
+            const int q = threadIdx.x + i * NTHREADS;
             int row, k;
             if (RMAJOR) { k = q / (R / 8); row = (q % (R / 8)) * 8; }
             else { row = q >> 3; k = (q & 7) * 8; }
             const bf16_t* p = RMAJOR ? base + (size_t)k * ld + row : base + (size_t)row * ld + k;
-            if (RAGGED) {
-                // chunks are 8 elements along the contiguous axis; shapes are multiples of 8 there
-                const bool ok = row < rows_valid && k < k_valid;
-                const u32x4 zero = {0u, 0u, 0u, 0u};
-                regs[i] = ok ? *reinterpret_cast<const u32x4*>(p) : zero;
-            } else {
-                regs[i] = *reinterpret_cast<const u32x4*>(p);
-            }
+            // chunks are 8 elements along the contiguous axis; shapes are multiples of 8 there
+            const bool ok = row < rows_valid && k < k_valid;
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            regs[i] = ok ? *reinterpret_cast<const u32x4*>(p) : zero;
         }
     }
     __device__ __forceinline__ void store(char* lds) const {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            const int q = threadIdx.x + i * NT;
+            const int q = threadIdx.x + i * NTHREADS;
             int off;
             if (RMAJOR) off = rmajor_off<R>(q / (R / 8), q % (R / 8));
             else off = kmajor_off(q >> 3, q & 7);
@@ -129,9 +125,9 @@ __device__ __forceinline__ bf16x8 read_frag(const char* lds, int row0, int kk, i
 
 // ---- the kernel
 // WM x WN waves, each owning a (BM/WM) x (BN/WN) sub-tile made of 32x32 MFMA tiles.
-template <int BM, int BN, int WM, int WN, bool A_RMAJOR, bool B_RMAJOR, bool RAGGED>
+template <int BM, int BN, int WM, int WN, bool A_RMAJOR, bool B_RMAJOR>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-    constexpr int NT = WM * WN * 64;
+    constexpr int NTHREADS = WM * WN * 64;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;   // MFMA tiles per wave
     constexpr int A_BYTES = tile_bytes<BM>(), B_BYTES = tile_bytes<BN>();
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -157,8 +153,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_kernel(GemmArgs g, int 
     const size_t b_step = B_RMAJOR ? (size_t)BK * g.ldb : BK;
     const int m_valid = g.M - m0, n_valid = g.N - n0;
 
-    TileLoader<BM, NT, A_RMAJOR, RAGGED> la;
-    TileLoader<BN, NT, B_RMAJOR, RAGGED> lb;
+    TileLoader<BM, NTHREADS, A_RMAJOR> la;
+    TileLoader<BN, NTHREADS, B_RMAJOR> lb;
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -217,14 +213,14 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_kernel(GemmArgs g, int 
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int n = n0 + wn * (BN / WN) + j * 32 + col_l;
-        if (RAGGED && n >= g.N) continue;
+        if (n >= g.N) continue;
         const float bias = (!g.accumulate && g.bias) ? g.bias[n] : 0.f;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int m = m0 + wm * (BM / WM) + i * 32 + 8 * (v >> 2) + row_l + (v & 3);
-                if (RAGGED && m >= g.M) continue;
+                if (m >= g.M) continue;
                 const size_t o = (size_t)m * g.ldc + n;
                 if (g.accumulate) {
                     float* c = (float*)g.C + o;
@@ -591,9 +587,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     auto interleave_boundary = [&]() { SchedRounds<0, NMFMA, NREAD, LPT, LF>::apply(); };
     // wait until at most `n` of the most recently requested slices are still on their way
     auto wait_slices = [&](int n) {
-        if (NS > 4 && n >= 3) { BP_WAIT_VMCNT(3 * LPT); }
-        else if (NS > 3 && n == 2) { BP_WAIT_VMCNT(2 * LPT); }
-        else if (NS > 2 && n == 1) { BP_WAIT_VMCNT(1 * LPT); }
+        if (NS > 2 && n == 1) { BP_WAIT_VMCNT(1 * LPT); }
         else { BP_WAIT_VMCNT(0); }
     };
 
@@ -952,14 +946,14 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
 }
 
 // ---- host-side selection
-template <int BM, int BN, int WM, int WN, bool RAGGED>
+template <int BM, int BN, int WM, int WN>
 static hipError_t launch_cfg(const GemmArgs& g, hipStream_t s) {
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     const dim3 grid(tiles_m * tiles_n), block(WM * WN * 64);
     const size_t smem = 2 * (size_t)(tile_bytes<BM>() + tile_bytes<BN>());
 #define BP_GEMM_LAUNCH(AR, BR)                                                                   \
     do {                                                                                         \
-        auto kern = gemm_mfma_kernel<BM, BN, WM, WN, AR, BR, RAGGED>;                            \
+        auto kern = gemm_mfma_kernel<BM, BN, WM, WN, AR, BR>;                                    \
         static std::atomic<bool> attr_set{false};   /* once per instantiation; host threads may race */ \
         if (smem > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {                                                     \
             hipError_t e = hipFuncSetAttribute((const void*)kern,                                \
@@ -1026,7 +1020,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, int spli
     }
 }
 
-template <int BM, int BN, int WM, int WN, int NS, int BKT, bool MI16, bool RING, bool RAG>
+// Operand forms (which of op(A), op(B) is r-major) that a tile shape is launched in; the others are not compiled.
+enum { NT = 1, TN = 2, OTHER = 4 };     // forward / data gradient; weight gradient; the remaining two
+
+template <int FORMS, bool SPLIT, int BM, int BN, int WM, int WN, int NS, int BKT, bool MI16, bool RING, bool RAG>
 static hipError_t launch_dma_rag(const GemmArgs& g, hipStream_t s, int splits, int n_full) {
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     const int nblk = tiles_m * tiles_n;
@@ -1051,25 +1048,30 @@ static hipError_t launch_dma_rag(const GemmArgs& g, hipStream_t s, int splits, i
         }                                                                                        \
         hipLaunchKernelGGL(kern, grid, block, smem, s, g, tiles_m, tiles_n, splits, n_full);     \
     } while (0)
-    if (!g.a_t && !g.b_t) BP_GEMM_LAUNCH(false, true);
-    else if (!g.a_t && g.b_t) BP_GEMM_LAUNCH(false, false);
-    else if (g.a_t && !g.b_t) BP_GEMM_LAUNCH(true, true);
-    else BP_GEMM_LAUNCH(true, false);
+    const int form = g.a_t == g.b_t ? OTHER : g.a_t ? TN : NT;
+    if (!(form & FORMS) || (!SPLIT && n_tail)) return hipErrorInvalidValue;
+    if constexpr (FORMS & NT) if (form == NT) BP_GEMM_LAUNCH(false, false);
+    if constexpr (FORMS & TN) if (form == TN) BP_GEMM_LAUNCH(true, true);
+    if constexpr (FORMS & OTHER) {
+        if (form == OTHER && !g.a_t) BP_GEMM_LAUNCH(false, true);
+        if (form == OTHER && g.a_t) BP_GEMM_LAUNCH(true, false);
+    }
 #undef BP_GEMM_LAUNCH
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n_tail == 0) return e;
-    hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, RAG>), dim3((unsigned)(n_tail * (BM * BN / 2048))), dim3(256), 0, s,
-                       g, splits, tiles_m, tiles_n, n_full);
+    if constexpr (SPLIT)
+        hipLaunchKernelGGL((splitk_reduce_kernel<BM, BN, RAG>), dim3((unsigned)(n_tail * (BM * BN / 2048))), dim3(256), 0, s,
+                           g, splits, tiles_m, tiles_n, n_full);
     return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int NS, int BKT = 64, bool MI16 = false, bool RING = false>
+template <int FORMS, bool SPLIT, int BM, int BN, int WM, int WN, int NS, int BKT = 64, bool MI16 = false, bool RING = false>
 static hipError_t launch_dma(const GemmArgs& g, hipStream_t s, int splits = 1, int n_full = -1) {
     // (slices of the other variant are addressed by 32-bit byte offsets from the tile's first row)
     const bool beyond = (g.a_t && 2L * g.K * g.lda > 0xffffffffL) || (!g.b_t && 2L * g.K * g.ldb > 0xffffffffL);
     if (g.M % BM || g.N % BN || g.K % BKT || beyond)
-        return launch_dma_rag<BM, BN, WM, WN, NS, BKT, MI16, RING, true>(g, s, splits, n_full);
-    return launch_dma_rag<BM, BN, WM, WN, NS, BKT, MI16, RING, false>(g, s, splits, n_full);
+        return launch_dma_rag<FORMS, SPLIT, BM, BN, WM, WN, NS, BKT, MI16, RING, true>(g, s, splits, n_full);
+    return launch_dma_rag<FORMS, SPLIT, BM, BN, WM, WN, NS, BKT, MI16, RING, false>(g, s, splits, n_full);
 }
 
 bool gemm_mfma_supported(const GemmArgs& g) {
@@ -1110,7 +1112,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     // (several segments come as weight gradients; the forward form's large tiles walk through one)
     if (g.nseg > 1 && (!dma || (!g.a_t && g.b_t)))
         return launch_gemm_per_segment(g, s, [](const GemmArgs& h, hipStream_t st) { return launch_gemm_mfma(h, st); });
-    if (!dma) return launch_cfg<128, 128, 2, 2, true>(g, s);
+    if (!dma) return launch_cfg<128, 128, 2, 2>(g, s);
     const int ncu = cu_count();
     const long k_total = (long)g.K * g.nseg;
     const long most = 3L * ncu / 4;       // a launch with at least this many blocks is taken to fill the chip
@@ -1155,24 +1157,24 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
         const double rounds = (double)(full / ncu) + (tail ? 1.0 / splits : 0.0);
         const double rounds192 = t192 >= most ? (double)((t192 + ncu - 1) / ncu) * 0.75 / 0.69 : 1e9;
         if ((full || 2 * tail * splits >= ncu) && rounds <= rounds192) {
-            if (splits > 1) return launch_dma<256, 256, 2, 4, 5, 64, true, true>(g, s, splits, (int)full);
-            return launch_dma<256, 256, 2, 4, 5, 64, true, true>(g, s);
+            if (splits > 1) return launch_dma<TN, true, 256, 256, 2, 4, 5, 64, true, true>(g, s, splits, (int)full);
+            return launch_dma<TN, true, 256, 256, 2, 4, 5, 64, true, true>(g, s);
         }
     }
     if (g.epi == EPI_NONE && t192 >= most && rate192 * fill(t192) * useful(256, 192) > fill(t256) * useful(256, 256)) {
-        if (nt) return launch_dma<256, 192, 2, 4, 2, 64, true>(g, s);
-        return launch_dma<256, 192, 4, 2, 2>(g, s);
+        if (nt) return launch_dma<NT, false, 256, 192, 2, 4, 2, 64, true>(g, s);
+        return launch_dma<TN | OTHER, false, 256, 192, 4, 2, 2>(g, s);
     }
     if (t256 >= most) {
         const long full = (t256 / ncu) * ncu, tail = t256 - full;
         const int splits =
             (g.split_ws && g.epi == EPI_NONE && tail < most) ? tail_splits(tail) : 1;
         if (g.a_t && !g.b_t) {      // weight gradients: the five-slot ring
-            if (splits > 1) return launch_dma<256, 256, 2, 4, 5, 64, true, true>(g, s, splits, (int)full);
-            return launch_dma<256, 256, 2, 4, 5, 64, true, true>(g, s);
+            if (splits > 1) return launch_dma<TN, true, 256, 256, 2, 4, 5, 64, true, true>(g, s, splits, (int)full);
+            return launch_dma<TN, true, 256, 256, 2, 4, 5, 64, true, true>(g, s);
         }
-        if (splits > 1) return launch_dma<256, 256, 2, 4, 2, 64, true>(g, s, splits, (int)full);
-        return launch_dma<256, 256, 2, 4, 2, 64, true>(g, s);
+        if (splits > 1) return launch_dma<NT | OTHER, true, 256, 256, 2, 4, 2, 64, true>(g, s, splits, (int)full);
+        return launch_dma<NT | OTHER, true, 256, 256, 2, 4, 2, 64, true>(g, s);
     }
     // Too few 256 x 256 tiles to fill the chip.  Up to a contraction depth of 4096, 128 x 128 tiles
     // that do fill it win over large tiles cut along K: one launch, no fp32 partials (inside the
@@ -1214,41 +1216,41 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     const long small_depth = slices <= 1 || (slices == 2 && t64 <= ncu) ? k_total :
                              t64 > ncu ? (edges ? 3584 : 5120) :
                              slices == 3 || t64 > ncu / 2 ? 6144 : t64 > ncu / 4 ? 3584 : 3072;
-    if (nt && t64 <= ncu && k_total <= small_depth) return launch_dma<64, 64, 2, 2, 3, 128, true>(g, s);
+    if (nt && t64 <= ncu && k_total <= small_depth) return launch_dma<NT | TN, false, 64, 64, 2, 2, 3, 128, true>(g, s);
     if (nt && t64 <= 2L * ncu && k_total <= small_depth)
-        return launch_dma<128, 64, 2, 2, 3, 64, true>(g, s);
-    if (wgrad && t64 <= ncu && k_total <= 2048) return launch_dma<64, 64, 2, 2, 3, 128, true>(g, s);
+        return launch_dma<NT, false, 128, 64, 2, 2, 3, 64, true>(g, s);
+    if (wgrad && t64 <= ncu && k_total <= 2048) return launch_dma<NT | TN, false, 64, 64, 2, 2, 3, 128, true>(g, s);
     const bool deep = g.K % 128 == 0 || (g.K % BK != 0 && g.K > 512);   // slices of 128 along K
     const bool small_fill = t128 >= most && (k_total <= 4096 || (nt && k_total <= 8192 && fill(t128) >= 0.95));
     if (small_fill && !wgrad) {
-        if (nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s);
-        if (deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s);
-        return launch_dma<128, 128, 2, 4, 2>(g, s);
+        if (nt) return launch_dma<NT, true, 128, 128, 2, 4, 3, 64, true>(g, s);
+        if (deep) return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2, 128>(g, s);
+        return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2>(g, s);
     }
     // Fewer tiles than that but a long K: 256 x 256 tiles on K slices keep the operand traffic per
     // flop at the large-tile level (128 x 128 tiles move twice the operand bytes per flop).
     if (t256 > 0 && g.split_ws && g.epi == EPI_NONE) {
         const int splits = tail_splits(t256);
         if (splits > 1 && t256 * splits * 8 >= 5L * ncu) {
-            if (g.a_t && !g.b_t) return launch_dma<256, 256, 2, 4, 5, 64, true, true>(g, s, splits, 0);
-            return launch_dma<256, 256, 2, 4, 2, 64, true>(g, s, splits, 0);
+            if (g.a_t && !g.b_t) return launch_dma<TN, true, 256, 256, 2, 4, 5, 64, true, true>(g, s, splits, 0);
+            return launch_dma<NT | OTHER, true, 256, 256, 2, 4, 2, 64, true>(g, s, splits, 0);
         }
     }
     // Small outputs (128 x 128 tiles on fewer than three quarters of the CUs) with a long K: the same split, on the small
     // tiles (slices at least 1024 deep: below that the second kernel costs what the split gains)
     if (slices > 1) {
-        if (nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s, slices, 0);
-        if (deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s, slices, 0);
-        return launch_dma<128, 128, 2, 4, 2>(g, s, slices, 0);
+        if (nt) return launch_dma<NT, true, 128, 128, 2, 4, 3, 64, true>(g, s, slices, 0);
+        if (deep) return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2, 128>(g, s, slices, 0);
+        return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2>(g, s, slices, 0);
     }
     // 8 waves (2 per SIMD) hide the LDS and load latencies better than 4 on 128 x 128 tiles.
     // Forward / data-gradient form: 16x16x32 MFMAs and loads first, as on the large tiles, and three
     // stages of 64 along K (96 KB), so that a slice has two barriers to land (against two stages of
     // 128: 2048^3 20.7 us against 21.9 us, 2048 x 2048 x 8192 63.7 us against 67.9 us).  The other forms: slices of 128 along K (two stages of 64 KB),
     // which halve the number of barriers per MFMA.
-    if (nt) return launch_dma<128, 128, 2, 4, 3, 64, true>(g, s);
-    if (deep) return launch_dma<128, 128, 2, 4, 2, 128>(g, s);
-    return launch_dma<128, 128, 2, 4, 2>(g, s);
+    if (nt) return launch_dma<NT, true, 128, 128, 2, 4, 3, 64, true>(g, s);
+    if (deep) return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2, 128>(g, s);
+    return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2>(g, s);
 }
 
 }  // namespace bp
