@@ -84,8 +84,8 @@ __device__ __forceinline__ float wave_max(float v) {
 
 // Kernel arguments sit in memory that is cold at every launch, and the compiler loads each where it is
 // first used: up to five waits one after the other before a block's first data load.  Naming them in an
-// empty asm at the top makes it load them together, with one wait: 0.3 - 1.1 us of a GEMM launch
-// (1024 x 3072 x 1024 12.0 -> 10.9 us, 2048^3 21.4 -> 20.0 us).
+// empty asm at the top makes it load them together, with one wait.  (The GEMM and row-wise kernels do the same
+// in place; their figures stand there.)
 template <class Args>           // AttnArgs
 __device__ __forceinline__ void attn_args_now(const Args& a, float scale) {
     asm volatile("" ::"s"(a.B), "s"(a.S), "s"(a.heads), "s"(a.d), "s"(a.causal), "s"(a.lens), "s"(a.qkv), "s"(a.ctx),

@@ -133,9 +133,11 @@ struct Stage : LaneState {
     std::vector<uint8_t> matrix_ready;
     hipEvent_t ev_vectors = nullptr;
     bool vectors_ready = false;
-    // Only where the copies take a while: below 16 MB of gradients in a chunk (0.3 ms over the host link) the events
-    // and the extra copy of grad_out cost more than they give (H 128, two layers, 2 MB: 1.63 -> 1.70 ms an
-    // iteration; H 768, two layers, 57 MB: fp32 6.63 -> 5.62 ms).
+    // Only where the copies take a while (16 MB of gradients in a chunk are 0.3 ms over the host link): below, the
+    // events and the extra copy of grad_out cost about what they give.  Early against late, two layers, ms an
+    // iteration of eight micro-batches of 384 / 2048 tokens: H 384 (13.5 MB) 2.76 - 2.90 / 3.03 against 2.67 - 2.88 /
+    // 3.45; H 448 (18.4 MB) 2.91 / 3.29 against 2.92 / 3.80; H 768 (54 MB) 3.80 / 5.67 against 3.98 / 6.32; fp32,
+    // 384 tokens, H 448 4.23 against 4.51.
     bool reads_early() const { return !is_view && (size_t)L * g_layer_bytes >= ((size_t)16 << 20); }
     bool leaves_events(hipStream_t on) const { return on != stream && wgrad_group > 1 && reads_early(); }
     void forget_ready() { matrix_ready.assign(matrix_ready.size(), 0); vectors_ready = false; }

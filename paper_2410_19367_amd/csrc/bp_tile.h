@@ -1,5 +1,5 @@
-// Device-side pieces shared by the GEMM kernels that load their operand slices straight into LDS:
-// the swizzle of k-major tiles, buffer descriptors, the load itself, the order of output tiles.
+// Device-side pieces shared by the GEMM and attention kernels that load their operands straight into LDS:
+// the swizzle of k-major tiles, buffer descriptors, the load itself and the wait for it, the order of output tiles.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

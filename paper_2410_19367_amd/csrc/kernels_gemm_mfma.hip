@@ -16,9 +16,10 @@
 // element (outputs whose rows are no multiple of 8 elements or not 16-byte aligned); gemm_dma_kernel
 // (further down) loads slices straight into LDS, for any shape with 16-byte rows, and carries the
 // fused epilogues, split-K and multi-segment contractions.  Slices land in LDS while earlier ones feed the MFMAs,
-// one barrier per slice: two LDS stages in gemm_mfma_kernel; in gemm_dma_kernel three of A and two of B
-// in the large tiles of the forward / data-gradient form, three in its 128 x 128 tiles, a ring of five
-// half-slices in the weight-gradient form, two elsewhere.
+// one barrier per slice.  LDS stages: two in gemm_mfma_kernel; in gemm_dma_kernel three of A and two of B in the
+// large tiles (256 x 256 and 256 x 192) of the forward / data-gradient form, three in its 128 x 128 and
+// 128 x 64 tiles and in the 64 x 64 tiles of either form, a ring of five half-slices in the 256 x 256 tiles of the
+// weight-gradient form, two in every other.
 #include <cstdlib>
 #include <type_traits>
 
@@ -510,8 +511,9 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     // under sustained load, where the chip runs against its power limit, a loop of nothing but MFMAs
     // on random operands reaches 1.9 PFLOP/s with it against 1.35 - 1.65 with the 32x32x16 shape
     // (two waves per SIMD; one wave alone cannot issue the 16-cycle instructions back to back).  Inside
-    // the stages the 256 x 256 tiles gain 2 % (step time), the weight-gradient form 4 - 6 %; on the
-    // 192-wide and the 128 x 128 tiles it made no difference, so those keep the 32x32x16 shape.
+    // the stages the 256 x 256 tiles gain 2 % (step time), the weight-gradient form 4 - 6 %.  All tiles of the
+    // forward / data-gradient form use it, and the 64 x 64 ones; the other 192-wide and 128 x 128 tiles, where it
+    // made no difference, have the 32x32x16 shape.
     typedef float f32x4acc __attribute__((ext_vector_type(4)));
     constexpr int FM = MI16 ? BM / WM / 16 : TM, FN = MI16 ? BN / WN / 16 : TN;   // fragments per k step
     f32x16 acc[MI16 ? 1 : TM][MI16 ? 1 : TN];
