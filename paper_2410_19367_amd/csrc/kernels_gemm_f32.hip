@@ -58,7 +58,8 @@ __device__ __forceinline__ f32x4 f32_frag(const char* lds, int row0, int j, int 
     return f32x4{p[0], p[R], p[2 * R], p[3 * R]};
 }
 
-template <int BM, int BN, int WM, int WN, int WK, int BK, int NS, bool A_RMAJOR, bool B_RMAJOR>
+// GROUP: several contraction segments (grouped weight gradients)
+template <int BM, int BN, int WM, int WN, int WK, int BK, int NS, bool A_RMAJOR, bool B_RMAJOR, bool GROUP>
 __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     constexpr int NW = WM * WN * WK;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
@@ -79,7 +80,6 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
 
     // the contraction: g.nseg operand pairs of g.K each, one after the other, in slices of BK
     const int nk_seg = (g.K + BK - 1) / BK;
-    const int nk = nk_seg * g.nseg;
     const long a_step = 4L * (A_RMAJOR ? BK * (long)g.lda : BK), b_step = 4L * (B_RMAJOR ? BK * (long)g.ldb : BK);
     F32Plan<BM, BK, NW, A_RMAJOR> pa;
     F32Plan<BN, BK, NW, B_RMAJOR> pb;
@@ -119,11 +119,24 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    // sums of the segments before: one chain of additions over all of them would round more than a launch per
+    // micro-batch does (1024 x 4096 over 4 x 2100 tokens: 1.6e-6 against 8.2e-7 in the 2-norm); up to 5 % of a launch
+    // over many short segments (472 x 708 over 8 x 328 tokens 39 -> 41 us)
+    f32x16 done[GROUP ? TM : 1][GROUP ? TN : 1];
+    if constexpr (GROUP) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) done[i][j][v] = 0.f;
+    }
 
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s) request(smem + s * STAGE);
     int cur = 0;
-    for (int kt = 0; kt < nk; ++kt) {
+    for (int sgm = 0; sgm < (GROUP ? g.nseg : 1); ++sgm) {
+    for (int kt = 0; kt < nk_seg; ++kt) {
         BP_WAIT_VMCNT((NS - 2) * LPT);                  // this wave's part of slice kt has landed
         __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0): its reads of slice kt - 1 are over
         __builtin_amdgcn_s_barrier();
@@ -149,6 +162,19 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void gemm_f32_kernel(GemmArgs g, i
         }
         __builtin_amdgcn_sched_barrier(0);
         cur = cur + 1 == NS ? 0 : cur + 1;
+    }
+    if constexpr (GROUP) {
+        const bool last = sgm + 1 == g.nseg;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    done[i][j][v] += acc[i][j][v];
+                    acc[i][j][v] = last ? done[i][j][v] : 0.f;
+                }
+    }
     }
     BP_WAIT_VMCNT(0);
 
@@ -233,9 +259,9 @@ static hipError_t launch_f32(const GemmArgs& g, hipStream_t s) {
     const size_t stages = (size_t)NS * (BM + BN) * BK * 4;
     const size_t merge = (size_t)(WK - 1) * BM * BN * 4;
     const size_t smem = stages > merge ? stages : merge;
-#define BP_GEMM_LAUNCH(AR, BR)                                                                   \
+#define BP_GEMM_LAUNCH(AR, BR, GROUP)                                                            \
     do {                                                                                         \
-        auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, BK, NS, AR, BR>;                         \
+        auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, BK, NS, AR, BR, GROUP>;                  \
         static std::atomic<bool> attr_set{false};   /* once per instantiation; host threads may race */ \
         if (smem > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {                     \
             hipError_t e = hipFuncSetAttribute((const void*)kern,                                \
@@ -245,10 +271,11 @@ static hipError_t launch_f32(const GemmArgs& g, hipStream_t s) {
         }                                                                                        \
         hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(WM * WN * WK * 64), smem, s, g, tiles_m, tiles_n); \
     } while (0)
-    if (!g.a_t && !g.b_t) BP_GEMM_LAUNCH(false, true);
-    else if (!g.a_t && g.b_t) BP_GEMM_LAUNCH(false, false);
-    else if (g.a_t && !g.b_t) BP_GEMM_LAUNCH(true, true);
-    else BP_GEMM_LAUNCH(true, false);
+    if (g.nseg > 1) BP_GEMM_LAUNCH(true, true, true);
+    else if (!g.a_t && !g.b_t) BP_GEMM_LAUNCH(false, true, false);
+    else if (!g.a_t && g.b_t) BP_GEMM_LAUNCH(false, false, false);
+    else if (g.a_t && !g.b_t) BP_GEMM_LAUNCH(true, true, false);
+    else BP_GEMM_LAUNCH(true, false, false);
 #undef BP_GEMM_LAUNCH
     return hipGetLastError();
 }
@@ -261,6 +288,7 @@ static hipError_t launch_f32(const GemmArgs& g, hipStream_t s) {
 // 16 / 9).  Larger tiles (128 x 64, 128 x 128) gain 2 % from 2048 x 4096 x 1024 on and lose below.
 // The generic kernel these replace: 1024 x 768..3072 products 290 us on average, 128 x 128 x 512 41 us.
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t s) {
+    if (g.nseg > 1 && !(g.a_t && !g.b_t)) return launch_gemm_per_segment(g, s, launch_gemm_f32);    // (groups are weight gradients)
     const int ncu = cu_count();
     auto fill = [&](int b) {
         const long t = (long)((g.M + b - 1) / b) * ((g.N + b - 1) / b);

@@ -533,3 +533,22 @@ def test_wgrad_operand_beyond_4_gib(M, N, T):
     torch.cuda.synchronize()
     err = float((w.double() - ref).abs().max() / ref.abs().max())
     assert err <= 1e-4, err
+
+
+@pytest.mark.parametrize("M,N,T,n", [(1024, 1024, 700, 4), (512, 512, 2000, 8)])
+def test_wgrad_group_f32_rounds_like_one_micro_batch(M, N, T, n):
+    """fp32: the sum over a group is no less accurate than micro-batch after micro-batch.  A chain of T additions of
+    random terms is off by 0.31 2^-24 sqrt(T) in the 2-norm (rounding errors of 0.43 2^-24 of the partial sum, rms,
+    partial sums growing like sqrt(k)); n such chains added up are too; a single one of n T is off by sqrt(n)
+    times that."""
+    import torch
+    import paper_2410_19367_amd as bp
+    xs = [_randn(f"rx{i}", (T, M), dtype="f32") for i in range(n)]
+    ys = [_randn(f"ry{i}", (T, N), dtype="f32") for i in range(n)]
+    ref = sum(x.astype(np.float64).T @ y.astype(np.float64) for x, y in zip(xs, ys))
+    w = torch.empty(M, N, device="cuda")
+    bp.bp_op_wgrad_group(bp.BP_F32, M, N, T, [_f32_dev(x) for x in xs], [_f32_dev(y) for y in ys], w, 1, None, 0)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(w.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+    print(f"  {M} x {N}, {n} x {T}: {err:.2e}", flush=True)
+    assert err <= 1.3 * 0.31 * 2.0 ** -24 * np.sqrt(T), err
