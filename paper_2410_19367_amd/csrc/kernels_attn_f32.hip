@@ -132,6 +132,12 @@ __device__ __forceinline__ bool rows_finite(const char* tile, int row0, int lane
     }
     return __builtin_amdgcn_ballot_w64(z != 0.f) == 0;
 }
+// exp(s scale - m).  The difference is taken before the change of base: scores are then rounded relative to what is left
+// of them and not to themselves (with log2 e folded into the scale, a score of 200 that is its row's only one
+// had the probability 1 +- 1e-5).
+__device__ __forceinline__ float exp_diff(float s, float scale, float m) {
+    return __builtin_amdgcn_exp2f(__builtin_fmaf(s, scale, -m) * kLog2e);
+}
 __device__ __forceinline__ f32x16 zero16() {
     f32x16 z;
 #pragma unroll
@@ -161,7 +167,6 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
     const int q_wave = qblk * 64 + qg * 32, q_lane = q_wave + (lane & 31);
     const int klen = a.causal ? S : (a.lens ? a.lens[b] : S);
     const int nt = ((a.causal ? min(qblk * 64 + 64, S) : klen) + 63) / 64;
-    const float c = scale * kLog2e;
 
     f32x4 qf[KS];
 #pragma unroll
@@ -204,11 +209,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
             if (need_mask && ((a.causal && key > q_lane) || key >= klen)) st2[v] = -INFINITY;
             mx = fmaxf(mx, st2[v]);
         }
-        mx = halves_max(mx) * c;
+        mx = halves_max(mx) * scale;
         // the running reference point moves only when a score is more than 8 binary orders above it
-        if (__builtin_amdgcn_ballot_w64(mx > m + 8.f) != 0) {
+        if (__builtin_amdgcn_ballot_w64(mx > m + 8.f * kLn2) != 0) {
             const float m_new = fmaxf(m, mx);
-            const float alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+            const float alpha = m == -INFINITY ? 0.f : exp_diff(m, 1.f, m_new);
             m = m_new;
             lsum *= alpha;
 #pragma unroll
@@ -219,7 +224,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
         const float m_use = m == -INFINITY ? 0.f : m;   // every key masked so far: no inf - inf
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            st2[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(st2[v], c, -m_use));
+            st2[v] = exp_diff(st2[v], scale, m_use);
             lsum += st2[v];
         }
         if (a.causal && kw + 31 > q_wave && !rows_finite<D, DC>(sv, 32 * kh, lane)) by_rows = true;
@@ -245,7 +250,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
     __syncthreads();
     if (kh == 1 || q_lane >= S) return;
     const float m1 = xo[DT * 16 * 64 + lane], mm = fmaxf(m, m1);
-    const float a0 = __builtin_amdgcn_exp2f(m - mm), a1 = __builtin_amdgcn_exp2f(m1 - mm);
+    const float a0 = exp_diff(m, 1.f, mm), a1 = exp_diff(m1, 1.f, mm);
     const float ls = l * a0 + xo[DT * 16 * 64 + 64 + lane] * a1;
     const float inv = 1.f / ls;
     float* out = (float*)a.ctx + ((size_t)b * S + q_lane) * H + head * dr;
@@ -261,7 +266,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
                 o[e] = (ot[t2][4 * g + e] * a0 + xo[(t2 * 16 + 4 * g + e) * 64 + lane] * a1) * inv;
             *reinterpret_cast<f32x4*>(out + col) = o;
         }
-    if (h == 0) a.lse[((size_t)b * a.heads + head) * S + q_lane] = (mm + log2f(ls)) * kLn2;
+    if (h == 0) a.lse[((size_t)b * a.heads + head) * S + q_lane] = mm + log2f(ls) * kLn2;
 }
 
 // dQ, and delta[q] = sum_d dO[q][d] O[q][d] for the dK/dV kernel
@@ -280,7 +285,6 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(A
     const int q_wave = qblk * 64 + qg * 32, q_lane = q_wave + (lane & 31), q_src = min(q_lane, S - 1);
     const int klen = a.causal ? S : (a.lens ? a.lens[b] : S);
     const int nt = ((a.causal ? min(qblk * 64 + 64, S) : klen) + 63) / 64;
-    const float c = scale * kLog2e;
 
     const size_t orow = ((size_t)b * S + q_src) * H + head * dr;
     f32x4 qf[KS], dof[KS];
@@ -296,7 +300,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(A
     delta = halves_sum(delta);
     const size_t li = ((size_t)b * a.heads + head) * S + q_src;
     if (kh == 0 && h == 0 && q_lane < S) a.delta[li] = delta;
-    const float lse2 = a.lse[li] * kLog2e;
+    const float lse = a.lse[li];
 
     f32x16 dq[DT];
 #pragma unroll
@@ -326,7 +330,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(A
         const bool need_mask = (a.causal && kw + 31 > q_wave) || kw + 32 > klen;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[v], c, -lse2));
+            float p = exp_diff(sacc[v], scale, lse);
             const int key = kw + f32_acc_row(v, h);
             if (need_mask && ((a.causal && key > q_lane) || key >= klen)) p = 0.f;
             dp[v] = p * (dp[v] - delta);                // dS^T
@@ -380,7 +384,6 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(
     const int k_src = max(min(k_lane, klen - 1), 0);     // row this lane reads (its own, unless it is padding)
     float* dk_out = (float*)a.dqkv + ((size_t)b * S + k_lane) * ld + H + head * dr;
     float* dv_out = dk_out + H;
-    const float c = scale * kLog2e;
     const float* lse = a.lse + ((size_t)b * a.heads + head) * S;
     const float* dlt = a.delta + ((size_t)b * a.heads + head) * S;
 
@@ -432,7 +435,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int qi = f32_acc_row(v, h), q = qw + qi;
-            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[v], c, -s_lse[qi] * kLog2e));
+            float p = exp_diff(sacc[v], scale, s_lse[qi]);
             if (need_mask && ((a.causal && k_lane > q) || q >= S || k_lane >= klen)) p = 0.f;
             sacc[v] = p;
             dp[v] = p * (dp[v] - s_dlt[qi]);            // dS

@@ -405,6 +405,33 @@ def test_attention_causal_token_that_is_not_finite(S, heads, d, t, dtype, where)
                 assert err <= (1e-2 if dtype == "bf16" else 5e-5), (name, err)
 
 
+@pytest.mark.parametrize("S,heads", [(600, 4), (64, 16), (333, 8)])
+def test_attention_f32_large_scores(S, heads):
+    """fp32, one valid key per sequence, scores of about +-200 (d = 64: the scale is a power of two): every
+    probability is exactly one whatever the score, so ctx is v to an ulp and dv = sum dctx with the rounding of a
+    sum of S terms (2^-24 sqrt(S) of their norm; twice that allowed)."""
+    import torch
+    import paper_2410_19367_amd as bp
+    B, d = 2, 64
+    H = heads * d
+    qkv = _randn("sqkv", (B, S, 3 * H), dtype="f32")
+    qkv[..., :2 * H] *= 14
+    dctx = _randn("sdctx", (B, S, H), dtype="f32")
+    lens = torch.ones(B, dtype=torch.int32, device="cuda")
+    qd, dd = hz.to_dev(qkv, "f32"), hz.to_dev(dctx, "f32")
+    ctx, dqkv = hz.empty_like_dev((B, S, H), "f32"), hz.empty_like_dev((B, S, 3 * H), "f32")
+    lse, delta = torch.empty((B, heads, S), device="cuda"), torch.empty((B, heads, S), device="cuda")
+    bp.bp_op_attention_fwd(bp.BP_F32, B, S, heads, d, False, lens, qd, ctx, lse)
+    bp.bp_op_attention_bwd(bp.BP_F32, B, S, heads, d, False, lens, qd, ctx, lse, dd, dqkv, delta)
+    torch.cuda.synchronize()
+    v0 = qkv[:, :1, 2 * H:].astype(np.float64)
+    assert np.allclose(hz.to_host(ctx), np.broadcast_to(v0, (B, S, H)), rtol=2.0 ** -22, atol=0)
+    ref = dctx.astype(np.float64).sum(1)
+    err = np.linalg.norm(hz.to_host(dqkv)[:, 0, 2 * H:] - ref) / np.linalg.norm(ref)
+    print(f"  S {S}: dv {err:.2e}", flush=True)
+    assert err <= 2 * 2.0 ** -24 * np.sqrt(S), err
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_attention_one_token(dtype):
     """S = 1: probability one, so ctx = v and dv = dctx exactly, and dq, dk vanish up to the rounding of
