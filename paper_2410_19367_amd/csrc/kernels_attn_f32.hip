@@ -12,7 +12,7 @@
 // float per lane of the same row-major tile.
 // Measured (forward / backward): B 2, S 512, 12 heads of 64, causal 26 / 81 us against 163 / 814 us for the
 // one-row-per-block kernels; without the mask 62 / 39 TFLOP/s.  Heads wider than 64 leave one wave per SIMD (dK/dV
-// at 128 spills 34 registers): S 300, 16 heads of 128, without the mask 34.5 / 107 us (rows 135 / 740 us), of 96
+// at 128 spills 18 registers): S 300, 16 heads of 128, without the mask 34.5 / 107 us (rows 135 / 740 us), of 96
 // 27.7 / 80 us.
 #include <atomic>
 
