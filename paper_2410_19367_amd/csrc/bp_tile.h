@@ -30,6 +30,18 @@ __device__ __forceinline__ void dma16(rsrc_t rsrc, uint32_t lane_off, uint32_t s
                                              (int)lane_off, (int)slice_off, 0, 0);
 }
 
+// LDS transpose read: lane i of a group of 16 receives element i % 4 of the four 8-byte pieces that lanes
+// 4 r + i / 4 (r = 0 .. 3) address.  `__restrict__` is what this function is for.  A bare call of the builtin is
+// taken to read what any load into LDS still on its way may write, and the compiler waits for all of them
+// (vmcnt(0)) in front of the first transpose read after a request: every kernel that prefetches the next slice and
+// then reads this one transposed waited a whole memory latency per slice (plain LDS reads carry the alias scope that
+// the parameter gives these).  The waits that are needed are the callers' own, in front of their barriers.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef s16x4 __attribute__((address_space(3))) lds_s16x4;
+__device__ __forceinline__ s16x4 lds_read_tr(const lds_s16x4* __restrict__ p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(const_cast<lds_s16x4*>(p));
+}
+
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
 #define BP_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
 

@@ -27,7 +27,6 @@
 namespace bp {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -120,10 +119,8 @@ __device__ __forceinline__ bf16x8 frag_cols(const char* lds, int r0, int col0, i
     const int col = col0 + 16 * g2 + 4 * (i & 3);
     const int chunk = col >> 3, byte = (col & 7) * 2;
     const int ra = r0 + 4 * h + (i >> 2);
-    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (s16x4 __attribute__((address_space(3)))*)(lds + tile_off<D>(ra, chunk) + byte));
-    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (s16x4 __attribute__((address_space(3)))*)(lds + tile_off<D>(ra + 8, chunk) + byte));
+    s16x4 lo = lds_read_tr((const lds_s16x4*)(lds + tile_off<D>(ra, chunk) + byte));
+    s16x4 hi = lds_read_tr((const lds_s16x4*)(lds + tile_off<D>(ra + 8, chunk) + byte));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 

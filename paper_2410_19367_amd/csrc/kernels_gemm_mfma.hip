@@ -33,7 +33,6 @@ namespace bp {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -114,10 +113,8 @@ __device__ __forceinline__ bf16x8 read_frag(const char* lds, int row0, int kk, i
         const int col = row0 + 16 * g2 + 4 * q;       // element index along the r-major row
         const int chunk = col >> 3, byte = (col & 7) * 2;
         const int k0 = kk * 16 + 8 * h;
-        s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (s16x4 __attribute__((address_space(3)))*)(lds + rmajor_off<R>(k0 + r, chunk) + byte));
-        s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (s16x4 __attribute__((address_space(3)))*)(lds + rmajor_off<R>(k0 + 4 + r, chunk) + byte));
+        s16x4 lo = lds_read_tr((const lds_s16x4*)(lds + rmajor_off<R>(k0 + r, chunk) + byte));
+        s16x4 hi = lds_read_tr((const lds_s16x4*)(lds + rmajor_off<R>(k0 + 4 + r, chunk) + byte));
         typedef short s16x8 __attribute__((ext_vector_type(8)));
         s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         return __builtin_bit_cast(bf16x8, v);
@@ -296,10 +293,8 @@ __device__ __forceinline__ bf16x8 read_frag2(const char* lds, int row0, int kk, 
         const int col = row0 + 16 * g2 + 4 * q;
         const int chunk = col >> 3, byte = (col & 7) * 2;
         const int k0 = kk * 16 + 8 * h;
-        s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (s16x4 __attribute__((address_space(3)))*)(lds + rmajor_off<R>(k0 + r, chunk) + byte));
-        s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (s16x4 __attribute__((address_space(3)))*)(lds + rmajor_off<R>(k0 + 4 + r, chunk) + byte));
+        s16x4 lo = lds_read_tr((const lds_s16x4*)(lds + rmajor_off<R>(k0 + r, chunk) + byte));
+        s16x4 hi = lds_read_tr((const lds_s16x4*)(lds + rmajor_off<R>(k0 + 4 + r, chunk) + byte));
         typedef short s16x8 __attribute__((ext_vector_type(8)));
         s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         return __builtin_bit_cast(bf16x8, v);
@@ -319,10 +314,8 @@ __device__ __forceinline__ bf16x8 read_frag16(const char* lds, int row0, int kk,
         const int col = row0 + 4 * q;
         const int chunk = col >> 3, byte = (col & 7) * 2;
         const int k0 = kk * 32 + 8 * g4;
-        s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (s16x4 __attribute__((address_space(3)))*)(lds + rmajor_off<R>(k0 + r, chunk) + byte));
-        s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (s16x4 __attribute__((address_space(3)))*)(lds + rmajor_off<R>(k0 + 4 + r, chunk) + byte));
+        s16x4 lo = lds_read_tr((const lds_s16x4*)(lds + rmajor_off<R>(k0 + r, chunk) + byte));
+        s16x4 hi = lds_read_tr((const lds_s16x4*)(lds + rmajor_off<R>(k0 + 4 + r, chunk) + byte));
         typedef short s16x8 __attribute__((ext_vector_type(8)));
         s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         return __builtin_bit_cast(bf16x8, v);
@@ -584,7 +577,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
     // that kernel runs at a higher clock than the 32x32x16 one (see above) and waits for its loads at
     // the next barrier (a quarter of a slice's time in a build with cycle-counter stamps), so every
     // cycle they go out earlier counts: +6 - 10 % on the large forward / data-gradient products.  The
-    // weight-gradient ring and the 32x32x16 tiles are faster the other way round.
+    // 32x32x16 tiles are faster the other way round.
     constexpr int LF = (MI16 && !RING && !A_RMAJOR && !B_RMAJOR) ? (NMFMA / 2 < 8 ? NMFMA / 2 : 8) : 0;
     auto interleave_boundary = [&]() { SchedRounds<0, NMFMA, NREAD, LPT, LF>::apply(); };
     // wait until at most `n` of the most recently requested slices are still on their way
@@ -610,9 +603,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
         // the iteration after next reads first, into the first slot it has just freed; the second freed
         // slot is requested one k step later, in the next iteration's first step, and has a barrier
         // more to land: the barrier only ever waits for the older of the two requests, and the loads
-        // go out in two bursts per iteration instead of one.  Measured on the
-        // weight-gradient shapes of the GPT-style stages: +13 % (2048 x 8192 x 16384: 1130 -> 1280
-        // TFLOP/s); with both operands contraction-major it is 2 % slower than two stages (a slot of 32
+        // go out in two bursts per iteration instead of one.  2048 x 8192 x 16384 434 -> 409 us (1340 TFLOP/s) since
+        // the transpose reads no longer wait for the loads on their way (lds_read_tr); with both operands contraction-major it is 2 % slower than two stages (a slot of 32
         // along K is then half a cache line per row, and the requests to the L2 double), so those keep
         // them.
         static_assert(!RING || (MI16 && BKT == 64 && NS == 5), "ring mode: 16x16x32 MFMAs, five slots of 32");
@@ -638,7 +630,13 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
             b_off += issued < nq ? b_step32 : 0u;
             if constexpr (RAG) rag_move(issued < nq ? a_step32 : 0u, issued < nq ? b_step32 : 0u);
         };
+        // Loads first in the barrier's step, fragment reads first in the other (5120 x 15360 x 16384 2150 -> 2039 us,
+        // 2048 x 6144 x 16384 384 -> 357 us; loads first in both steps 2045, 353 us, but 418 instead of 409 us at
+        // 2048 x 8192 x 16384).  Shapes off the tile grid, whose loads take a descriptor each, are 3 % faster with
+        // the reads first in both (1600 x 4800 x 8000 157 against 161 us).
+        constexpr int LB = RAG ? 0 : L32;
         auto interleave_l = [&]() { SchedRounds<0, NMFMA, NREAD, L32>::apply(); };
+        auto interleave_b = [&]() { SchedRounds<0, NMFMA, NREAD, L32, LB>::apply(); };
         // The requests walk through the contraction segments 32 deep at a time; a segment holds an even
         // number of slots and the loop requests two per iteration, so the change from one segment to
         // the next falls between two runs of the (branch-free) loop, as in the staged loop below.
@@ -682,11 +680,12 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(GemmArgs g, int t
                 BP_WAIT_VMCNT(L32);                          // only the request just made may still be on its way
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_sched_barrier(0);
-                read_step(smem + n0 * SLOT, 0, 0);
+                if constexpr (LB == 0) read_step(smem + n0 * SLOT, 0, 0);
                 request(s0);
+                if constexpr (LB > 0) read_step(smem + n0 * SLOT, 0, 0);
                 late = s1;
                 mfma_step(1);
-                interleave_l();
+                interleave_b();
                 s0 = n0;
             }
             it += run;
