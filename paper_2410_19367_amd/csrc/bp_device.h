@@ -87,9 +87,9 @@ __device__ __forceinline__ float wave_max(float v) {
 // empty asm at the top makes it load them together, with one wait.  (The GEMM and row-wise kernels do the same
 // in place; their figures stand there.)
 template <class Args>           // AttnArgs
-__device__ __forceinline__ void attn_args_now(const Args& a, float scale) {
+__device__ __forceinline__ void attn_args_now(const Args& a, float scale, int order = 0) {
     asm volatile("" ::"s"(a.B), "s"(a.S), "s"(a.heads), "s"(a.d), "s"(a.causal), "s"(a.lens), "s"(a.qkv), "s"(a.ctx),
-                 "s"(a.lse), "s"(a.dctx), "s"(a.dqkv), "s"(a.delta), "s"(scale));
+                 "s"(a.lse), "s"(a.dctx), "s"(a.dqkv), "s"(a.delta), "s"(scale), "s"(order));
 }
 
 // ---- GELU, tanh form (the approximation GPT-2 / Megatron use):

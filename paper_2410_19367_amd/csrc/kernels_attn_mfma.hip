@@ -207,23 +207,32 @@ __device__ __forceinline__ bool rows_finite(const char* tile, int row0, int lane
     return __builtin_amdgcn_ballot_w64(!ok) == 0;
 }
 
-// Heavy-first, then light-last block order for causal masks: the first half of the grid walks the
-// query (or key) blocks from the most expensive down, the second half from the cheapest up, so the
-// two blocks that share a CU's two slots add up to roughly the same work everywhere.
-__device__ __forceinline__ void block_coords(int nblk, int heads, bool causal, bool heavy_is_last_index,
-                                            bool paired, int& blk, int& head, int& b) {
+// Which block of rows (queries or keys) of which head a launched block takes.  Under a causal mask the blocks of a
+// head differ in work, and the position of a block in the launch counts:
+//   ORDER_FOLDED: the first half of the positions walks from the most expensive block down, the second half from the
+//     cheapest up, so that two blocks that share a CU add up to the same everywhere; else heaviest first, which lets
+//     the hardware hand the light blocks to whichever CU finishes first;
+//   ORDER_ALL: positions run over all batch entries together, else over one entry after the other, which keeps fewer
+//     heads' keys and values in the L2s at a time but pairs heavy blocks of one entry with heavy ones of another.
+enum { ORDER_FOLDED = 1, ORDER_ALL = 2 };
+__device__ __forceinline__ void block_coords(int nblk, int heads, int batch, bool causal, bool heavy_is_last_index,
+                                            int order, int& blk, int& head, int& b) {
     const int per = nblk * heads;             // blocks per batch entry
-    const int lin = blockIdx.x % per;
-    b = blockIdx.x / per;
-    int i = lin / heads;                      // position in the work-sorted order
-    head = lin % heads;
+    int i;                                    // position in the work-sorted order
+    if (causal && (order & ORDER_ALL)) {
+        i = blockIdx.x / (heads * batch);
+        const int r = blockIdx.x - i * (heads * batch);
+        b = r / heads;
+        head = r - b * heads;
+    } else {
+        const int lin = blockIdx.x % per;
+        b = blockIdx.x / per;
+        i = lin / heads;
+        head = lin % heads;
+    }
     if (causal) {
-        // positions 0, 1, 2, ... -> heaviest, lightest, 2nd heaviest, 2nd lightest, ... folded so that
-        // the first half of the launch is the heavy half
-        // paired: for kernels with two resident blocks per CU; otherwise plain heaviest-first, which
-        // lets the hardware hand the light blocks to whichever CU finishes first
         const int half = (nblk + 1) / 2;
-        const int rank = !paired ? i : i < half ? i : nblk - 1 - (i - half);      // 0 = heaviest
+        const int rank = !(order & ORDER_FOLDED) ? i : i < half ? i : nblk - 1 - (i - half);      // 0 = heaviest
         blk = heavy_is_last_index ? nblk - 1 - rank : rank;
     } else {
         blk = i;
@@ -237,6 +246,8 @@ __device__ __forceinline__ void block_coords(int nblk, int heads, bool causal, b
 // (D = 128) of LDS, two blocks per CU.  NT = 2: 8 waves, 128 KB, one block per CU: the heaviest
 // causal block then needs half as many steps, and because blocks are dealt out heaviest first
 // as CUs become free the tail of the launch stays short.
+// WIDE: block = 128 queries, a wave takes 32 of them and both halves of every tile, so nothing is merged and a tile
+// is loaded for twice as many products: for launches with enough blocks (wide_rows).
 // =====================================================================================
 // RAG: the sequence length is not a multiple of 64.  The last query block and the last key tile are
 // then partly filled: tile rows of keys past the end, or past the sequence's valid length, are zeros
@@ -248,10 +259,12 @@ __device__ __forceinline__ void block_coords(int nblk, int heads, bool causal, b
 // bf16 parts that add up to it exactly.  Against one product with the rounded value: forward B 3, S 2550,
 // 12 heads of 64, causal 55 -> 79 us, backward B 2, S 1058, 32 heads of 128 237 -> 340 us, 5 - 20 % below S 300;
 // the kernels of one row per block take ten times as long.)
-template <int D, int DR, int NT, bool RAG>
-__global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kernel(AttnArgs a, float scale) {
-    attn_args_now(a, scale);
-    constexpr int NW = 4 * NT, NSUB = 2 * NT, KS = D / 16, DT = D / 32;
+template <int D, int DR, int NT, bool RAG, bool WIDE = false>
+__global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kernel(AttnArgs a, float scale, int order) {
+    static_assert(!WIDE || (NT == 1 && !RAG), "128 queries: one tile a step, whole tiles");
+    attn_args_now(a, scale, order);
+    constexpr int NW = 4 * NT, NSUB = WIDE ? 1 : 2 * NT, KS = D / 16, DT = D / 32;
+    constexpr int QB = WIDE ? 128 : 64, NH = WIDE ? 2 : 1;      // queries of a block; halves of a tile that a wave takes
     constexpr int TILE = 64 * D * 2, STAGE = NT * 2 * TILE;   // per tile: K then V
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -261,7 +274,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     const int tj = sub >> 1, kh = sub & 1;
     const int h = lane >> 5;
     int qblk, head, b;
-    block_coords((a.S + 63) / 64, a.heads, a.causal != 0, true, NT == 1, qblk, head, b);
+    block_coords((a.S + QB - 1) / QB, a.heads, a.B, a.causal != 0, true, order, qblk, head, b);
     // real head dimension: the tile width (no padding, every guard below folds away), a fixed narrower
     // width (the guards fold to constants), or with DR = 0 whatever the call says
     constexpr bool PAD = DR != D;
@@ -270,10 +283,10 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     const bf16_t* qkv = (const bf16_t*)a.qkv + (size_t)b * a.S * ld + head * dr;
     const bf16_t* kbase = qkv + H;
     const bf16_t* vbase = qkv + 2 * H;
-    const int q_wave = qblk * 64 + qg * 32;
+    const int q_wave = qblk * QB + qg * 32;
     const int q_lane = q_wave + (lane & 31);
     const int klen = a.causal ? a.S : (a.lens ? a.lens[b] : a.S);
-    const int kend = a.causal ? (RAG ? min(qblk * 64 + 64, a.S) : qblk * 64 + 64) : klen;   // keys [0, kend) matter to this block
+    const int kend = a.causal ? (RAG || WIDE ? min(qblk * QB + QB, a.S) : qblk * QB + QB) : klen;   // keys [0, kend) matter to this block
     const int nt = (kend + 63) / 64;                        // tiles
     const int nsteps = (nt + NT - 1) / NT;
     const float c = scale * kLog2e;
@@ -281,7 +294,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     bf16x8 qf[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s)
-        qf[s] = load_frag(qkv + (size_t)(RAG ? min(q_lane, a.S - 1) : q_lane) * ld, 16 * s + 8 * h, dr);
+        qf[s] = load_frag(qkv + (size_t)(RAG || WIDE ? min(q_lane, a.S - 1) : q_lane) * ld, 16 * s + 8 * h, dr);
 
     f32x16 ot[DT];
 #pragma unroll
@@ -317,27 +330,36 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
         const int tile = t * NT + tj;
         const int kw = tile * 64 + 32 * kh;             // first key of this wave's sub-range
         if (tile >= nt || (a.causal && kw > q_wave + 31) || kw >= klen) continue;   // nothing unmasked for this wave
+        if (WIDE && q_wave >= a.S) continue;                        // the second half of the last block: no queries
         const char* sk = smem + (t & 1) * STAGE + tj * 2 * TILE;
         const char* sv = sk + TILE;
 
-        // S^T (32 keys x 32 queries)
-        f32x16 st2;
+        // S^T (32 keys x 32 queries), of both halves of the tile in a wide block
+        f32x16 st2[NH];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) st2[v] = 0.f;
+        for (int u = 0; u < NH; ++u)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) st2[u][v] = 0.f;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
             if (16 * s < dr)
-                st2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sk, 32 * kh, s, lane), qf[s], st2, 0, 0, 0);
-        if ((a.causal && kw + 31 > q_wave) || kw + 32 > klen) {     // the diagonal, or padded keys
+#pragma unroll
+                for (int u = 0; u < NH; ++u)
+                    st2[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sk, 32 * (kh + u), s, lane), qf[s], st2[u], 0, 0, 0);
+        if ((a.causal && kw + 32 * NH - 1 > q_wave) || kw + 32 * NH > klen) {     // the diagonal, or padded keys
             stay_a_branch();
             const int last = a.causal ? min(q_lane, klen - 1) : klen - 1;     // last key this query attends
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (kw + acc_row(v, h) > last) st2[v] = -INFINITY;
-        }
-        float mx = st2[0];
+            for (int u = 0; u < NH; ++u)
 #pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, st2[v]);
+                for (int v = 0; v < 16; ++v)
+                    if (kw + 32 * u + acc_row(v, h) > last) st2[u][v] = -INFINITY;
+        }
+        float mx = st2[0][0];
+#pragma unroll
+        for (int u = 0; u < NH; ++u)
+#pragma unroll
+            for (int v = u == 0; v < 16; ++v) mx = fmaxf(mx, st2[u][v]);
         mx = halves_max(mx) * c;     // c > 0: the maximum commutes with the scaling
         // The reference point m of the running softmax only has to stay within a bounded distance of
         // the true maximum: it moves (and O, l are rescaled) only when some query of the wave sees a
@@ -354,17 +376,25 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
         }
         // a row whose keys are all masked so far keeps m = -inf; avoid inf - inf
         const float m_use = m == -INFINITY ? 0.f : m;
-        float ps = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float p = fast_exp2(__builtin_fmaf(st2[v], c, -m_use));
-            st2[v] = p;
-            ps += p;
+        for (int u = 0; u < NH; ++u) {
+            float ps = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float p = fast_exp2(__builtin_fmaf(st2[u][v], c, -m_use));
+                st2[u][v] = p;
+                ps += p;
+            }
+            lsum += ps;
         }
-        lsum += ps;
-        // O^T (D x 32 queries) += V^T P^T over this wave's 32 keys
+        // O^T (D x 32 queries) += V^T P^T over this wave's keys
         if (RAG && a.causal && kw + 31 > q_wave && !rows_finite<D>(sv, 32 * kh, lane, dr)) by_rows = true;
-        contract<D, DT, RAG>(sv, 32 * kh, lane, dr, st2, ot);
+#pragma unroll
+        for (int u = 0; u < NH; ++u) {
+            // (a half that is masked throughout contributes nothing, whatever its values are)
+            if (u && ((a.causal && kw + 32 > q_wave + 31) || kw + 32 >= klen)) break;
+            contract<D, DT, RAG>(sv, 32 * (kh + u), lane, dr, st2[u], ot);
+        }
     }
     if (RAG && a.causal && any_wave(by_rows, smem)) {
         for (int q = qblk * 64; q < min(qblk * 64 + 64, a.S); ++q) attn_fwd_row<bf16_t>(a, scale, q, head, b, (float*)smem);
@@ -372,7 +402,8 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     }
 
     // merge the key sub-ranges: waves 1 .. NSUB-1 of a query group hand (m, l, O^T) to wave 0 through LDS
-    float l = halves_sum(lsum);
+    float l = halves_sum(lsum), mm = m;
+    if constexpr (!WIDE) {
     __syncthreads();                                    // all tile reads are over; LDS is free
     constexpr int XO = DT * 16 * 64 + 128;              // [DT*16][64 lanes] + m[64] + l[64]
     float* xo = (float*)smem + (size_t)qg * (NSUB - 1) * XO;
@@ -387,7 +418,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     }
     __syncthreads();
     if (sub != 0) return;
-    float mm = m;                                       // finite: key 0 lies in this wave's sub-range
+    // (m is finite: key 0 lies in this wave's sub-range)
 #pragma unroll
     for (int j = 0; j < NSUB - 1; ++j) mm = fmaxf(mm, xo[(size_t)j * XO + DT * 16 * 64 + lane]);
     const float a0 = fast_exp2(m - mm);
@@ -406,7 +437,8 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
 #pragma unroll
             for (int v = 0; v < 16; ++v) ot[t2][v] += other[(t2 * 16 + v) * 64 + lane] * aj;
     }
-    if (RAG && q_lane >= a.S) return;
+    }
+    if ((RAG || WIDE) && q_lane >= a.S) return;
     const float inv = 1.f / l;
     bf16_t* out = (bf16_t*)a.ctx + ((size_t)b * a.S + q_lane) * H + head * dr;
 #pragma unroll
@@ -427,9 +459,11 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
 //   dQ^T (D x 32) += K^T dS^T         (K tile read plainly for S^T and transposed for dQ^T)
 // The two halves' partial dQ^T are added through LDS at the end.
 // =====================================================================================
-template <int D, int DR, bool RAG>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, float scale) {
-    attn_args_now(a, scale);
+template <int D, int DR, bool RAG, bool WIDE = false>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, float scale, int order) {
+    static_assert(!WIDE || !RAG, "128 queries: whole tiles");
+    attn_args_now(a, scale, order);
+    constexpr int QB = WIDE ? 128 : 64;                 // queries of a block
     constexpr int NW = 4, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE;
     // dP - delta: -delta is what the accumulators of dP start from, where 16 registers are left for it
@@ -438,10 +472,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int qg = wave >> 1, kh = wave & 1;
+    const int qg = WIDE ? wave : wave >> 1, kh0 = WIDE ? 0 : wave & 1;
     const int h = lane >> 5;
     int qblk, head, b;
-    block_coords((a.S + 63) / 64, a.heads, a.causal != 0, true, true, qblk, head, b);
+    block_coords((a.S + QB - 1) / QB, a.heads, a.B, a.causal != 0, true, order, qblk, head, b);
     // real head dimension: the tile width (no padding, every guard below folds away), a fixed narrower
     // width (the guards fold to constants), or with DR = 0 whatever the call says
     constexpr bool PAD = DR != D;
@@ -450,14 +484,14 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
     const bf16_t* qkv = (const bf16_t*)a.qkv + (size_t)b * a.S * ld + head * dr;
     const bf16_t* kbase = qkv + H;
     const bf16_t* vbase = qkv + 2 * H;
-    const int q_wave = qblk * 64 + qg * 32;
+    const int q_wave = qblk * QB + qg * 32;
     const int q_lane = q_wave + (lane & 31);
     const int klen = a.causal ? a.S : (a.lens ? a.lens[b] : a.S);
-    const int kend = a.causal ? (RAG ? min(qblk * 64 + 64, a.S) : qblk * 64 + 64) : klen;
+    const int kend = a.causal ? (RAG || WIDE ? min(qblk * QB + QB, a.S) : qblk * QB + QB) : klen;
     const int nt = (kend + 63) / 64;
     const float c = scale * kLog2e;
 
-    const int q_src = RAG ? min(q_lane, a.S - 1) : q_lane;     // row this lane reads
+    const int q_src = RAG || WIDE ? min(q_lane, a.S - 1) : q_lane;     // row this lane reads
     const bf16_t* dob = (const bf16_t*)a.dctx + ((size_t)b * a.S + q_src) * H + head * dr;
     bf16x8 qf[KS], dof[KS];
 #pragma unroll
@@ -479,7 +513,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
             for (int e = 0; e < 8; ++e) delta += (float)of[e] * (float)dof[s][e];
         }
         delta = halves_sum(delta);
-        if (kh == 0 && h == 0 && (!RAG || q_lane < a.S)) a.delta[li] = delta;
+        if (kh0 == 0 && h == 0 && (!(RAG || WIDE) || q_lane < a.S)) a.delta[li] = delta;
     }
 
     f32x16 dq[DT];
@@ -507,10 +541,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
         BP_WAIT_VMCNT(0);
         __syncthreads();
         if (t + 1 < nt) request(k0 + 64, smem + ((t + 1) & 1) * STAGE);
-        const int kw = k0 + 32 * kh;
-        if ((a.causal && kw > q_wave + 31) || kw >= klen) continue;
+        if (WIDE && q_wave >= a.S) continue;            // the second half of the last block: no queries
         const char* sk = smem + (t & 1) * STAGE;
         const char* sv = sk + TILE;
+#pragma unroll
+        for (int kh = kh0; kh < (WIDE ? 2 : kh0 + 1); ++kh) {
+        const int kw = k0 + 32 * kh;
+        if ((a.causal && kw > q_wave + 31) || kw >= klen) break;
         // (a value that is not finite makes dP of the queries that do not attend it NaN)
         if (RAG && a.causal && kw + 31 > q_wave &&
             (!rows_finite<D>(sk, 32 * kh, lane, dr) || !rows_finite<D>(sv, 32 * kh, lane, dr))) by_rows = true;
@@ -534,21 +571,25 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
         for (int v = 0; v < 16; ++v)
             dp[v] = fast_exp2(__builtin_fmaf(sacc[v], c, -lse2)) * (DELTA_FIRST ? dp[v] : dp[v] - delta);   // dS^T
         contract<D, DT, RAG>(sk, 32 * kh, lane, dr, dp, dq);
+        }
     }
     if (RAG && a.causal && any_wave(by_rows, smem)) {
         for (int q = qblk * 64; q < min(qblk * 64 + 64, a.S); ++q) attn_bwd_dq_row<bf16_t>(a, scale, q, head, b, (float*)smem);
         return;
     }
+    if (WIDE && q_lane >= a.S) return;
+    float* xo = (float*)smem + (WIDE ? 0 : qg * (DT * 16 * 64));
+    if constexpr (!WIDE) {
     __syncthreads();
-    float* xo = (float*)smem + qg * (DT * 16 * 64);
-    if (kh == 1) {
+    if (kh0 == 1) {
 #pragma unroll
         for (int t2 = 0; t2 < DT; ++t2)
 #pragma unroll
             for (int v = 0; v < 16; ++v) xo[(t2 * 16 + v) * 64 + lane] = dq[t2][v];
     }
     __syncthreads();
-    if (kh == 1 || (RAG && q_lane >= a.S)) return;
+    if (kh0 == 1 || (RAG && q_lane >= a.S)) return;
+    }
     bf16_t* out = (bf16_t*)a.dqkv + ((size_t)b * a.S + q_lane) * ld + head * dr;
 #pragma unroll
     for (int t2 = 0; t2 < DT; ++t2)
@@ -557,7 +598,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
             float o4[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                o4[e] = (dq[t2][4 * g + e] + xo[(t2 * 16 + 4 * g + e) * 64 + lane]) * scale;
+                o4[e] = (WIDE ? dq[t2][4 * g + e] : dq[t2][4 * g + e] + xo[(t2 * 16 + 4 * g + e) * 64 + lane]) * scale;
             uint2 pk;
             pk.x = pack_bf16x2(o4[0], o4[1]);
             pk.y = pack_bf16x2(o4[2], o4[3]);
@@ -572,19 +613,21 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
 //   dV^T (D x 32 keys) += dO^T P,   dK^T (D x 32 keys) += Q^T dS
 // The two query halves' partial sums are added through LDS at the end.
 // =====================================================================================
-template <int D, int DR, bool RAG>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, float scale) {
-    attn_args_now(a, scale);
+template <int D, int DR, bool RAG, bool WIDE = false>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, float scale, int order) {
+    static_assert(!WIDE || !RAG, "128 keys: whole tiles");
+    attn_args_now(a, scale, order);
+    constexpr int KB = WIDE ? 128 : 64;                 // keys of a block
     constexpr int NW = 4, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE + 512;   // Q, dO, then lse[64], delta[64]
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int kg = wave >> 1, qh = wave & 1;
+    const int kg = WIDE ? wave : wave >> 1, qh0 = WIDE ? 0 : wave & 1;
     const int h = lane >> 5;
     int kblk, head, b;
-    block_coords((a.S + 63) / 64, a.heads, a.causal != 0, false, true, kblk, head, b);   // key block 0 is the heaviest
+    block_coords((a.S + KB - 1) / KB, a.heads, a.B, a.causal != 0, false, order, kblk, head, b);   // key block 0 is the heaviest
     // real head dimension: the tile width (no padding, every guard below folds away), a fixed narrower
     // width (the guards fold to constants), or with DR = 0 whatever the call says
     constexpr bool PAD = DR != D;
@@ -592,13 +635,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
     const int H = a.heads * dr, ld = 3 * H;
     const bf16_t* qkv = (const bf16_t*)a.qkv + (size_t)b * a.S * ld + head * dr;
     const bf16_t* dobase = (const bf16_t*)a.dctx + (size_t)b * a.S * H + head * dr;
-    const int k_wave = kblk * 64 + kg * 32;
+    const int k_wave = kblk * KB + kg * 32;
     const int k_lane = k_wave + (lane & 31);
     const int klen = a.causal ? a.S : (a.lens ? a.lens[b] : a.S);
     bf16_t* dk_out = (bf16_t*)a.dqkv + ((size_t)b * a.S + k_lane) * ld + H + head * dr;
     bf16_t* dv_out = dk_out + H;
-    if (kblk * 64 >= klen) {      // the whole block of keys is padding: no query attends it
-        if (qh == 0 && (!RAG || k_lane < a.S)) {
+    if (kblk * KB >= klen) {      // the whole block of keys is padding: no query attends it
+        if (qh0 == 0 && (!(RAG || WIDE) || k_lane < a.S)) {
             const uint2 z = make_uint2(0u, 0u);
 #pragma unroll
             for (int t2 = 0; t2 < DT; ++t2)
@@ -615,7 +658,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
     const float* lse = a.lse + ((size_t)b * a.heads + head) * a.S;
     const float* dlt = a.delta + ((size_t)b * a.heads + head) * a.S;
 
-    const int k_src = RAG ? min(k_lane, klen - 1) : k_lane;     // row this lane reads (its own, unless it is padding)
+    const int k_src = RAG || WIDE ? min(k_lane, RAG ? klen - 1 : a.S - 1) : k_lane;     // row this lane reads (its own, unless it is padding)
     bf16x8 kf[KS], vf[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -629,8 +672,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
         for (int v = 0; v < 16; ++v) { dk[t][v] = 0.f; dv[t][v] = 0.f; }
 
     bool by_rows = false;       // a query on the diagonal is not finite
-    const bool pad_in_block = kblk * 64 + 64 > klen;   // some of this block's keys are padding
-    const int t0 = a.causal ? kblk : 0;        // first 64-query tile that can see this block's keys
+    const bool some_padded = (WIDE ? k_wave + 32 : kblk * 64 + 64) > klen;   // some of this wave's (block's) keys are padding
+    const int t0 = a.causal ? kblk * (KB / 64) : 0;        // first 64-query tile that can see this block's keys
     const int nt = (a.S + 63) / 64;
 
     TilePlan<D, NW, PAD> plan_q, plan_do;
@@ -669,10 +712,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             load_stage(t + 1, smem + ((t + 1) & 1) * STAGE);
             stat_next = fetch_stat(t + 2);
         }
-        const int qw = q0 + 32 * qh;                     // first query of this wave's half
-        if (a.causal && qw + 31 < k_wave) continue;      // no query of this half reaches this wave's keys
+        if (WIDE && k_wave >= klen) continue;            // none of this wave's keys exists, or is attended
         const char* sq = smem + (t & 1) * STAGE;
         const char* sdo = sq + TILE;
+#pragma unroll
+        for (int qh = qh0; qh < (WIDE ? 2 : qh0 + 1); ++qh) {
+        const int qw = q0 + 32 * qh;                     // first query of this wave's half
+        if (a.causal && qw + 31 < k_wave) continue;      // no query of this half reaches this wave's keys
         const float* s_nlse = (const float*)(sq + 2 * TILE) + 32 * qh;
         const float* s_ndlt = (const float*)(sq + 2 * TILE) + 64 + 32 * qh;
         const bool need_mask = a.causal && qw < k_wave + 31;
@@ -701,7 +747,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             for (int v = 0; v < 16; ++v)
                 if (qw + acc_row(v, h) >= a.S) sacc[v] = -INFINITY;
         }
-        if (pad_in_block) {
+        if (some_padded) {
             stay_a_branch();
 #pragma unroll
             for (int v = 0; v < 16; ++v)
@@ -730,14 +776,17 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             }
         }
         }
+        }
     }
     if (RAG && a.causal && any_wave(by_rows, smem)) {
         for (int k = kblk * 64; k < min(kblk * 64 + 64, a.S); ++k) attn_bwd_dkv_row<bf16_t>(a, scale, k, head, b, (float*)smem);
         return;
     }
+    if (WIDE && k_lane >= a.S) return;
+    float* xo = (float*)smem + (WIDE ? 0 : kg * (2 * DT * 16 * 64));
+    if constexpr (!WIDE) {
     __syncthreads();
-    float* xo = (float*)smem + kg * (2 * DT * 16 * 64);
-    if (qh == 1) {
+    if (qh0 == 1) {
 #pragma unroll
         for (int t2 = 0; t2 < DT; ++t2)
 #pragma unroll
@@ -747,7 +796,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             }
     }
     __syncthreads();
-    if (qh == 1 || (RAG && k_lane >= a.S)) return;
+    if (qh0 == 1 || (RAG && k_lane >= a.S)) return;
+    }
 #pragma unroll
     for (int t2 = 0; t2 < DT; ++t2)
 #pragma unroll
@@ -755,8 +805,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             float k4[4], v4[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                k4[e] = (dk[t2][4 * g + e] + xo[(t2 * 16 + 4 * g + e) * 64 + lane]) * scale;
-                v4[e] = dv[t2][4 * g + e] + xo[((DT + t2) * 16 + 4 * g + e) * 64 + lane];
+                k4[e] = (WIDE ? dk[t2][4 * g + e] : dk[t2][4 * g + e] + xo[(t2 * 16 + 4 * g + e) * 64 + lane]) * scale;
+                v4[e] = WIDE ? dv[t2][4 * g + e] : dv[t2][4 * g + e] + xo[((DT + t2) * 16 + 4 * g + e) * 64 + lane];
             }
             if (t2 * 32 + 8 * g + 4 * h >= dr) continue;
             uint2 pk;
@@ -791,26 +841,63 @@ static int tiles_per_step(const AttnArgs& a) {
     return (a.S >= 512 && blocks <= 2L * cu_count()) ? 2 : 1;
 }
 
-template <int D, int DR, int NT, bool RAG>
+// Blocks of 128 rows whose four waves take 32 rows and all 64 columns of a tile each, in place of blocks of 64 rows
+// whose waves share the tile's halves: half the loads and barriers per product, nothing to merge, but half as many
+// blocks.  Whole tiles only.  Narrow / wide, us, on 256 CUs:
+//   forward, no mask: 16 heads, S 512, B 8 (512 wide blocks), d 64 15.7 / 14.7, d 128 24.5 / 19.8; 256 blocks, d 64
+//     0.95, d 128 1.21 of the speed; B 8, S 2048, 16 heads of 128, causal 194 / 164, B 2, S 2048, 40 heads of 128 129 / 104;
+//   forward, causal, d 64 and less: loses at S 2048 and 4096 with 512 blocks (0.82 - 0.93: narrow ones balance better),
+//     wins at S 512 (1.08) and from 768 on (1.07 - 1.3); d 96 and 128: 1.05 - 1.4 from 512 on;
+//   dQ: 1.03 - 1.15 of the whole backward from 512 on, 0.92 - 0.95 causal with long sequences below 768;
+//   dK/dV, whose registers allow two blocks per CU: 1.02 - 1.14 without a mask where rounds of two blocks per CU are
+//     full (0.95 - 0.97 at 768), causal only at S 512 and less (1.05 - 1.15; else 0.85 - 1.0).
+enum Which { FWD, DQ, DKV };
+static bool wide_rows(const AttnArgs& a, Which k) {
+    if (a.S % 64) return false;
+    const long cu = cu_count(), n = (long)((a.S + 127) / 128) * a.heads * a.B, rounds = (n + 2 * cu - 1) / (2 * cu);
+    if (n < (k == FWD && !a.causal && a.d > 64 ? cu : 2 * cu)) return false;
+    if (!a.causal) {
+        if (k != FWD && a.S % 128 && a.S < 384) return false;       // an idle half block counts (S 192 0.97 - 0.99 of the backward)
+        return k != DKV || n * 100 >= 85 * rounds * 2 * cu;
+    }
+    if (a.S <= 512) return true;
+    return k == FWD ? a.d > 64 || n >= 3 * cu : k == DQ && (a.S <= 1024 || n >= 3 * cu);
+}
+
+// Folded for two resident blocks per CU (narrow kernels, wide ones up to two blocks per CU; 768 wide blocks of d 128,
+// forward: heaviest first 1.38, folded 1.16 of the narrow speed).  All batch entries together while about four blocks per CU
+// hold the launch (16 heads of 64, S 1024, B 4, forward, narrow 1.37, backward 1.07; at 2048 blocks 0.9), one fewer for wide
+// heads, whose keys and values fill the L2s (backward, d 128, 1024 blocks 0.95 - 0.98).
+static int block_order(const AttnArgs& a, long blocks, bool wide, bool one_per_cu) {
+    const long cu = cu_count();
+    const bool folded = !one_per_cu && (!wide || blocks <= 2 * cu);
+    const bool all = a.d > 64 ? blocks < 4 * cu : blocks <= 4 * cu;
+    return (folded ? ORDER_FOLDED : 0) | (all ? ORDER_ALL : 0);
+}
+
+template <int D, int DR, int NT, bool RAG, bool WIDE = false>
 static hipError_t launch_fwd_nt(const AttnArgs& a, hipStream_t s) {
     const float scale = 1.f / sqrtf((float)a.d);
-    const dim3 grid(((a.S + 63) / 64) * a.heads * a.B), block(256 * NT);
+    constexpr int QB = WIDE ? 128 : 64;
+    const dim3 grid(((a.S + QB - 1) / QB) * a.heads * a.B), block(256 * NT);
     const size_t stages = (size_t)2 * NT * 2 * 64 * D * 2;
-    const size_t merge = (size_t)2 * (2 * NT - 1) * ((D / 32) * 16 * 64 + 128) * sizeof(float);
+    const size_t merge = WIDE ? 0 : (size_t)2 * (2 * NT - 1) * ((D / 32) * 16 * 64 + 128) * sizeof(float);
     const size_t smem = std::max(std::max(stages, merge), RAG && a.causal ? attn_row_lds_fwd(a) : 0);
     static std::atomic<bool> set{false};   // several host threads may launch at once
     if (!set.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_fwd_mfma_kernel<D, DR, NT, RAG>, std::max(std::max(stages, merge), kMaxAttnRowLds));
+        hipError_t e = set_smem(attn_fwd_mfma_kernel<D, DR, NT, RAG, WIDE>, std::max(std::max(stages, merge), kMaxAttnRowLds));
         if (e != hipSuccess) return e;
         set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, DR, NT, RAG>), grid, block, smem, s, a, scale);
+    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, DR, NT, RAG, WIDE>), grid, block, smem, s, a, scale,
+                       block_order(a, grid.x, WIDE, NT == 2));
     return hipGetLastError();
 }
 template <int D, int DR>
 static hipError_t launch_fwd_t(const AttnArgs& a, hipStream_t s) {
     if (a.S % 64)
         return tiles_per_step(a) == 2 ? launch_fwd_nt<D, DR, 2, true>(a, s) : launch_fwd_nt<D, DR, 1, true>(a, s);
+    if (wide_rows(a, FWD)) return launch_fwd_nt<D, DR, 1, false, true>(a, s);
     return tiles_per_step(a) == 2 ? launch_fwd_nt<D, DR, 2, false>(a, s) : launch_fwd_nt<D, DR, 1, false>(a, s);
 }
 
@@ -823,28 +910,48 @@ hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) {
     return a.d > 64 ? launch_fwd_t<128, 0>(a, s) : launch_fwd_t<64, 0>(a, s);
 }
 
-template <int D, int DR, bool RAG>
-static hipError_t launch_bwd_rag(const AttnArgs& a, hipStream_t s) {
+template <int D, int DR, bool RAG, bool WIDE>
+static hipError_t launch_dq(const AttnArgs& a, hipStream_t s) {
     const float scale = 1.f / sqrtf((float)a.d);
-    const dim3 grid(((a.S + 63) / 64) * a.heads * a.B), block(256);
-    constexpr size_t stages = 2 * 2 * 64 * D * 2, stages2 = 2 * (2 * 64 * D * 2 + 512);
-    const bool rows = RAG && a.causal;
-    const size_t smem = std::max(stages, rows ? attn_row_lds_dq(a) : 0), smem2 = std::max(stages2, rows ? attn_row_lds_dkv(a) : 0);
+    constexpr int QB = WIDE ? 128 : 64;
+    const dim3 grid(((a.S + QB - 1) / QB) * a.heads * a.B), block(256);
+    constexpr size_t stages = 2 * 2 * 64 * D * 2;
+    const size_t smem = std::max(stages, RAG && a.causal ? attn_row_lds_dq(a) : 0);
     static std::atomic<bool> set{false};   // several host threads may launch at once
     if (!set.load(std::memory_order_acquire)) {
-        hipError_t e = set_smem(attn_bwd_dq_mfma_kernel<D, DR, RAG>, std::max(stages, kMaxAttnRowLds));
-        if (e == hipSuccess) e = set_smem(attn_bwd_dkv_mfma_kernel<D, DR, RAG>, std::max(stages2, kMaxAttnRowLds));
+        hipError_t e = set_smem(attn_bwd_dq_mfma_kernel<D, DR, RAG, WIDE>, std::max(stages, kMaxAttnRowLds));
         if (e != hipSuccess) return e;
         set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<D, DR, RAG>), grid, block, smem, s, a, scale);
-    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<D, DR, RAG>), grid, block, smem2, s, a, scale);
+    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<D, DR, RAG, WIDE>), grid, block, smem, s, a, scale,
+                       block_order(a, grid.x, WIDE, false));
+    return hipGetLastError();
+}
+template <int D, int DR, bool RAG, bool WIDE>
+static hipError_t launch_dkv(const AttnArgs& a, hipStream_t s) {
+    const float scale = 1.f / sqrtf((float)a.d);
+    constexpr int KB = WIDE ? 128 : 64;
+    const dim3 grid(((a.S + KB - 1) / KB) * a.heads * a.B), block(256);
+    constexpr size_t stages = 2 * (2 * 64 * D * 2 + 512);
+    const size_t smem = std::max(stages, RAG && a.causal ? attn_row_lds_dkv(a) : 0);
+    static std::atomic<bool> set{false};
+    if (!set.load(std::memory_order_acquire)) {
+        hipError_t e = set_smem(attn_bwd_dkv_mfma_kernel<D, DR, RAG, WIDE>, std::max(stages, kMaxAttnRowLds));
+        if (e != hipSuccess) return e;
+        set.store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<D, DR, RAG, WIDE>), grid, block, smem, s, a, scale,
+                       block_order(a, grid.x, WIDE, false));
     return hipGetLastError();
 }
 
 template <int D, int DR>
 static hipError_t launch_bwd_t(const AttnArgs& a, hipStream_t s) {
-    return a.S % 64 ? launch_bwd_rag<D, DR, true>(a, s) : launch_bwd_rag<D, DR, false>(a, s);
+    hipError_t e = a.S % 64 ? launch_dq<D, DR, true, false>(a, s) :
+                   wide_rows(a, DQ) ? launch_dq<D, DR, false, true>(a, s) : launch_dq<D, DR, false, false>(a, s);
+    if (e != hipSuccess) return e;
+    return a.S % 64 ? launch_dkv<D, DR, true, false>(a, s) :
+           wide_rows(a, DKV) ? launch_dkv<D, DR, false, true>(a, s) : launch_dkv<D, DR, false, false>(a, s);
 }
 
 hipError_t launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t s) {
