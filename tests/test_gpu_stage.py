@@ -196,6 +196,17 @@ def test_next_iteration_while_gradients_are_still_computed(forward_ahead):
     _assert_same(last, refs[3], "last")
 
 
+@pytest.mark.parametrize("forward_ahead,layers", [(0, 2), (1, 1), (0, 3)])
+def test_open_group_dropped_and_its_buffers_used_again_at_once(forward_ahead, layers):
+    """Three micro-batches of a group of four, cleared and started over several times without a wait: the buffers of
+    a dropped group go to the next backwards while column reductions that read them may still run."""
+    e = _EarlyReads(n_micro=3, wgrad_group=4, forward_ahead=forward_ahead, layers=layers)
+    with e.stage() as g:
+        keep = [e.iteration(g, it) for it in range(4)]
+        got = {k: g.grad(*k) for k in e.names}
+    _assert_same(got, e.reference(3), "last")
+
+
 @pytest.mark.parametrize("stash_recompute", [0, 1])
 def test_parameters_set_while_gradients_are_still_computed(stash_recompute):
     """Parameters set right after the first read: the gradients still to come are those of the old ones (the
