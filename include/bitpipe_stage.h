@@ -74,6 +74,10 @@ typedef struct bp_opts {
                            group keeps the stashes of its waiting micro-batches (beyond
                            max_inflight) plus their output gradients until it is complete or
                            until bp_stage_get_grad / bp_run_schedule's merge flushes it.
+                           With 0 and 16 MB of gradients or more in a chunk, groups that complete while
+                           other stashes are live are kept too, up to 16384 tokens and 8 GiB of them,
+                           so that their products run while the first gradients are read; a given
+                           size keeps no complete group.
                            bp_run_schedule uses groups no larger than the number of backward
                            calls a (direction, stage) gets in the iteration.                  */
     int stash_recompute;/* 0: the stash keeps everything the backward reads, 16*T*H elements per

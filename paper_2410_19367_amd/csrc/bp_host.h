@@ -60,7 +60,20 @@ struct StashSlot {
 // group: its stash slot stays held and `buf` keeps, per layer, the gradients w.r.t. the outputs
 // of the four linear maps (dz, du, dy, dqkv).
 struct PendingMb { int slot; void* buf; };
-struct PendGroup { std::vector<PendingMb> items; };
+struct PendGroup {
+    std::vector<PendingMb> items;
+    // complete groups whose GEMMs wait for the reads at the end of the iteration, oldest first; of these
+    // the matrix that is read first has been multiplied (first_written: since the last clear)
+    std::vector<std::vector<PendingMb>> kept;
+    bool first_written = false;
+    size_t kept_items() const {
+        size_t n = 0;
+        for (const auto& k : kept) n += k.size();
+        return n;
+    }
+    // accumulate mode of the next contribution to matrix k of layer l: the first one after a clear overwrites
+    int acc(uint8_t clean, int l, int k) const { return (clean & 1) && !(first_written && l == 0 && k == 3) ? 2 : 1; }
+};
 
 // Everything one stream pair needs to run forwards and backwards on its own: the streams, the
 // events that order the two, and the workspaces the kernels of a backward share.  A stage object has
@@ -125,7 +138,7 @@ struct Stage : LaneState {
     int wgrad_group = 1;
     bool lean = false;                   // stash without LN outputs and GELU output: recomputed for the weight gradients
     std::vector<PendGroup> pend[2];
-    // Reading gradients while others are still computed: wgrad_one leaves an event behind every weight gradient of
+    // Reading gradients while others are still computed: mark_ready leaves an event behind every weight gradient of
     // direction 0 ([chunk][layer][k]), flush_group one in front of a group's GEMMs, behind which the side stream
     // holds no column reduction that came before.  "ready" says that the event was recorded after the tensor's last
     // writer; whoever writes in another way takes it back.
@@ -140,6 +153,17 @@ struct Stage : LaneState {
     // 384 tokens, H 448 4.23 against 4.51.
     bool reads_early() const { return !is_view && (size_t)L * g_layer_bytes >= ((size_t)16 << 20); }
     bool leaves_events(hipStream_t on) const { return on != stream && wgrad_group > 1 && reads_early(); }
+    // Complete groups are kept until the reads behind the last backward (see Stage::backward) if the library chose the
+    // group size itself, as many as hold kKeptTokens tokens (what a default group holds at most) and 8 GiB: about what the
+    // GEMMs of the last group leave of the time that the link takes (per element of a weight matrix 70 ps of link
+    // against 26 ps of GEMM over 16384 tokens).  Not with the reduced stash, which is for callers short of memory.
+    static constexpr size_t kKeptTokens = 16384;
+    bool own_group = false;
+    bool keeps_groups(hipStream_t on) const {
+        return own_group && !lean && leaves_events(on) && (size_t)wgrad_group * T <= kKeptTokens &&
+               (kKeptTokens / T + 1) * (size_t)L * (s_layer_bytes + q_layer_bytes) <= ((size_t)8 << 30);
+    }
+    static bool is_first_read(int l, int k) { return l == 0 && k == 3; }    // Wqkv of layer 0
     void forget_ready() { matrix_ready.assign(matrix_ready.size(), 0); vectors_ready = false; }
     size_t q_dz = 0, q_du = 0, q_dy = 0, q_dqkv = 0, q_layer_bytes = 0;
     int slot_capacity = 8;                           // most live stashes (held ones come on top)
@@ -207,9 +231,11 @@ struct Stage : LaneState {
     int acquire_slot(int chunk, int mb, int* out);
     int live_slots() const;
 
-    int wgrad_one(int dir, int chunk, int l, int k, const void* cur_x, const void* cur_dy, int acc,
-                  hipStream_t ss);
-    int release_group(PendGroup& grp, hipStream_t ss);
+    int wgrad_one(int dir, int chunk, int l, int k, const std::vector<PendingMb>& items, const void* cur_x,
+                  const void* cur_dy, int acc, hipStream_t ss);
+    int mark_ready(int dir, int chunk, int l, int k, hipStream_t ss);
+    int multiply_kept(int dir, int chunk, int l, const std::vector<PendingMb>& items, hipStream_t ss);
+    int release_group(std::vector<PendingMb>& items, hipStream_t ss);
     int flush_group(int dir, int chunk);
     int flush_all();
     int drop_pending();

@@ -164,6 +164,7 @@ int Stage::create(Stage** out, int layers, int hidden, int heads, int seq, int m
     if (hipGetDevice(&st->device) != hipSuccess) { delete st; return fail(BP_EHIP, "hipGetDevice failed"); }
     st->esz = dtype_size(st->dtype);
     st->lean = opt.stash_recompute == 1;
+    st->own_group = opt.wgrad_group == 0;
     st->wgrad_group = opt.wgrad_group ? opt.wgrad_group : std::min(kMaxGemmSegments, std::max(1, 16384 / st->T));
     st->pend[0].resize(st->n_chunks);
     st->pend[1].resize(st->n_chunks);
@@ -365,7 +366,11 @@ Stage::~Stage() {
     }
     for (int dir = 0; dir < 2; ++dir)
         for (auto& grp : pend[dir])
-            for (auto& it : grp.items) hipFree(it.buf);
+            {
+                for (auto& it : grp.items) hipFree(it.buf);
+                for (auto& kept : grp.kept)
+                    for (auto& it : kept) hipFree(it.buf);
+            }
     for (auto e : sched_ev) if (e) hipEventDestroy(e);
     for (auto e : ev_matrix) if (e) hipEventDestroy(e);
     if (ev_vectors) hipEventDestroy(ev_vectors);
@@ -495,15 +500,14 @@ int Stage::merge_directions() {
 
 // ------------------------------------------------------------------ grouped weight gradients
 
-// Gradient of weight matrix k (0: W2, 1: W1, 2: Wo, 3: Wqkv) of one layer over the group's waiting
+// Gradient of weight matrix k (0: W2, 1: W1, 2: Wo, 3: Wqkv) of one layer over a group's waiting
 // micro-batches plus, when cur_x (the current micro-batch's stash of this layer) is given, the
 // current one: a single GEMM whose contraction runs over all their tokens.
-int Stage::wgrad_one(int dir, int chunk, int l, int k, const void* cur_x, const void* cur_dy, int acc,
-                     hipStream_t ss) {
+int Stage::wgrad_one(int dir, int chunk, int l, int k, const std::vector<PendingMb>& items, const void* cur_x,
+                     const void* cur_dy, int acc, hipStream_t ss) {
     static const int ids[4] = {BP_W2, BP_W1, BP_WO, BP_WQKV};
     const size_t sx[4] = {s_g, s_m, s_ctx, s_a}, qy[4] = {q_dz, q_du, q_dy, q_dqkv};
     const int Mk[4] = {F, H, H, H}, Nk[4] = {H, F, H, 3 * H};
-    const PendGroup& grp = pend[dir][chunk];
     const void* xs[kMaxGemmSegments];
     const void* ys[kMaxGemmSegments];
     int n = 0;
@@ -530,7 +534,7 @@ int Stage::wgrad_one(int dir, int chunk, int l, int k, const void* cur_x, const 
         return BP_OK;
     };
     int rc;
-    for (const PendingMb& it : grp.items) {
+    for (const PendingMb& it : items) {
         if (n >= kMaxGemmSegments) return fail(BP_ESTATE, "weight-gradient group overflow");
         if ((rc = operand((const char*)slots[it.slot].buf + (size_t)l * s_layer_bytes, n, &xs[n]))) return rc;
         ys[n] = (const char*)it.buf + (size_t)l * q_layer_bytes + qy[k];
@@ -556,23 +560,38 @@ int Stage::wgrad_one(int dir, int chunk, int l, int k, const void* cur_x, const 
     Scoped sc(this, BP_K_GEMM, 2.0 * Mk[k] * Nk[k] * (double)T * n, 0);
     hipError_t e = launch_gemm(dtype, g, ss);
     if (e != hipSuccess) return fail(BP_EHIP, "weight-gradient GEMM: %s", hipGetErrorString(e));
-    if (dir == 0 && leaves_events(ss)) {        // get_grad waits for this one only
-        const size_t i = ((size_t)chunk * L + l) * 4 + k;
-        if (matrix_ready.empty()) {
-            ev_matrix.assign((size_t)n_chunks * L * 4, nullptr);
-            matrix_ready.assign(ev_matrix.size(), 0);
-        }
-        e = ev_matrix[i] ? hipSuccess : hipEventCreateWithFlags(&ev_matrix[i], hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventRecord(ev_matrix[i], ss);
-        if (e != hipSuccess) return fail(BP_EHIP, "weight-gradient event: %s", hipGetErrorString(e));
-        matrix_ready[i] = 1;
+    return BP_OK;
+}
+
+// Behind the last contribution to a weight gradient of direction 0: get_grad waits for this one only.
+int Stage::mark_ready(int dir, int chunk, int l, int k, hipStream_t ss) {
+    if (dir != 0 || !leaves_events(ss)) return BP_OK;
+    const size_t i = ((size_t)chunk * L + l) * 4 + k;
+    if (matrix_ready.empty()) {
+        ev_matrix.assign((size_t)n_chunks * L * 4, nullptr);
+        matrix_ready.assign(ev_matrix.size(), 0);
     }
+    hipError_t e = ev_matrix[i] ? hipSuccess : hipEventCreateWithFlags(&ev_matrix[i], hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(ev_matrix[i], ss);
+    if (e != hipSuccess) return fail(BP_EHIP, "weight-gradient event: %s", hipGetErrorString(e));
+    matrix_ready[i] = 1;
+    return BP_OK;
+}
+
+// The four GEMMs of one layer for a complete group that was kept.
+int Stage::multiply_kept(int dir, int chunk, int l, const std::vector<PendingMb>& items, hipStream_t ss) {
+    uint8_t& clean = grad_clean[dir][(size_t)chunk * L + l];
+    for (int k = 3; k >= 0; --k) {
+        if (is_first_read(l, k)) continue;              // multiplied when the group was complete
+        if (int rc = wgrad_one(dir, chunk, l, k, items, nullptr, nullptr, (clean & 1) ? 2 : 1, ss)) return rc;
+    }
+    clean &= ~1;
     return BP_OK;
 }
 
 // The group's stashes and buffers become reusable once the side stream has passed this point.
-int Stage::release_group(PendGroup& grp, hipStream_t ss) {
-    for (PendingMb& it : grp.items) {
+int Stage::release_group(std::vector<PendingMb>& items, hipStream_t ss) {
+    for (PendingMb& it : items) {
         StashSlot& sl = slots[it.slot];
         if (ss != stream) {
             hipError_t e = hipSuccess;
@@ -584,13 +603,13 @@ int Stage::release_group(PendGroup& grp, hipStream_t ss) {
         sl.held = false;
         pend_pool.push_back(it.buf);
     }
-    grp.items.clear();
+    items.clear();
     return BP_OK;
 }
 
 int Stage::flush_group(int dir, int chunk) {
     PendGroup& grp = pend[dir][chunk];
-    if (grp.items.empty()) return BP_OK;
+    if (grp.items.empty() && grp.kept.empty()) return BP_OK;
     hipStream_t ss = side_stream();
     if (ss != stream) {     // the waiting gradients were written on the main stream
         hipError_t e = hipEventRecord(ev_ready[0], stream);
@@ -608,11 +627,23 @@ int Stage::flush_group(int dir, int chunk) {
     int rc;
     for (int l = 0; l < L; ++l) {       // the order in which the gradients are usually read
         uint8_t& clean = grad_clean[dir][(size_t)chunk * L + l];
-        for (int k = 3; k >= 0; --k)
-            if ((rc = wgrad_one(dir, chunk, l, k, nullptr, nullptr, (clean & 1) ? 2 : 1, ss))) return rc;
+        for (int k = 3; k >= 0; --k) {
+            int acc = grp.acc(clean, l, k);
+            for (const auto& kept : grp.kept) {
+                if (is_first_read(l, k)) continue;
+                if ((rc = wgrad_one(dir, chunk, l, k, kept, nullptr, nullptr, acc, ss))) return rc;
+                acc = 1;
+            }
+            if ((rc = wgrad_one(dir, chunk, l, k, grp.items, nullptr, nullptr, acc, ss))) return rc;
+            if ((rc = mark_ready(dir, chunk, l, k, ss))) return rc;
+        }
         clean &= ~1;
     }
-    if ((rc = release_group(grp, ss))) return rc;
+    for (auto& kept : grp.kept)
+        if ((rc = release_group(kept, ss))) return rc;
+    grp.kept.clear();
+    grp.first_written = false;
+    if ((rc = release_group(grp.items, ss))) return rc;
     if (ss != stream) {     // the next backward must not overwrite buffers these GEMMs still read
         hipError_t e = hipEventRecord(ev_misc, ss);
         if (e != hipSuccess) return fail(BP_EHIP, "flush_group: %s", hipGetErrorString(e));
@@ -635,9 +666,13 @@ int Stage::drop_pending() {
     bool any = false;
     for (int dir = 0; dir < 2; ++dir)
         for (auto& grp : pend[dir]) {
-            any = any || !grp.items.empty();
-            int rc = release_group(grp, ss);      // column sums of those calls may still be running
+            any = any || !grp.items.empty() || !grp.kept.empty();
+            int rc = release_group(grp.items, ss);      // column sums of those calls may still be running
+            for (auto& kept : grp.kept)
+                if (!rc) rc = release_group(kept, ss);
             if (rc) return rc;
+            grp.kept.clear();
+            grp.first_written = false;
         }
     if (any && ss != stream) {      // ... and read the buffers that the next backward takes from the pool
         hipError_t e = hipEventRecord(ev_misc, ss);
@@ -686,7 +721,7 @@ void Stage::held_bytes(size_t out[3]) const {
         else if (sl.held) out[1] += (size_t)L * s_layer_bytes;
     }
     for (int dir = 0; dir < 2; ++dir)
-        for (const auto& grp : pend[dir]) out[2] += grp.items.size() * (size_t)L * q_layer_bytes;
+        for (const auto& grp : pend[dir]) out[2] += (grp.items.size() + grp.kept_items()) * (size_t)L * q_layer_bytes;
 }
 
 void Stage::note_held() {
@@ -896,13 +931,28 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
     // With a side stream (and enough to read), the completing call too writes into such a buffer and multiplies at
     // its end, in the order in which get_grad is usually called, if no other stash is live: behind the last backward of an
     // iteration the gradients are then read one by one while the GEMMs run.  While others are live more backwards
-    // follow, and the GEMMs start as soon as their operands exist, beside the rest of this call's chain (two groups
-    // an iteration, forwards one ahead: H 1024 677 -> 691 TFLOP/s with nothing read, 15.19 -> 15.09 ms with all
-    // read, H 2560 45.7 -> 45.5 ms).  A stream of their own and spare buffers, so that the next backward need
-    // not wait for the GEMMs, gave nothing over this, and 1 % less at H 5120, where single products fill the chip.
+    // follow.  Then, if the library chose the group size, the complete group is kept for a while (keeps_groups): its
+    // GEMMs run behind the last backward too, where the host link is busy with what is read first and the chip idle:
+    // two layers of H 2048 31.0 -> 29.2 ms with all gradients read, H 3072 64.9 -> 59.0, H 2560 42.5 -> 38.4 ms.  Only
+    // the matrix that is read first (Wqkv of layer 0) is multiplied at once, so that the reads start no later.  With a
+    // given group size (or no memory for the buffer) the GEMMs start as soon as their operands exist, beside the
+    // rest of this call's chain (two groups an iteration, forwards one ahead: H 1024 677 -> 691 TFLOP/s with nothing read).
+    // A stream of their own and spare buffers, so that the next backward need not wait for the GEMMs, gave nothing
+    // over this, and 1 % less at H 5120, where single products fill the chip.
     PendGroup& grp = pend[dir][chunk];
     const bool completes = (int)grp.items.size() + 1 >= wgrad_group;
-    bool defer = !completes || (leaves_events(ss) && live_slots() == 1);
+    const bool keep = completes && keeps_groups(ss) && live_slots() > 1;
+    bool defer = !completes || keep || (leaves_events(ss) && live_slots() == 1);
+    // the oldest kept group makes room: its GEMMs run beside this call's chain, layer by layer
+    std::vector<PendingMb> oldest;
+    if (keep && (grp.kept_items() + grp.items.size() + 1) * (size_t)T > kKeptTokens && !grp.kept.empty()) {
+        oldest.swap(grp.kept.front());
+        grp.kept.erase(grp.kept.begin());
+    }
+    struct OldestGuard {    // a call that fails half-way: back to where it came from
+        PendGroup& grp; std::vector<PendingMb>& items;
+        ~OldestGuard() { if (!items.empty()) grp.kept.insert(grp.kept.begin(), items); }
+    } oldest_guard{grp, oldest};
     vectors_ready = false;                  // column reductions are on their way
     if (!leaves_events(ss)) forget_ready(); // ... and GEMMs without events behind them
     char* qbuf = nullptr;
@@ -914,6 +964,10 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             if (!completes) return rc;
             qbuf = nullptr;             // no room for the one buffer more: multiply along the way
             defer = false;
+            if (!oldest.empty()) {
+                grp.kept.insert(grp.kept.begin(), oldest);
+                oldest.clear();
+            }
         }
     }
     struct PoolGuard {      // hand the buffer back if the call fails half-way
@@ -938,7 +992,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         auto P = [&](int id) { return param(chunk, l, id); };
         auto G = [&](int id) { return grad(dir, chunk, l, id); };
         uint8_t& clean = grad_clean[dir][(size_t)chunk * L + l];
-        const int acc = (clean & 1) ? 2 : 1;    // first contribution after a clear overwrites
+        auto acc = [&](int k) { return grp.acc(clean, l, k); };
         char* qb = defer ? qbuf + (size_t)l * q_layer_bytes : nullptr;
         void* dx = l == 0 ? grad_in : defer ? (void*)(qb - q_layer_bytes + q_dz) : ws_dx[l % 3];
         void* big1 = defer ? (void*)(qb + q_du) : ws_big1[p];
@@ -949,6 +1003,10 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             BP_HIP(hipStreamWaitEvent(stream, ev_layer_done[p], 0));
             layer_done_pending[p] = false;
         }
+        auto wgrad_along = [&](int k, const void* dy) {
+            const int rc = wgrad_one(dir, chunk, l, k, grp.items, sb, dy, acc(k), ss);
+            return rc ? rc : mark_ready(dir, chunk, l, k, ss);
+        };
         // column-sum partial regions: db2 | (dgamma2, dbeta2) | dbo | dbqkv | (dgamma1, dbeta1) | db1
         const size_t ch = colsum_chunks(T);
         float* p_b2 = ws_colsum[p];
@@ -960,7 +1018,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
 
         // z = y + g W2 + b2
         if (!defer) BP_HIP(hand_over(0));                                                                               // dz
-        if (!defer && (rc = wgrad_one(dir, chunk, l, 0, sb, dz, acc, ss))) return rc;                 // dW2
+        if (!defer && (rc = wgrad_along(0, dz))) return rc;                 // dW2
         {   // du = (dz W2^T) * gelu'(u + b1) with the db1 partials: one kernel unless the caller's gradient is unaligned
             GemmArgs bg;
             bg.A = dz; bg.B = P(BP_W2); bg.C = big1; bg.bias = (const float*)P(BP_B1); bg.residual = nullptr;
@@ -979,7 +1037,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             }
         }
         if (!defer) BP_HIP(hand_over(1));                                                                               // du
-        if (!defer && (rc = wgrad_one(dir, chunk, l, 1, sb, big1, acc, ss))) return rc;              // dW1
+        if (!defer && (rc = wgrad_along(1, big1))) return rc;              // dW1
         if ((rc = gemm(big1, F, 0, P(BP_W1), F, 1, h1, H, T, H, F, nullptr, nullptr, 0))) return rc;        // dm
         {   // dy = dz + LN2bwd(dm)
             Scoped sc(this, BP_K_LN_BWD, 0, 4 * unit);
@@ -988,7 +1046,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         }
         // y = x + ctx Wo + bo
         if (!defer) BP_HIP(hand_over(2));                                                                               // dy
-        if (!defer && (rc = wgrad_one(dir, chunk, l, 2, sb, h2, acc, ss))) return rc;              // dWo
+        if (!defer && (rc = wgrad_along(2, h2))) return rc;              // dWo
         if ((rc = gemm(h2, H, 0, P(BP_WO), H, 1, ws_h4, H, T, H, H, nullptr, nullptr, 0))) return rc;       // dctx
         {
             AttnArgs a{B, S, heads, d, causal ? 1 : 0, ln, sb + s_qkv, sb + s_ctx, (float*)(sb + s_lse),
@@ -998,7 +1056,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         }
         // qkv = a Wqkv + bqkv
         if (!defer) BP_HIP(hand_over(3));                                                                               // dqkv
-        if (!defer && (rc = wgrad_one(dir, chunk, l, 3, sb, big2, acc, ss))) return rc;              // dWqkv
+        if (!defer && (rc = wgrad_along(3, big2))) return rc;              // dWqkv
         if ((rc = gemm(big2, 3 * H, 0, P(BP_WQKV), 3 * H, 1, h5, H, T, H, 3 * H, nullptr, nullptr, 0))) return rc;  // da
         BP_HIP(hand_over(4));                                                                               // da
         {   // every bias and LayerNorm-parameter gradient of the layer in one batched reduction
@@ -1017,6 +1075,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             BP_LAUNCH(launch_colsum_batch(dtype, T, cb, ss));
         }
         clean &= defer ? ~2 : 0;
+        if (!oldest.empty() && (rc = multiply_kept(dir, chunk, l, oldest, ss))) return rc;
         if (two) {
             BP_HIP(hipEventRecord(ev_layer_done[p], ss));
             layer_done_pending[p] = true;
@@ -1049,9 +1108,26 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         grp.items.push_back(PendingMb{slot, qbuf});
         qbuf = nullptr;                         // owned by the group now
         note_held();                            // (before the flush: a complete group holds the most)
-        if (completes && (rc = flush_group(dir, chunk))) return rc;
+        if (!oldest.empty()) {                  // the next backward takes the buffers that these GEMMs read
+            if ((rc = release_group(oldest, ss))) return rc;
+            BP_HIP(hipEventRecord(ev_misc, ss));
+            call_done_pending = true;
+        }
+        if (keep) {
+            for (int l = 0; l < L; ++l)
+                for (int k = 3; k >= 0; --k) {
+                    if (!is_first_read(l, k)) continue;
+                    const uint8_t clean = grad_clean[dir][(size_t)chunk * L + l];
+                    if ((rc = wgrad_one(dir, chunk, l, k, grp.items, nullptr, nullptr, grp.acc(clean, l, k), ss))) return rc;
+                    grp.first_written = true;
+                }
+            grp.kept.emplace_back();
+            grp.kept.back().swap(grp.items);
+        } else if (completes && (rc = flush_group(dir, chunk))) {
+            return rc;
+        }
     } else {
-        if ((rc = release_group(grp, ss))) return rc;
+        if ((rc = release_group(grp.items, ss))) return rc;
         if (two) {
             // the stash may be handed to a new forward only after the side stream has read it
             if (!slots[slot].side_done)

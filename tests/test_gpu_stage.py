@@ -207,6 +207,30 @@ def test_open_group_dropped_and_its_buffers_used_again_at_once(forward_ahead, la
     _assert_same(got, e.reference(3), "last")
 
 
+@pytest.mark.parametrize("n_micro,n_chunks,layers", [(16, 1, 2), (26, 1, 2), (17, 2, 1), (33, 1, 1)])
+def test_kept_groups_give_the_bits_of_given_groups(n_micro, n_chunks, layers):
+    """Groups of eight by default and one micro-batch ahead: complete groups are kept (two of 8 x 1024 tokens, a third
+    makes the oldest multiply).  Their GEMMs add up in the same order as with a group size of eight given, where none
+    is kept: the same bits, also when iterations are cleared unread, and the memory they take is bounded."""
+    import paper_2410_19367_amd as bp
+    kept, given = [_EarlyReads(n_micro=n_micro, wgrad_group=w, forward_ahead=1, n_chunks=n_chunks, layers=layers) for w in (0, 8)]
+    got = []
+    for e in (kept, given):
+        with e.stage() as g:
+            bp.bp_stage_reset_peak_bytes(g.h)
+            one = bp.bp_stage_stash_bytes(g.h) + layers * e.cfg.T * (e.cfg.F + 5 * e.cfg.hidden) * 2
+            results = []
+            alive = [e.iteration(g, 0)]
+            results.append({k: g.grad(*k) for k in e.names})
+            alive += [e.iteration(g, 1), e.iteration(g, 2)]     # the first of these is cleared unread
+            results.append({k: g.grad(*k) for k in e.names})
+            got.append(results)
+            most = bp.bp_stage_held_bytes(g.h)["peak_total"] / one / n_chunks
+            assert most <= (16 + 8 + 2 if e is kept else 8 + 2), most
+    for a, b in zip(*got):
+        _assert_same(a, b, "kept")
+
+
 @pytest.mark.parametrize("stash_recompute", [0, 1])
 def test_parameters_set_while_gradients_are_still_computed(stash_recompute):
     """Parameters set right after the first read: the gradients still to come are those of the old ones (the
