@@ -235,6 +235,7 @@ struct Stage : LaneState {
                   const void* cur_dy, int acc, hipStream_t ss);
     int mark_ready(int dir, int chunk, int l, int k, hipStream_t ss);
     int multiply_kept(int dir, int chunk, int l, const std::vector<PendingMb>& items, hipStream_t ss);
+    int give_back_kept(bool* any);
     int release_group(std::vector<PendingMb>& items, hipStream_t ss);
     int flush_group(int dir, int chunk);
     int flush_all();

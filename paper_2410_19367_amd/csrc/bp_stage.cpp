@@ -119,6 +119,7 @@ static int dev_alloc(void** p, size_t bytes) {
     hipError_t e = hipMalloc(p, bytes ? bytes : 256);
     if (e != hipSuccess) {
         (void)hipGetLastError();
+        *p = nullptr;
         return fail(BP_ENOMEM, "hipMalloc(%zu bytes) failed: %s", bytes, hipGetErrorString(e));
     }
     return BP_OK;
@@ -589,6 +590,34 @@ int Stage::multiply_kept(int dir, int chunk, int l, const std::vector<PendingMb>
     return BP_OK;
 }
 
+// Memory is short: the kept groups multiply now, and their stashes and buffers go back to the pools.  *any: there were some.
+int Stage::give_back_kept(bool* any) {
+    *any = false;
+    hipStream_t ss = side_stream();
+    int rc;
+    for (int dir = 0; dir < 2; ++dir)
+        for (int c = 0; c < n_chunks; ++c) {
+            PendGroup& grp = pend[dir][c];
+            for (auto& kept : grp.kept) {
+                for (int l = 0; l < L; ++l)
+                    if ((rc = multiply_kept(dir, c, l, kept, ss))) return rc;
+                if ((rc = release_group(kept, ss))) return rc;
+                *any = true;
+            }
+            grp.kept.clear();
+            grp.first_written = false;
+        }
+    if (*any) {
+        forget_ready();
+        if (ss != stream) {
+            hipError_t e = hipEventRecord(ev_misc, ss);
+            if (e != hipSuccess) return fail(BP_EHIP, "give_back_kept: %s", hipGetErrorString(e));
+            call_done_pending = true;
+        }
+    }
+    return BP_OK;
+}
+
 // The group's stashes and buffers become reusable once the side stream has passed this point.
 int Stage::release_group(std::vector<PendingMb>& items, hipStream_t ss) {
     for (PendingMb& it : items) {
@@ -750,11 +779,18 @@ int Stage::acquire_slot(int chunk, int mb, int* out) {
         slots.emplace_back();
         pick = (int)slots.size() - 1;
     }
-    StashSlot& sl = slots[pick];
-    if (!sl.buf) {
-        int rc = dev_alloc(&sl.buf, (size_t)L * s_layer_bytes);
+    if (!slots[pick].buf) {
+        int rc = dev_alloc(&slots[pick].buf, (size_t)L * s_layer_bytes);
+        if (rc == BP_ENOMEM) {      // one of a kept group instead
+            bool any;
+            int rc2 = give_back_kept(&any);
+            if (rc2) return rc2;
+            for (size_t i = 0; any && i < slots.size(); ++i)
+                if (slots[i].buf && !slots[i].live && !slots[i].held) { pick = (int)i; rc = BP_OK; break; }
+        }
         if (rc) return rc;
     }
+    StashSlot& sl = slots[pick];
     if (sl.side_pending) {
         // the previous owner's weight-gradient kernels may still be reading this stash
         hipError_t e = hipStreamWaitEvent(forward_stream(), sl.side_done, 0);
@@ -957,10 +993,19 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
     if (!leaves_events(ss)) forget_ready(); // ... and GEMMs without events behind them
     char* qbuf = nullptr;
     if (defer) {
-        if (!pend_pool.empty()) {
+        rc = BP_OK;
+        if (pend_pool.empty() && (rc = dev_alloc((void**)&qbuf, (size_t)L * q_layer_bytes)) && !completes) {
+            bool any;
+            if (int rc2 = give_back_kept(&any)) return rc2;
+            if (any) {
+                if (two) BP_HIP(hipStreamWaitEvent(stream, ev_misc, 0));
+                rc = BP_OK;
+            }
+        }
+        if (!rc && !qbuf) {
             qbuf = (char*)pend_pool.back();
             pend_pool.pop_back();
-        } else if ((rc = dev_alloc((void**)&qbuf, (size_t)L * q_layer_bytes))) {
+        } else if (rc) {
             if (!completes) return rc;
             qbuf = nullptr;             // no room for the one buffer more: multiply along the way
             defer = false;

@@ -231,6 +231,33 @@ def test_kept_groups_give_the_bits_of_given_groups(n_micro, n_chunks, layers):
         _assert_same(a, b, "kept")
 
 
+def test_kept_groups_give_way_when_memory_is_short():
+    """With room on the device for a few stashes only, kept groups multiply at once and hand over theirs: nothing
+    fails that went through without keeping, and the bits stay."""
+    import torch
+    e = _EarlyReads(n_micro=26, wgrad_group=0, forward_ahead=1, n_chunks=1, layers=2)
+    peaks, results = [], []
+    for room in (None, 8):                          # stashes with their buffers
+        with e.stage() as g:
+            torch.cuda.synchronize()
+            torch.cuda.empty_cache()
+            one = g.bp.bp_stage_stash_bytes(g.h) + 2 * e.cfg.T * (e.cfg.F + 5 * e.cfg.hidden) * 2
+            # inputs and outputs of the iteration, left in torch's cache
+            io = [hz.empty_like_dev((e.cfg.microbatch, e.cfg.seq, e.cfg.hidden), e.cfg.dtype) for _ in range(6 * e.cfg.n_micro)]
+            hog = None
+            if room:
+                hog = torch.empty(torch.cuda.mem_get_info()[0] - room * one, dtype=torch.uint8, device="cuda")
+            del io
+            keep = e.iteration(g, 0)
+            peaks.append(g.bp.bp_stage_held_bytes(g.h)["peak_total"])
+            results.append({k: g.grad(*k) for k in e.names})
+            del hog, keep
+            torch.cuda.empty_cache()
+    assert peaks[1] < peaks[0], peaks               # kept groups did give way
+    ref, got = results
+    _assert_same(got, ref, "short of memory")
+
+
 @pytest.mark.parametrize("stash_recompute", [0, 1])
 def test_parameters_set_while_gradients_are_still_computed(stash_recompute):
     """Parameters set right after the first read: the gradients still to come are those of the old ones (the
