@@ -142,6 +142,7 @@ hipError_t launch_attn_bwd_generic(int dtype, const AttnArgs& a, hipStream_t str
 hipError_t launch_loss(int dtype, size_t n, const void* z, const void* target, float scale,
                        void* grad, float* loss_out, float* ws, hipStream_t stream);
 
+hipError_t launch_read_small(const float* src, float* dst, int n, hipStream_t stream);   // dst: pinned host memory
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t stream);
 hipError_t launch_add_f32(float* dst, const float* src, size_t n, hipStream_t stream);   // dst += src
 // host fp32 staging (already on device as fp32) -> storage dtype

@@ -433,6 +433,22 @@ int Stage::set_param(int chunk, int layer, int id, const float* host, size_t n) 
     return BP_OK;
 }
 
+// The device's view of a host range that is pinned from its first to its last byte, else null.
+static float* pinned_range(void* host, size_t bytes) {
+    hipPointerAttribute_t first, last;
+    if ((uintptr_t)host % sizeof(float) == 0 && hipPointerGetAttributes(&first, host) == hipSuccess &&
+        first.type == hipMemoryTypeHost && first.devicePointer &&
+        hipPointerGetAttributes(&last, (char*)host + bytes - 1) == hipSuccess && last.type == hipMemoryTypeHost &&
+        (char*)last.devicePointer == (char*)first.devicePointer + bytes - 1)
+        return (float*)first.devicePointer;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+// Up to this size the runtime copies with a kernel of its own, which finds no room beside GEMM blocks that fill a CU;
+// above, over the DMA engines (8.6 us instead of 11.7).  Reads beside the last weight gradients, H 2048, two layers: 28.9 -> 28.1 ms.
+constexpr size_t kSmallRead = 16384;
+
 int Stage::get_grad(int chunk, int layer, int id, float* host, size_t n) {
     int rc = check_tensor(chunk, layer, id, n);
     if (rc) return rc;
@@ -457,8 +473,12 @@ int Stage::get_grad(int chunk, int layer, int id, float* host, size_t n) {
         memset(host, 0, n * sizeof(float));
         return BP_OK;
     }
-    hipError_t e = hipMemcpyAsync(host, grad(0, chunk, layer, id), n * sizeof(float),
-                                  hipMemcpyDeviceToHost, stream);
+    const size_t bytes = n * sizeof(float);
+    hipError_t e;
+    if (float* mapped = bytes <= kSmallRead ? pinned_range(host, bytes) : nullptr)
+        e = launch_read_small(grad(0, chunk, layer, id), mapped, (int)n, stream);
+    else
+        e = hipMemcpyAsync(host, grad(0, chunk, layer, id), bytes, hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return fail(BP_EHIP, "get_grad: %s", hipGetErrorString(e));
     return BP_OK;

@@ -258,6 +258,29 @@ def test_kept_groups_give_way_when_memory_is_short():
     _assert_same(got, ref, "short of memory")
 
 
+@pytest.mark.parametrize("hidden,dtype", [(64, "f32"), (1024, "bf16"), (4096, "bf16"), (4104, "bf16")])
+def test_gradients_read_into_pinned_memory(hidden, dtype):
+    """Small tensors are written to pinned host memory by a kernel, others copied: the same values as in pageable
+    memory, at any offset of whole floats, with nothing around them touched (sizes on both sides of 16 KB)."""
+    import torch
+    import paper_2410_19367_amd as bp
+    cfg = si.scaled(si.CONFIGS[1], name="pinned", layers=1, hidden=hidden, heads=1 if hidden == 64 else hidden // 8 if hidden == 4104 else 8, seq=16,
+                    microbatch=1, n_micro=1, dtype=dtype)
+    vectors = [n for n in si.PARAM_NAMES if n not in ("wqkv", "wo", "w1", "w2")]
+    with hz.GpuStage(cfg) as g:
+        g.forward(0, 0, hz.to_dev(si.make_activation(cfg, "act_in", 0, 0), cfg.dtype))
+        g.backward(0, 0, hz.to_dev(si.make_activation(cfg, "grad_out", 0, 0), cfg.dtype))
+        for n in vectors:
+            ref = g.grad(0, 0, n).ravel()
+            for off in (0, 1, 7):
+                buf = torch.full((ref.size + 16,), 7.0, pin_memory=True)
+                rc = bp.lib().bp_stage_get_grad(g.h, 0, 0, bp.TENSOR_IDS[n], buf.data_ptr() + 4 * off, ref.size)
+                assert rc == bp.BP_OK
+                got = buf.numpy()
+                assert np.array_equal(got[off:off + ref.size], ref), (n, off)
+                assert np.all(got[:off] == 7) and np.all(got[off + ref.size:] == 7), (n, off)
+
+
 @pytest.mark.parametrize("stash_recompute", [0, 1])
 def test_parameters_set_while_gradients_are_still_computed(stash_recompute):
     """Parameters set right after the first read: the gradients still to come are those of the old ones (the
