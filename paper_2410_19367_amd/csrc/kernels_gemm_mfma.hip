@@ -17,8 +17,8 @@
 // (further down) loads slices straight into LDS, for any shape with 16-byte rows, and carries the
 // fused epilogues, split-K and multi-segment contractions.  Slices land in LDS while earlier ones feed the MFMAs,
 // one barrier per slice.  LDS stages: two in gemm_mfma_kernel; in gemm_dma_kernel three of A and two of B in the
-// large tiles (256 x 256 and 256 x 192) of the forward / data-gradient form, three in its 128 x 128 and
-// 128 x 64 tiles and in the 64 x 64 tiles of either form, a ring of five half-slices in the 256 x 256 tiles of the
+// large tiles (256 x 256 and 256 x 192) of the forward / data-gradient form and in its 128 x 128 tiles where two blocks
+// share a CU, three in its other 128 x 128 and 128 x 64 tiles and in the 64 x 64 tiles of either form, a ring of five half-slices in the 256 x 256 tiles of the
 // weight-gradient form, two in every other.
 #include <cstdlib>
 #include <type_traits>
@@ -1106,6 +1106,21 @@ bool gemm_can_fuse_epilogue(int dtype, const GemmArgs& g) {
     return false;
 }
 
+// Forward / data-gradient form on 128 x 128 tiles.  More blocks than CUs: the stages of the large tiles, three of A and
+// two of B (80 KB), so that two blocks share a CU; each hides the other's first loads, barriers and epilogue, and
+// a partly filled second round is not waited for: 1998 x 2304 x 768 20.5 -> 16.2 us, 1000 x 6400 x 1600 32.6 -> 27.1 us,
+// 6144 x 1024 x 4096 59.6 -> 53.3 us.  At most one block per CU: three stages of both (96 KB), 2 - 6 % faster there
+// (2048^3 19.7 / 20.1 us, 1024 x 3072 x 1024 11.1 / 11.8 us; two stages of B everywhere cost stages with 256 such blocks
+// 2.8 %).  Four waves of 64 x 64 in place of eight are slower with either (2048^3 23.8, 1998 x 2304 x 768 18.3 us with two
+// blocks per CU).  Where a long K sends 257 .. 512 tiles to K slices of larger tiles, this kernel is up to 15 % faster with
+// operands that the caches hold (2048 x 2560 x 7680 104 / 93 us, 1024 x 5120 x 20480 348 / 300), but a stage with such
+// products 5 % slower, whose operands come from memory; the same for GELU epilogues on 320 large tiles (3.5 %).
+static hipError_t launch_nt128(const GemmArgs& g, hipStream_t s, int slices = 1, int n_full = -1) {
+    const long blocks = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * slices;
+    if (blocks > cu_count()) return launch_dma<NT, true, 128, 128, 2, 4, 2, 64, true>(g, s, slices, n_full);
+    return launch_dma<NT, true, 128, 128, 2, 4, 3, 64, true>(g, s, slices, n_full);
+}
+
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
     const bool dma = dma_path_ok(g);
@@ -1224,7 +1239,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     const bool deep = g.K % 128 == 0 || (g.K % BK != 0 && g.K > 512);   // slices of 128 along K
     const bool small_fill = t128 >= most && (k_total <= 4096 || (nt && k_total <= 8192 && fill(t128) >= 0.95));
     if (small_fill && !wgrad) {
-        if (nt) return launch_dma<NT, true, 128, 128, 2, 4, 3, 64, true>(g, s);
+        if (nt) return launch_nt128(g, s);
         if (deep) return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2, 128>(g, s);
         return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2>(g, s);
     }
@@ -1240,7 +1255,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     // Small outputs (128 x 128 tiles on fewer than three quarters of the CUs) with a long K: the same split, on the small
     // tiles (slices at least 1024 deep: below that the second kernel costs what the split gains)
     if (slices > 1) {
-        if (nt) return launch_dma<NT, true, 128, 128, 2, 4, 3, 64, true>(g, s, slices, 0);
+        if (nt) return launch_nt128(g, s, slices, 0);
         if (deep) return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2, 128>(g, s, slices, 0);
         return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2>(g, s, slices, 0);
     }
@@ -1249,7 +1264,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     // stages of 64 along K (96 KB), so that a slice has two barriers to land (against two stages of
     // 128: 2048^3 20.7 us against 21.9 us, 2048 x 2048 x 8192 63.7 us against 67.9 us).  The other forms: slices of 128 along K (two stages of 64 KB),
     // which halve the number of barriers per MFMA.
-    if (nt) return launch_dma<NT, true, 128, 128, 2, 4, 3, 64, true>(g, s);
+    if (nt) return launch_nt128(g, s);
     if (deep) return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2, 128>(g, s);
     return launch_dma<TN | OTHER, true, 128, 128, 2, 4, 2>(g, s);
 }

@@ -102,6 +102,17 @@ def test_gemm_small_tiles(form, M, N, K):
     test_gemm_forms(M, N, K, form, "bf16")
 
 
+# 128 x 128 tiles of the forward form with two blocks per CU (more than 256 tiles on 256 CUs) and, at the limit, one: fewer
+# slices than LDS stages, every phase of the 3 x 2 stage cycle at the end, edge tiles and K tails
+@pytest.mark.parametrize("form,M,N,K", [
+    ("dgrad", 2176, 2048, 64), ("dgrad", 2176, 2048, 128), ("dgrad", 2176, 2048, 192), ("dgrad", 2176, 2048, 448), ("dgrad", 2048, 2048, 128),
+    ("dgrad", 2048, 4096, 320), ("dgrad", 2050, 4096, 72), ("dgrad", 1998, 2304, 8), ("dgrad", 1998, 2304, 200), ("dgrad", 1000, 4808, 264),
+    ("fwd", 1998, 2304, 136),
+])
+def test_gemm_two_blocks_per_cu(form, M, N, K):
+    test_gemm_forms(M, N, K, form, "bf16")
+
+
 # fp32 kernel: both tile widths, one element past a tile, the shortest K, K tails of four, unaligned rows
 # (the generic kernel); 1e-5 relative to the largest element bounds fp32 sums of this length
 @pytest.mark.parametrize("form,M,N,K", [
