@@ -116,8 +116,8 @@ __device__ __forceinline__ void attn_bwd_dq_row(const AttnArgs& a, float scale, 
     }
 }
 
-// dk and dv of one key (needs delta from the dq kernel)
-template <typename T>
+// dk and dv of one key.  Needs delta from the dq kernel, or with OWN_DELTA takes it from ctx and dctx.
+template <typename T, bool OWN_DELTA = false>
 __device__ __forceinline__ void attn_bwd_dkv_row(const AttnArgs& a, float scale, int j, int h, int b, float* smem) {
     __syncthreads();              // the row before is done with the LDS
     float* ps = smem;             // [S]
@@ -131,6 +131,7 @@ __device__ __forceinline__ void attn_bwd_dkv_row(const AttnArgs& a, float scale,
     const T* krow = qkv + tok * ld + H + h * a.d;
     const T* vrow = krow + H;
     const T* dobase = (const T*)a.dctx + ((size_t)b * a.S) * H + h * a.d;
+    const T* obase = (const T*)a.ctx + ((size_t)b * a.S) * H + h * a.d;
     T* dk = (T*)a.dqkv + tok * ld + H + h * a.d;
     T* dv = dk + H;
     const int klen = a.causal ? a.S : (a.lens ? a.lens[b] : a.S);
@@ -152,14 +153,16 @@ __device__ __forceinline__ void attn_bwd_dkv_row(const AttnArgs& a, float scale,
     for (int i = i0 + threadIdx.x; i < a.S; i += blockDim.x) {
         const T* qr = qbase + (size_t)i * ld;
         const T* dor = dobase + (size_t)i * H;
-        float s = 0.f, dp = 0.f;
+        float s = 0.f, dp = 0.f, dl = 0.f;
         for (int c = 0; c < a.d; ++c) {
             s += to_float<T>(qr[c]) * ks[c];
             dp += to_float<T>(dor[c]) * vs[c];
+            if (OWN_DELTA) dl += to_float<T>(dor[c]) * to_float<T>(obase[(size_t)i * H + c]);
         }
+        if (!OWN_DELTA) dl = delta[i];
         const float p = __expf(s * scale - lse[i]);
         ps[i] = p;
-        dss[i] = p * (dp - delta[i]);
+        dss[i] = p * (dp - dl);
     }
     __syncthreads();
     for (int c = threadIdx.x; c < a.d; c += blockDim.x) {

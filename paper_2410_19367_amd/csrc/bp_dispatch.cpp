@@ -59,10 +59,21 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
 //   narrower: 16 of 24, backward, S 32 10.2 / 11.4, S 48 13.7 / 11.8; 2 of 24, forward, S 24 4.3 / 4.5, S 32 4.6 / 4.1;
 //   bf16 backward: 16 of 64, S 16 9.0 / 9.2, 64 of 64 10.4 / 9.3; 2 of 128, S 48 15.6 / 16.8; widths above 64 without a kernel
 //     of their own spill registers: 1 of 80, S 76 16.6 / 24.5;
+//   backward where dQ and dK/dV share a launch:
+//     fp32, d 24 always (S 16 7.5 / 6.5, S 48 13.8 / 7.0); d 64 8 heads, S 32 (8192) 9.8 / 10.7, 4 heads, S 48 (9216) 12.6 / 11.1,
+//       2 of 40, S 77 (11858) 15.8 / 16.4, 2 of 64, S 150 (45000) 31.5 / 23.8; d 96 4 heads, S 32 11.0 / 14.7, 16 heads, S 63 22.6 /
+//       16.1; d 128 4 heads, S 90 26.2 / 33.4, d 104 S 128 32.7 / 31.9;
+//     bf16, d 64 16 heads, S 16 8.8 / 6.2, 4 heads, S 4 7.6 / 5.9; d 96 S 12 9.6 / 8.6; d 128 S 40 13.4 / 13.4, S 16 11.2 / 12.9;
+//       d 112 S 30 12.2 / 16.1, S 60 18.0 / 16.8; d 80 S 76 16.4 / 18.0, S 100 25.8 / 16.8;
 //   bf16 forward: 16 of 64, S 4 4.2 / 4.1 (causal 4.2 / 4.6); 16 of 128, S 12 5.4 / 5.5 (causal 5.4 / 6.1).
 // (bf16 at multiples of 64 has always been on the matrix cores.)
 static bool rows_are_faster(int dtype, const AttnArgs& a, bool bwd) {
     const long rows = (long)a.B * a.heads * a.S, work = rows * a.S;
+    if (dtype == F32 && bwd && attn_bwd_f32_one_launch(a)) {
+        if (a.d <= 32) return false;
+        if (a.d <= 64) return work <= (a.S <= 64 ? 8192 : 12000);
+        return a.d <= 96 ? a.S <= 44 && work <= 40000 : a.S <= 112 && work <= 60000;
+    }
     if (dtype == F32) {
         if (a.d > 32 && rows > 3072) return work <= 40000;
         if (a.d > 32 && rows <= 512) return work <= (a.d > 64 ? 120000 : 80000);
@@ -70,6 +81,10 @@ static bool rows_are_faster(int dtype, const AttnArgs& a, bool bwd) {
         return a.S <= (bwd ? 48 : 24) && work <= 20000;
     }
     if (a.S % 64 == 0) return false;
+    if (bwd && attn_bwd_mfma_one_launch(a)) {
+        if (a.d <= 64 || a.d == 96) return false;
+        return a.d == 128 ? a.S <= 40 && work <= 16384 : (a.S <= 52 || (a.S > 64 && a.S <= 80)) && work <= 40000;
+    }
     if (bwd && a.d > 64 && a.d != 96) return a.d == 128 ? a.S <= 48 && work <= 16384 : work <= 40000;
     if (bwd) return a.S <= (a.d == 96 ? 24 : 16) && work <= 8192;
     return a.d > 32 && a.d <= 64 ? a.S <= 4 && work <= 2048 : a.S <= 12 && work <= 4096;

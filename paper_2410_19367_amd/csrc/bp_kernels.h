@@ -131,9 +131,11 @@ hipError_t launch_attn_bwd(int dtype, const AttnArgs& a, hipStream_t stream);
 bool attn_mfma_supported(const AttnArgs& a);                       // bf16, head dim a multiple of 8 up to 128
 hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t stream);
 hipError_t launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t stream);
+bool attn_bwd_mfma_one_launch(const AttnArgs& a);       // dQ and dK/dV in one launch
 bool attn_f32_supported(const AttnArgs& a);                        // fp32, head dim a multiple of 8 up to 128
 hipError_t launch_attn_fwd_f32(const AttnArgs& a, hipStream_t stream);
 hipError_t launch_attn_bwd_f32(const AttnArgs& a, hipStream_t stream);
+bool attn_bwd_f32_one_launch(const AttnArgs& a);
 hipError_t launch_attn_fwd_generic(int dtype, const AttnArgs& a, hipStream_t stream);
 hipError_t launch_attn_bwd_generic(int dtype, const AttnArgs& a, hipStream_t stream);
 

@@ -1,6 +1,6 @@
 // Fused fp32 attention on the gfx950 matrix cores (v_mfma_f32_32x32x2_f32), the fp32 counterpart of the
-// bf16 kernels: forward with online softmax and the backward as two deterministic kernels (dQ; dK and
-// dV), for any sequence length and head widths that are multiples of 8 up to 128.
+// bf16 kernels: forward with online softmax and the backward in two deterministic parts (dQ; dK and
+// dV; one launch each or both in one), for any sequence length and head widths that are multiples of 8 up to 128.
 //
 // Bound: the fp32 matrix rate (an eighth of the bf16 one), so the kernels are kept simple: four waves,
 // 32 queries (keys in dK/dV) x one half of every 64-row tile each, tiles through two LDS stages.
@@ -10,7 +10,7 @@
 // Register v of the accumulator then is, as it stands, the B operand of the two-deep MFMA that
 // contracts over rows {v, lower half} and {v, upper half}; its A operand (V^T, K^T, dO^T, Q^T) is one
 // float per lane of the same row-major tile.
-// Measured (forward / backward): B 2, S 512, 12 heads of 64, causal 26 / 81 us against 163 / 814 us for the
+// Measured (forward / backward): B 2, S 512, 12 heads of 64, causal 26 / 68 us against 163 / 814 us for the
 // one-row-per-block kernels; without the mask 62 / 39 TFLOP/s.  Heads wider than 64 leave one wave per SIMD (dK/dV
 // at 128 spills 18 registers): S 300, 16 heads of 128, without the mask 34.5 / 107 us (rows 135 / 740 us), of 96
 // 27.7 / 80 us.
@@ -145,9 +145,9 @@ __device__ __forceinline__ f32x16 zero16() {
     return z;
 }
 // Query (key) block of this thread block: the most expensive causal blocks start first
-__device__ __forceinline__ void f32_block(const AttnArgs& a, bool last_is_heavy, int& blk, int& head, int& b) {
-    const int nblk = (a.S + 63) / 64, per = nblk * a.heads, lin = blockIdx.x % per;
-    b = blockIdx.x / per;
+__device__ __forceinline__ void f32_block(const AttnArgs& a, int bid, bool last_is_heavy, int& blk, int& head, int& b) {
+    const int nblk = (a.S + 63) / 64, per = nblk * a.heads, lin = bid % per;
+    b = bid / per;
     head = lin % a.heads;
     blk = a.causal && last_is_heavy ? nblk - 1 - lin / a.heads : lin / a.heads;
 }
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int qg = wave >> 1, kh = wave & 1;
     int qblk, head, b;
-    f32_block(a, true, qblk, head, b);
+    f32_block(a, blockIdx.x, true, qblk, head, b);
     const int dr = a.d, H = a.heads * dr, ld = 3 * H, S = a.S;
     const float* qkv = (const float*)a.qkv + (size_t)b * S * ld + head * dr;
     const int q_wave = qblk * 64 + qg * 32, q_lane = q_wave + (lane & 31);
@@ -271,15 +271,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(Attn
 
 // dQ, and delta[q] = sum_d dO[q][d] O[q][d] for the dK/dV kernel
 template <int D, int DC>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(AttnArgs a, float scale) {
-    attn_args_now(a, scale);
+__device__ __forceinline__ void attn_bwd_dq_f32_block(const AttnArgs& a, float scale, int bid, char* smem) {
     constexpr int KS = DC / 8, DT = DC / 32, TILE = 64 * D * 4, STAGE = 2 * TILE;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int qg = wave >> 1, kh = wave & 1;
     int qblk, head, b;
-    f32_block(a, true, qblk, head, b);
+    f32_block(a, bid, true, qblk, head, b);
     const int dr = a.d, H = a.heads * dr, ld = 3 * H, S = a.S;
     const float* qkv = (const float*)a.qkv + (size_t)b * S * ld + head * dr;
     const int q_wave = qblk * 64 + qg * 32, q_lane = q_wave + (lane & 31), q_src = min(q_lane, S - 1);
@@ -366,16 +364,14 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(A
 }
 
 // dK and dV: 32 keys per wave, one half of every 64-query tile of Q and dO that streams by
-template <int D, int DC>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(AttnArgs a, float scale) {
-    attn_args_now(a, scale);
+template <int D, int DC, bool ALONE>
+__device__ __forceinline__ void attn_bwd_dkv_f32_block(const AttnArgs& a, float scale, int bid, char* smem) {
     constexpr int KS = DC / 8, DT = DC / 32, TILE = 64 * D * 4, STAGE = 2 * TILE + 512;   // Q, dO, lse[64], delta[64]
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kg = wave >> 1, qh = wave & 1;
     int kblk, head, b;
-    f32_block(a, false, kblk, head, b);
+    f32_block(a, bid, false, kblk, head, b);
     const int dr = a.d, H = a.heads * dr, ld = 3 * H, S = a.S;
     const float* qkv = (const float*)a.qkv + (size_t)b * S * ld + head * dr;
     const float* dobase = (const float*)a.dctx + (size_t)b * S * H + head * dr;
@@ -411,17 +407,62 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(
         if (wave == 0)
             __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(lse + q),
                                              (void __attribute__((address_space(3)))*)(st + 2 * TILE), 4, 0, 0);
-        else if (wave == 1)
+        else if (ALONE && wave == 1)
             __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(dlt + q),
                                              (void __attribute__((address_space(3)))*)(st + 2 * TILE + 256), 4, 0, 0);
     };
-    if (t0 < nt) request(t0);
+    // Beside the dQ blocks, which leave delta in memory too late for this launch, a block takes delta of a tile's rows
+    // from O and dO itself, four lanes to a row, in two halves that arrive under the products of the tile before.
+    constexpr int NO = DC / 32;
+    f32x4 o_row[ALONE ? 1 : NO], do_row[ALONE ? 1 : NO];
+    float delta_part = 0.f;
+    auto fetch_delta = [&](int t, int half) {
+        if constexpr (!ALONE) {
+            const size_t row = ((size_t)b * S + min(t * 64 + (int)(threadIdx.x >> 2), S - 1)) * H + head * dr;
+#pragma unroll
+            for (int j = 0; j < NO; ++j) {
+                const int col = 16 * (half * NO + j) + 4 * (threadIdx.x & 3);
+                o_row[j] = row_piece((const float*)a.ctx + row, col, dr);
+                do_row[j] = row_piece((const float*)a.dctx + row, col, dr);
+            }
+        }
+    };
+    auto fold_delta = [&]() {
+        if constexpr (!ALONE) {
+#pragma unroll
+            for (int j = 0; j < NO; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) delta_part += o_row[j][e] * do_row[j][e];
+        }
+    };
+    // (rows past the end of the last tile, and the tile past the last one, repeat the last row)
+    auto first_half = [&](int t) { fold_delta(); fetch_delta(t, 1); };
+    auto second_half = [&](int t) {
+        if constexpr (!ALONE) {
+            fold_delta();
+            delta_part += __shfl_xor(delta_part, 1, 64);
+            delta_part += __shfl_xor(delta_part, 2, 64);
+            if ((threadIdx.x & 3) == 0) ((float*)(smem + (t & 1) * STAGE + 2 * TILE))[64 + (threadIdx.x >> 2)] = delta_part;
+            delta_part = 0.f;
+        }
+    };
+    if (t0 < nt) {
+        request(t0);
+        fetch_delta(t0, 0);
+        first_half(t0);
+        second_half(t0);
+    }
     for (int t = t0; t < nt; ++t) {
         BP_WAIT_VMCNT(0);
         __syncthreads();
         if (t + 1 < nt) request(t + 1);
+        fetch_delta(t + 1, 0);
         const int qw = t * 64 + 32 * qh;
-        if ((a.causal && qw + 31 < k_wave) || qw >= S) continue;
+        if ((a.causal && qw + 31 < k_wave) || qw >= S) {
+            first_half(t + 1);
+            second_half(t + 1);
+            continue;
+        }
         const char* sq = smem + (t & 1) * STAGE;
         const char* sdo = sq + TILE;
         const float* s_lse = (const float*)(sq + 2 * TILE) + 32 * qh;
@@ -440,11 +481,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(
             sacc[v] = p;
             dp[v] = p * (dp[v] - s_dlt[qi]);            // dS
         }
+        first_half(t + 1);
         contract<D, DC>(sdo, 32 * qh, lane, sacc, dv);
         contract<D, DC>(sq, 32 * qh, lane, dp, dk);
+        second_half(t + 1);
     }
     if (a.causal && any_wave(by_rows, smem)) {
-        for (int k = kblk * 64; k < min(kblk * 64 + 64, S); ++k) attn_bwd_dkv_row<float>(a, scale, k, head, b, (float*)smem);
+        for (int k = kblk * 64; k < min(kblk * 64 + 64, S); ++k) attn_bwd_dkv_row<float, !ALONE>(a, scale, k, head, b, (float*)smem);
         return;
     }
     __syncthreads();
@@ -477,11 +520,41 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(
         }
 }
 
+template <int D, int DC>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(AttnArgs a, float scale) {
+    attn_args_now(a, scale);
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    attn_bwd_dq_f32_block<D, DC>(a, scale, blockIdx.x, smem);
+}
+template <int D, int DC>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_dkv_f32_kernel(AttnArgs a, float scale) {
+    attn_args_now(a, scale);
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    attn_bwd_dkv_f32_block<D, DC, true>(a, scale, blockIdx.x, smem);
+}
+// Both in one launch (attn_bwd_f32_one_launch): the first half of the blocks, which have more to do, dK and dV, the others dQ.
+template <int D, int DC>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_f32_kernel(AttnArgs a, float scale) {
+    attn_args_now(a, scale);
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int n = gridDim.x / 2, bid = blockIdx.x;
+    if (bid < n) attn_bwd_dkv_f32_block<D, DC, false>(a, scale, bid, smem);
+    else attn_bwd_dq_f32_block<D, DC>(a, scale, bid - n, smem);
+}
+
 bool attn_f32_supported(const AttnArgs& a) {
     auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
     // (a tile's rows are addressed with 32-bit byte offsets)
     if (a.d % 8 || a.d < 8 || a.d > 128 || a.S < 1 || (long)a.heads * a.d > 1 << 20) return false;
     return al16(a.qkv) && al16(a.ctx) && (!a.dctx || al16(a.dctx)) && (!a.dqkv || al16(a.dqkv));
+}
+
+// dQ and dK/dV side by side in one launch while the blocks of both find room at once, two per CU (one for heads wider than
+// 64).  n blocks of each on 256 CUs, two launches / one, us: d 64 n 40 52.6 / 36.0, 96 78.8 / 55.5, 192 79.4 / 68.4, 220
+// 104 / 110, 256 79.2 / 80.1; d 40 192 76.8 / 70.1; d 24 64 28.0 / 16.2; d 96 128 120 / 67; d 128 64 151 / 90, 128 152 / 91.
+bool attn_bwd_f32_one_launch(const AttnArgs& a) {
+    const long n = (long)((a.S + 63) / 64) * a.heads * a.B, cu = cu_count();
+    return a.d <= 64 ? 4 * n <= 3 * cu : 2 * n <= cu;
 }
 
 template <int D, int DC>
@@ -498,10 +571,14 @@ static hipError_t launch_f32_attn(const AttnArgs& a, bool bwd, hipStream_t s) {
             e = hipFuncSetAttribute((const void*)(attn_bwd_dq_f32_kernel<D, DC>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
         if (e == hipSuccess)
             e = hipFuncSetAttribute((const void*)(attn_bwd_dkv_f32_kernel<D, DC>), hipFuncAttributeMaxDynamicSharedMemorySize, smem2);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute((const void*)(attn_bwd_f32_kernel<D, DC>), hipFuncAttributeMaxDynamicSharedMemorySize, smem2);
         if (e != hipSuccess) return e;
         set.store(true, std::memory_order_release);
     }
-    if (bwd) {
+    if (bwd && attn_bwd_f32_one_launch(a)) {
+        hipLaunchKernelGGL((attn_bwd_f32_kernel<D, DC>), dim3(2 * grid.x), block, smem2, s, a, scale);
+    } else if (bwd) {
         hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<D, DC>), grid, block, smem, s, a, scale);
         hipLaunchKernelGGL((attn_bwd_dkv_f32_kernel<D, DC>), grid, block, smem2, s, a, scale);
     } else {

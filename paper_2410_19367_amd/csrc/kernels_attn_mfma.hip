@@ -1,6 +1,6 @@
 // Fused attention on the gfx950 matrix cores (bf16 inputs, fp32 softmax and accumulation; P and dS enter their
 // second product in bf16 where the sequence length is a multiple of 64, else in fp32):
-// forward with online softmax, and the backward as two deterministic kernels (dQ; dK and dV).
+// forward with online softmax, and the backward in two deterministic parts (dQ; dK and dV), one launch each or both in one.
 //
 // All three kernels stream [64 rows][D] tiles of the packed qkv / dctx tensors through LDS with
 // direct global->LDS loads and never materialise an S x S matrix.  Scores are produced
@@ -215,18 +215,18 @@ __device__ __forceinline__ bool rows_finite(const char* tile, int row0, int lane
 //   ORDER_ALL: positions run over all batch entries together, else over one entry after the other, which keeps fewer
 //     heads' keys and values in the L2s at a time but pairs heavy blocks of one entry with heavy ones of another.
 enum { ORDER_FOLDED = 1, ORDER_ALL = 2 };
-__device__ __forceinline__ void block_coords(int nblk, int heads, int batch, bool causal, bool heavy_is_last_index,
+__device__ __forceinline__ void block_coords(int bid, int nblk, int heads, int batch, bool causal, bool heavy_is_last_index,
                                             int order, int& blk, int& head, int& b) {
     const int per = nblk * heads;             // blocks per batch entry
     int i;                                    // position in the work-sorted order
     if (causal && (order & ORDER_ALL)) {
-        i = blockIdx.x / (heads * batch);
-        const int r = blockIdx.x - i * (heads * batch);
+        i = bid / (heads * batch);
+        const int r = bid - i * (heads * batch);
         b = r / heads;
         head = r - b * heads;
     } else {
-        const int lin = blockIdx.x % per;
-        b = blockIdx.x / per;
+        const int lin = bid % per;
+        b = bid / per;
         i = lin / heads;
         head = lin % heads;
     }
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     const int tj = sub >> 1, kh = sub & 1;
     const int h = lane >> 5;
     int qblk, head, b;
-    block_coords((a.S + QB - 1) / QB, a.heads, a.B, a.causal != 0, true, order, qblk, head, b);
+    block_coords(blockIdx.x, (a.S + QB - 1) / QB, a.heads, a.B, a.causal != 0, true, order, qblk, head, b);
     // real head dimension: the tile width (no padding, every guard below folds away), a fixed narrower
     // width (the guards fold to constants), or with DR = 0 whatever the call says
     constexpr bool PAD = DR != D;
@@ -459,23 +459,21 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
 //   dQ^T (D x 32) += K^T dS^T         (K tile read plainly for S^T and transposed for dQ^T)
 // The two halves' partial dQ^T are added through LDS at the end.
 // =====================================================================================
-template <int D, int DR, bool RAG, bool WIDE = false>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, float scale, int order) {
+template <int D, int DR, bool RAG, bool WIDE>
+__device__ __forceinline__ void attn_bwd_dq_block(const AttnArgs& a, float scale, int order, int bid, char* smem) {
     static_assert(!WIDE || !RAG, "128 queries: whole tiles");
-    attn_args_now(a, scale, order);
     constexpr int QB = WIDE ? 128 : 64;                 // queries of a block
     constexpr int NW = 4, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE;
     // dP - delta: -delta is what the accumulators of dP start from, where 16 registers are left for it
     constexpr bool DELTA_FIRST = !(RAG && D == 128);
-    extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int qg = WIDE ? wave : wave >> 1, kh0 = WIDE ? 0 : wave & 1;
     const int h = lane >> 5;
     int qblk, head, b;
-    block_coords((a.S + QB - 1) / QB, a.heads, a.B, a.causal != 0, true, order, qblk, head, b);
+    block_coords(bid, (a.S + QB - 1) / QB, a.heads, a.B, a.causal != 0, true, order, qblk, head, b);
     // real head dimension: the tile width (no padding, every guard below folds away), a fixed narrower
     // width (the guards fold to constants), or with DR = 0 whatever the call says
     constexpr bool PAD = DR != D;
@@ -613,21 +611,19 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, fl
 //   dV^T (D x 32 keys) += dO^T P,   dK^T (D x 32 keys) += Q^T dS
 // The two query halves' partial sums are added through LDS at the end.
 // =====================================================================================
-template <int D, int DR, bool RAG, bool WIDE = false>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, float scale, int order) {
-    static_assert(!WIDE || !RAG, "128 keys: whole tiles");
-    attn_args_now(a, scale, order);
+template <int D, int DR, bool RAG, bool WIDE, bool ALONE>
+__device__ __forceinline__ void attn_bwd_dkv_block(const AttnArgs& a, float scale, int order, int bid, char* smem) {
+    static_assert(!WIDE || (!RAG && ALONE), "128 keys: whole tiles, a launch of their own");
     constexpr int KB = WIDE ? 128 : 64;                 // keys of a block
     constexpr int NW = 4, KS = D / 16, DT = D / 32;
     constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE + 512;   // Q, dO, then lse[64], delta[64]
-    extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kg = WIDE ? wave : wave >> 1, qh0 = WIDE ? 0 : wave & 1;
     const int h = lane >> 5;
     int kblk, head, b;
-    block_coords((a.S + KB - 1) / KB, a.heads, a.B, a.causal != 0, false, order, kblk, head, b);   // key block 0 is the heaviest
+    block_coords(bid, (a.S + KB - 1) / KB, a.heads, a.B, a.causal != 0, false, order, kblk, head, b);   // key block 0 is the heaviest
     // real head dimension: the tile width (no padding, every guard below folds away), a fixed narrower
     // width (the guards fold to constants), or with DR = 0 whatever the call says
     constexpr bool PAD = DR != D;
@@ -694,14 +690,47 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
     // They are fetched two tiles ahead, so that nothing waits for them but the wait at the top of a step.
     const float* stat = wave == 0 ? lse : dlt;
     const float stat_factor = wave == 0 ? -kLog2e : -1.f;
-    auto fetch_stat = [&](int t) { return wave < 2 && t < nt ? stat[RAG ? min(t * 64 + lane, a.S - 1) : t * 64 + lane] : 0.f; };
+    const int stats = ALONE ? 2 : 1;                     // waves with statistics to fetch
+    auto fetch_stat = [&](int t) { return wave < stats && t < nt ? stat[RAG ? min(t * 64 + lane, a.S - 1) : t * 64 + lane] : 0.f; };
     auto put_stat = [&](float v, char* st) {
-        if (wave < 2) ((float*)(st + 2 * TILE))[wave * 64 + lane] = v * stat_factor;
+        if (wave < stats) ((float*)(st + 2 * TILE))[wave * 64 + lane] = v * stat_factor;
     };
+    // Beside the dQ blocks, which leave delta in memory too late for this launch, a block takes delta of a tile's rows
+    // from O and dO itself, four lanes to a row; the loads are made when the tile is requested and used a step later.
+    constexpr int NO = D / 32;
+    bf16x8 o_row[ALONE ? 1 : NO], do_row[ALONE ? 1 : NO];
+    auto fetch_delta = [&](int t) {
+        if constexpr (!ALONE) {
+            if (t >= nt) return;
+            const size_t row = (size_t)b * a.S + (RAG ? min(t * 64 + (int)(threadIdx.x >> 2), a.S - 1) : t * 64 + (int)(threadIdx.x >> 2));
+            const bf16_t* ob = (const bf16_t*)a.ctx + row * H + head * dr;
+            const bf16_t* gb = (const bf16_t*)a.dctx + row * H + head * dr;
+#pragma unroll
+            for (int j = 0; j < NO; ++j) {
+                o_row[j] = load_frag(ob, 32 * j + 8 * (threadIdx.x & 3), dr);
+                do_row[j] = load_frag(gb, 32 * j + 8 * (threadIdx.x & 3), dr);
+            }
+        }
+    };
+    auto put_delta = [&](int t, char* st) {
+        if constexpr (!ALONE) {
+            if (t >= nt) return;
+            float d = 0.f;
+#pragma unroll
+            for (int j = 0; j < NO; ++j)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) d += (float)o_row[j][e] * (float)do_row[j][e];
+            d += __shfl_xor(d, 1, 64);
+            d += __shfl_xor(d, 2, 64);
+            if ((threadIdx.x & 3) == 0) ((float*)(st + 2 * TILE))[64 + (threadIdx.x >> 2)] = -d;
+        }
+    };
+    fetch_delta(t0);
     const float stat_first = fetch_stat(t0);
     float stat_next = fetch_stat(t0 + 1);
     load_stage(t0, smem + (t0 & 1) * STAGE);
     put_stat(stat_first, smem + (t0 & 1) * STAGE);
+    put_delta(t0, smem + (t0 & 1) * STAGE);
 
     for (int t = t0; t < nt; ++t) {
         const int q0 = t * 64;
@@ -711,6 +740,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             put_stat(stat_next, smem + ((t + 1) & 1) * STAGE);
             load_stage(t + 1, smem + ((t + 1) & 1) * STAGE);
             stat_next = fetch_stat(t + 2);
+            fetch_delta(t + 1);
         }
         if (WIDE && k_wave >= klen) continue;            // none of this wave's keys exists, or is attended
         const char* sq = smem + (t & 1) * STAGE;
@@ -777,9 +807,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
         }
         }
         }
+        put_delta(t + 1, smem + ((t + 1) & 1) * STAGE);
     }
     if (RAG && a.causal && any_wave(by_rows, smem)) {
-        for (int k = kblk * 64; k < min(kblk * 64 + 64, a.S); ++k) attn_bwd_dkv_row<bf16_t>(a, scale, k, head, b, (float*)smem);
+        for (int k = kblk * 64; k < min(kblk * 64 + 64, a.S); ++k) attn_bwd_dkv_row<bf16_t, !ALONE>(a, scale, k, head, b, (float*)smem);
         return;
     }
     if (WIDE && k_lane >= a.S) return;
@@ -817,6 +848,29 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, f
             pk.y = pack_bf16x2(v4[2], v4[3]);
             *reinterpret_cast<uint2*>(dv_out + t2 * 32 + 8 * g + 4 * h) = pk;
         }
+}
+
+template <int D, int DR, bool RAG, bool WIDE = false>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a, float scale, int order) {
+    attn_args_now(a, scale, order);
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    attn_bwd_dq_block<D, DR, RAG, WIDE>(a, scale, order, blockIdx.x, smem);
+}
+template <int D, int DR, bool RAG, bool WIDE = false>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(AttnArgs a, float scale, int order) {
+    attn_args_now(a, scale, order);
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    attn_bwd_dkv_block<D, DR, RAG, WIDE, true>(a, scale, order, blockIdx.x, smem);
+}
+
+// Both parts in one launch (attn_bwd_mfma_one_launch): the first half of the blocks, which have more to do, dK and dV, the others dQ.
+template <int D, int DR, bool RAG>
+__global__ __launch_bounds__(256, 2) void attn_bwd_mfma_kernel(AttnArgs a, float scale, int order) {
+    attn_args_now(a, scale, order);
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int n = gridDim.x / 2, bid = blockIdx.x;
+    if (bid < n) attn_bwd_dkv_block<D, DR, RAG, false, false>(a, scale, order, bid, smem);
+    else attn_bwd_dq_block<D, DR, RAG, false>(a, scale, order, bid - n, smem);
 }
 
 // ---- host side
@@ -945,8 +999,43 @@ static hipError_t launch_dkv(const AttnArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int D, int DR, bool RAG>
+static hipError_t launch_bwd_both(const AttnArgs& a, hipStream_t s) {
+    const float scale = 1.f / sqrtf((float)a.d);
+    const dim3 grid(2 * ((a.S + 63) / 64) * a.heads * a.B), block(256);
+    constexpr size_t stages = 2 * (2 * 64 * D * 2 + 512);
+    const size_t smem = std::max(stages, RAG && a.causal ? std::max(attn_row_lds_dq(a), attn_row_lds_dkv(a)) : 0);
+    static std::atomic<bool> set{false};   // several host threads may launch at once
+    if (!set.load(std::memory_order_acquire)) {
+        hipError_t e = set_smem(attn_bwd_mfma_kernel<D, DR, RAG>, std::max(stages, kMaxAttnRowLds));
+        if (e != hipSuccess) return e;
+        set.store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL((attn_bwd_mfma_kernel<D, DR, RAG>), grid, block, smem, s, a, scale,
+                       block_order(a, grid.x / 2, false, false));
+    return hipGetLastError();
+}
+
+// dQ and dK/dV side by side in one launch: while neither fills the chip by itself, they take the time of the longer one and
+// one launch is saved; delta is then computed twice, and the registers of both (198 - 234 at width 64) allow two blocks
+// per CU, where three of the split kernels' fit at lengths that are multiples of 64 (two at others).  n blocks of each on
+// 256 CUs, two launches / one, us:
+//   d up to 64: n 24 13.3 / 8.0, 128 20.6 / 14.0, 256 32.6 / 25.7 (causal), 384 27.2 / 24.8, 46.5 / 37.1 (causal), 512 76.3 / 79.7,
+//     causal 58.9 / 51.9, 35.4 / 33.2, 18.2 / 16.9, d 40 23.8 / 24.8, 1024 48.2 / 58.2, causal 58.1 / 60.7;
+//     other lengths: 72 22.7 / 15.1, 400 49.2 / 40.7, 504 32.8 / 32.0, 512 66.3 / 66.7, 576 44.6 / 36.4, 720 46.7 / 45.2;
+//   d 96: 256 28.3 / 23.0, 60.3 / 56.2 (S 1000), 512 49.7 / 50.6;
+//   other wide heads, which spill registers: d 128 96 47.2 / 44.5, 128 36.9 / 33.0, 192 44.8 / 54.7 (S 333), 256 59.2 / 68.0;
+//     d 112 96 47.3 / 39.3 (S 333).
+bool attn_bwd_mfma_one_launch(const AttnArgs& a) {
+    const long cu = cu_count(), n = (long)((a.S + 63) / 64) * a.heads * a.B;
+    if (a.d == 96) return n <= cu;
+    if (a.d > 64) return 2 * n <= cu;
+    return 2 * n <= 3 * cu || (a.S % 64 ? n <= 3 * cu : a.causal && a.d > 40 && n <= 2 * cu);
+}
+
 template <int D, int DR>
 static hipError_t launch_bwd_t(const AttnArgs& a, hipStream_t s) {
+    if (attn_bwd_mfma_one_launch(a)) return a.S % 64 ? launch_bwd_both<D, DR, true>(a, s) : launch_bwd_both<D, DR, false>(a, s);
     hipError_t e = a.S % 64 ? launch_dq<D, DR, true, false>(a, s) :
                    wide_rows(a, DQ) ? launch_dq<D, DR, false, true>(a, s) : launch_dq<D, DR, false, false>(a, s);
     if (e != hipSuccess) return e;

@@ -300,6 +300,25 @@ def test_attention_blocks_of_128_rows(B, S, heads, d, causal, lens):
     test_attention_fwd_bwd(B, S, heads, d, causal, lens, "bf16")
 
 
+# Backward: both sides of the limits up to which dQ and dK/dV share a launch (on 256 CUs: 384, 512 causal, 768 ragged
+# blocks of each up to head width 64, 256 of 96, 128 of other wide heads; fp32 256), and every head width on either side
+@pytest.mark.parametrize("B,S,heads,d,causal,lens,dtype", [
+    (6, 256, 16, 64, False, [1, 63, 64, 65, 200, 256], "bf16"), (5, 320, 16, 64, False, None, "bf16"), (4, 512, 16, 64, True, None, "bf16"),
+    (5, 448, 16, 64, True, None, "bf16"), (6, 100, 64, 64, False, [1, 33, 64, 65, 99, 100], "bf16"), (7, 100, 64, 40, False, None, "bf16"),
+    (6, 70, 64, 64, True, None, "bf16"), (7, 70, 64, 24, True, None, "bf16"), (2, 512, 16, 96, True, None, "bf16"), (2, 576, 16, 96, True, None, "bf16"),
+    (2, 256, 16, 128, True, None, "bf16"), (2, 320, 16, 128, True, None, "bf16"), (2, 200, 16, 112, False, [200, 129], "bf16"), (3, 200, 16, 112, True, None, "bf16"),
+    (2, 512, 16, 64, True, None, "f32"), (3, 400, 16, 64, False, [400, 1, 70], "f32"), (2, 512, 16, 24, True, None, "f32"), (3, 400, 16, 24, True, None, "f32"),
+    (2, 200, 16, 96, True, None, "f32"), (3, 200, 16, 128, False, None, "f32"),
+    # and between those and the kernels of one row per block
+    (1, 32, 8, 64, True, None, "f32"), (1, 33, 8, 64, True, None, "f32"), (1, 78, 2, 40, False, [70], "f32"), (1, 44, 2, 96, True, None, "f32"),
+    (1, 45, 2, 96, True, None, "f32"), (1, 112, 2, 128, True, None, "f32"), (1, 113, 2, 128, False, None, "f32"), (2, 3, 2, 24, True, None, "f32"),
+    (1, 2, 2, 64, True, None, "bf16"), (2, 3, 2, 96, False, [1, 3], "bf16"), (1, 40, 2, 128, True, None, "bf16"), (1, 41, 2, 128, True, None, "bf16"),
+    (1, 52, 2, 80, True, None, "bf16"), (1, 53, 2, 80, True, None, "bf16"), (1, 80, 2, 80, True, None, "bf16"), (1, 81, 2, 80, False, [64], "bf16"),
+])
+def test_attention_bwd_one_launch(B, S, heads, d, causal, lens, dtype):
+    test_attention_fwd_bwd(B, S, heads, d, causal, lens, dtype)
+
+
 # Both sides of the limits between the kernels of one row per block and the matrix-core ones
 @pytest.mark.parametrize("B,S,heads,d,causal,lens", [
     (2, 5, 2, 64, True, None), (8, 3, 32, 64, False, [1, 2, 3, 3, 1, 2, 3, 1]), (2, 12, 2, 128, True, None), (3, 13, 2, 128, False, None),
