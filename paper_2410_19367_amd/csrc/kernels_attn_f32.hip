@@ -12,8 +12,8 @@
 // float per lane of the same row-major tile.
 // Measured (forward / backward): B 2, S 512, 12 heads of 64, causal 26 / 68 us against 163 / 814 us for the
 // one-row-per-block kernels; without the mask 62 / 39 TFLOP/s.  Heads wider than 64 leave one wave per SIMD (dK/dV
-// at 128 spills 18 registers): S 300, 16 heads of 128, without the mask 34.5 / 107 us (rows 135 / 740 us), of 96
-// 27.7 / 80 us.
+// at 128 spills 18 registers): S 300, 16 heads of 128, without the mask 34.5 / 61 us (rows 135 / 740 us), of 96
+// 27.7 / 44 us (107 and 80 us in two launches).
 #include <atomic>
 
 #include "bp_kernels.h"
