@@ -90,7 +90,10 @@ struct LaneState {
     hipEvent_t ev_ready[5] = {};         // main -> side: dz, du, dy, dqkv, da of the current layer
     hipEvent_t ev_layer_done[2] = {};    // side -> main: workspaces of layer parity p are free again
     bool layer_done_pending[2] = {false, false};
-    hipEvent_t ev_misc = nullptr;        // side -> main: end of the previous backward call
+    // side -> main: recorded behind all side work so far where no layer event covers some of it (products along the way, of a
+    // flush, of a kept group).  Pending: the main stream has yet to wait.  Whoever waits clears the flag, so that the event is
+    // never taken for the end of side work that came after it.
+    hipEvent_t ev_misc = nullptr;
     bool call_done_pending = false;
     // lean mode: forward scratch for a, m, g; per contraction segment the recomputed a, m, g and
     // throw-away LayerNorm statistics for the side stream's weight-gradient GEMMs

@@ -1018,7 +1018,11 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             bool any;
             if (int rc2 = give_back_kept(&any)) return rc2;
             if (any) {
-                if (two) BP_HIP(hipStreamWaitEvent(stream, ev_misc, 0));
+                if (two) {      // waited for here: the next call must not take this event for the end of this one
+                    BP_HIP(hipStreamWaitEvent(stream, ev_misc, 0));
+                    call_done_pending = false;
+                    layer_done_pending[0] = layer_done_pending[1] = false;
+                }
                 rc = BP_OK;
             }
         }

@@ -1,0 +1,184 @@
+"""CPU: the host side of the stage library on a HIP runtime that records instead of computing (hip_recorder.cpp).  Every
+access of every launch is checked for order between the streams, for its bounds and for what it reads, and a gradient is
+the list of the contributions added into it: with device memory that runs short at a chosen call, and with launches
+that fail, nothing is read before it is written or overwritten while it is read, and nothing is counted twice or lost."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from paper_2410_19367_amd.binding import BP_BF16, BP_EHIP, BP_ENOMEM, BP_F32, BP_OK, TENSOR_IDS, bp_op, bp_opts
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+MATRICES = ("wqkv", "wo", "w1", "w2")
+
+
+@pytest.fixture(scope="module")
+def rec(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("recorder") / "stage_on_recorder.so")
+    csrc = os.path.join(ROOT, "paper_2410_19367_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-Wl,--no-undefined",
+                    "-fno-gnu-unique", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "hip_recorder.cpp"), os.path.join(csrc, "bp_stage.cpp"),
+                    os.path.join(csrc, "bp_schedule.cpp"), "-o", so], check=True)
+    lib = C.CDLL(so)
+    vp, ci, sz, u64 = C.c_void_p, C.c_int, C.c_size_t, C.c_uint64
+    lib.rec_errors.restype = C.c_char_p
+    lib.bp_last_error.restype = C.c_char_p
+    lib.rec_memory.argtypes = [sz]
+    lib.rec_used.restype = sz
+    lib.rec_fail.argtypes = [C.c_char_p, C.c_long]
+    lib.rec_launches.argtypes, lib.rec_launches.restype = [C.c_char_p], C.c_long
+    lib.rec_pin.argtypes = [vp, sz]
+    lib.rec_tensor.argtypes, lib.rec_tensor.restype = [sz, u64], vp
+    lib.rec_hash.argtypes, lib.rec_hash.restype = [vp, sz], u64
+    lib.rec_terms.argtypes = [C.c_uint32, C.POINTER(u64), ci]
+    lib.bp_stage_init_ex.argtypes = [C.POINTER(vp), ci, ci, ci, ci, ci, ci, C.POINTER(bp_opts)]
+    lib.bp_stage_stash_bytes.argtypes, lib.bp_stage_stash_bytes.restype = [vp], sz
+    lib.bp_stage_held_bytes.argtypes = [vp] + [C.POINTER(sz)] * 4
+    for name, args in (("destroy", []), ("set_param", [ci, ci, ci, vp, sz]), ("get_grad", [ci, ci, ci, vp, sz]),
+                       ("zero_grad", []), ("merge_directions", []), ("wait_forward", []), ("set_seqlens", [ci, vp]),
+                       ("forward", [ci, ci, vp, vp]), ("backward_dir", [ci, ci, vp, vp, ci])):
+        getattr(lib, "bp_stage_" + name).argtypes = [vp] + args
+    lib.bp_schedule_generate.argtypes = [ci, ci, ci, C.POINTER(bp_op), ci, C.POINTER(ci)]
+    lib.bp_run_schedule.argtypes = [vp, C.POINTER(bp_op), ci, ci, vp, vp, C.POINTER(C.c_float)]
+    return lib
+
+
+class Rec:
+    """One stage object on the recorder.  Widths are those of real stages (gradients worth reading early), as nothing
+    is computed or allocated."""
+
+    def __init__(self, lib, layers=1, hidden=1024, seq=1024, batch=1, n_chunks=1, dtype=BP_BF16, max_inflight=0, wgrad_group=0,
+                 stash_recompute=0, forward_ahead=0, causal=1):
+        self.lib, self.layers, self.n_chunks = lib, layers, n_chunks
+        lib.rec_reset()
+        self.cfg = si.scaled(si.CONFIGS[1], name="rec", layers=layers, hidden=hidden, heads=hidden // 64, seq=seq,
+                             microbatch=batch, n_chunks=n_chunks)
+        self.bytes = batch * seq * hidden * (2 if dtype == BP_BF16 else 4)
+        self.q = layers * 9 * self.bytes                    # output gradients of one waiting micro-batch
+        opts = bp_opts(n_chunks=n_chunks, dtype=dtype, max_inflight=max_inflight, wgrad_group=wgrad_group,
+                       stash_recompute=stash_recompute, forward_ahead=forward_ahead)
+        self.h = C.c_void_p()
+        self.ok(lib.bp_stage_init_ex(C.byref(self.h), layers, hidden, hidden // 64, seq, batch, causal, C.byref(opts)))
+        self.stash = lib.bp_stage_stash_bytes(self.h)
+        self.names = [(c, l, n) for c in range(n_chunks) for l in range(layers) for n in TENSOR_IDS]
+        self.io = {}
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, kind, *a):
+        self.lib.bp_stage_destroy(self.h)
+        if kind is None:
+            self.check()
+
+    def check(self):
+        assert self.lib.rec_errors() == b"", self.lib.rec_errors().decode()
+
+    def ok(self, rc):
+        assert rc == BP_OK, (rc, self.lib.bp_last_error())
+
+    def tensor(self, *key):     # inputs carry the seed of their name, outputs start unwritten; a new one for every key
+        if key not in self.io:
+            self.io[key] = self.lib.rec_tensor(self.bytes, 1000 + hash(key) % 10**9 if key[0] in ("x", "g") else 0)
+        return self.io[key]
+
+    def forward(self, mb, c=0, it=0):
+        return self.lib.bp_stage_forward(self.h, c, mb, self.tensor("x", it, c, mb), self.tensor("z", it, c, mb))
+
+    def backward(self, mb, c=0, it=0, dir=0):
+        return self.lib.bp_stage_backward_dir(self.h, c, mb, self.tensor("g", it, c, mb), self.tensor("dx", it, c, mb), dir)
+
+    def set_param(self, c, l, name, seed=1):
+        n = int(np.prod(si.param_shape(self.cfg, name)))
+        host = np.zeros(n, np.float32)
+        host[0] = seed
+        return self.lib.bp_stage_set_param(self.h, c, l, TENSOR_IDS[name], host.ctypes.data, n)
+
+    def terms(self, c, l, name, host=None):
+        """The contributions that were added into one gradient, in order."""
+        n = int(np.prod(si.param_shape(self.cfg, name)))
+        host = np.zeros(n, np.float32) if host is None else host
+        self.ok(self.lib.bp_stage_get_grad(self.h, c, l, TENSOR_IDS[name], host.ctypes.data, n))
+        out = (C.c_uint64 * 4096)()
+        return list(out[:self.lib.rec_terms(int(host[:1].view(np.uint32)[0]), out, 4096)])
+
+    def gradients(self):
+        return {k: self.terms(*k) for k in self.names}
+
+    def fill_up(self, spare):
+        """The rest of the device is taken by others, but for `spare` bytes."""
+        self.lib.rec_memory(spare)
+
+    def live(self):
+        out = [C.c_size_t() for _ in range(4)]
+        self.ok(self.lib.bp_stage_held_bytes(self.h, *[C.byref(o) for o in out]))
+        return [o.value for o in out]
+
+
+def _iteration(r, n, it=0, ahead=1, before=lambda call, mb: None, dirs=lambda mb: 0):
+    """Forwards `ahead` micro-batches before the backwards; `before` is told of every call."""
+    r.ok(r.lib.bp_stage_zero_grad(r.h))
+    f = 0
+    for mb in range(n):
+        while f < min(n, mb + ahead + 1):
+            for c in range(r.n_chunks):
+                before("F", f)
+                r.ok(r.forward(f, c, it))
+            f += 1
+        for c in range(r.n_chunks):
+            before("B", mb)
+            r.ok(r.backward(mb, c, it, dirs(mb)))
+    r.ok(r.lib.bp_stage_wait_forward(r.h))
+
+
+def _expect(lib, n, it=0, **kw):
+    """What an object with room for everything and a given group size adds up (micro-batch order)."""
+    with Rec(lib, wgrad_group=1, **kw) as r:
+        _iteration(r, n, it)
+        return r.gradients()
+
+
+def _same_sums(got, ref):
+    """The same contributions; matrices may have been added in another order."""
+    for k in ref:
+        assert sorted(got[k]) == sorted(ref[k]), k
+
+
+@pytest.mark.parametrize("opts", [dict(), dict(forward_ahead=1), dict(wgrad_group=3), dict(wgrad_group=8, stash_recompute=1, forward_ahead=1),
+                                  dict(dtype=BP_F32, layers=2), dict(layers=2, n_chunks=2, forward_ahead=1), dict(layers=3), dict(hidden=256)])
+@pytest.mark.parametrize("n", [1, 3, 19])
+def test_iterations_are_ordered(rec, n, opts):
+    with Rec(rec, **opts) as r:
+        for it in range(3):
+            _iteration(r, n, it)
+            if it != 1:
+                got = r.gradients()
+    plain = {k: v for k, v in opts.items() if k in ("dtype", "layers", "n_chunks", "hidden", "stash_recompute")}
+    _same_sums(got, _expect(rec, n, 2, **plain))
+    assert all(len(v) == n for v in got.values())
+
+
+@pytest.mark.parametrize("layers", [1, 2, 3])
+@pytest.mark.parametrize("forward_ahead", [0, 1])
+def test_group_buffer_short_of_memory(rec, layers, forward_ahead):
+    """No memory for the group buffer of a call that does not complete its group while a complete group is kept: the
+    group multiplies at once and hands over its buffers.  The calls behind that one must still wait for its column
+    reductions before they write the workspaces that these read."""
+    with Rec(rec, layers=layers, forward_ahead=forward_ahead) as r:
+        stashes = []
+
+        def before(call, mb):
+            if call == "B" and mb == 9:         # group 0 .. 7 is kept, 8 waits
+                r.fill_up(r.q - 1)
+                stashes.append(rec.rec_launches(b"wgrad"))
+            if call == "B" and mb == 10:
+                assert rec.rec_launches(b"wgrad") > stashes[0]      # the kept group did multiply
+
+        _iteration(r, 16, before=before, ahead=7)
+        got = r.gradients()
+    _same_sums(got, _expect(rec, 16, layers=layers))
