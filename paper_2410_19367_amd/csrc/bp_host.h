@@ -60,19 +60,22 @@ struct StashSlot {
 // group: its stash slot stays held and `buf` keeps, per layer, the gradients w.r.t. the outputs
 // of the four linear maps (dz, du, dy, dqkv).
 struct PendingMb { int slot; void* buf; };
-struct PendGroup {
+// A group whose GEMMs are to come, or under way: `done` has, per layer, bit k set for every matrix whose GEMM is enqueued,
+// so that nothing is multiplied twice, also when a call fails between two of them.
+struct WaitingGroup {
     std::vector<PendingMb> items;
-    // complete groups whose GEMMs wait for the reads at the end of the iteration, oldest first; of these
-    // the matrix that is read first has been multiplied (first_written: since the last clear)
-    std::vector<std::vector<PendingMb>> kept;
-    bool first_written = false;
+    std::vector<uint8_t> done;
+};
+struct PendGroup {
+    std::vector<PendingMb> items;        // the open group
+    // complete groups whose GEMMs wait for the reads at the end of the iteration, oldest first; of these the matrix that
+    // is read first has been multiplied
+    std::vector<WaitingGroup> kept;
     size_t kept_items() const {
         size_t n = 0;
-        for (const auto& k : kept) n += k.size();
+        for (const auto& k : kept) n += k.items.size();
         return n;
     }
-    // accumulate mode of the next contribution to matrix k of layer l: the first one after a clear overwrites
-    int acc(uint8_t clean, int l, int k) const { return (clean & 1) && !(first_written && l == 0 && k == 3) ? 2 : 1; }
 };
 
 // Everything one stream pair needs to run forwards and backwards on its own: the streams, the
@@ -132,10 +135,11 @@ struct Stage : LaneState {
     // parameters (matrices in the storage dtype, vectors fp32) and fp32 gradients per direction
     void* params = nullptr;
     float* grads[2] = {nullptr, nullptr};
-    // per (direction, chunk, layer): bit 0 set while the layer's weight-matrix gradients are
-    // logically zero, bit 1 the same for its vector gradients (biases, LayerNorm).  The buffer
+    // per (direction, chunk, layer): bit k (0: W2, 1: W1, 2: Wo, 3: Wqkv) set while that matrix' gradient is
+    // logically zero, kVectors the same for the vector gradients (biases, LayerNorm).  The buffer
     // contents are then undefined and the next contribution overwrites them instead of adding,
     // which saves both the clearing pass and the first read of every read-modify-write.
+    static constexpr uint8_t kVectors = 16, kClean = 31;
     std::vector<uint8_t> grad_clean[2];
     // Grouped weight gradients: per (direction, chunk) the micro-batches waiting for their group.
     int wgrad_group = 1;
@@ -235,10 +239,13 @@ struct Stage : LaneState {
     int live_slots() const;
 
     int wgrad_one(int dir, int chunk, int l, int k, const std::vector<PendingMb>& items, const void* cur_x,
-                  const void* cur_dy, int acc, hipStream_t ss);
+                  const void* cur_dy, hipStream_t ss);
+    int wgrad_waiting(int dir, int chunk, int l, int k, WaitingGroup& grp, hipStream_t ss);
     int mark_ready(int dir, int chunk, int l, int k, hipStream_t ss);
-    int multiply_kept(int dir, int chunk, int l, const std::vector<PendingMb>& items, hipStream_t ss);
+    int multiply_layer(int dir, int chunk, int l, WaitingGroup& grp, hipStream_t ss);
+    void close_group(PendGroup& grp);
     int give_back_kept(bool* any);
+    int side_work_ends(hipStream_t ss);
     int release_group(std::vector<PendingMb>& items, hipStream_t ss);
     int flush_group(int dir, int chunk);
     int flush_all();

@@ -346,8 +346,8 @@ int Stage::run_lanes(const Layout& L, const bp_op* order, int n_ops, int D, int 
         v->overlap = false;
         v->copy_grad_out = false;
         v->lens = lens;                                       // key-padding lengths (owned by this object)
-        v->grad_clean[0].assign(grad_clean[0].size(), 3);
-        v->grad_clean[1].assign(grad_clean[1].size(), 3);
+        v->grad_clean[0].assign(grad_clean[0].size(), kClean);
+        v->grad_clean[1].assign(grad_clean[1].size(), kClean);
         v->peak_held_bytes = 0;
         BP_EV(hipStreamWaitEvent(v->stream, ev_fork, 0));
     }

@@ -229,8 +229,8 @@ int Stage::create(Stage** out, int layers, int hidden, int heads, int seq, int m
     hipError_t e = hipMemsetAsync(st->params, 0, n_layers * poff, st->stream);
     if (e == hipSuccess) e = launch_fill_f32(st->grads[0], n_layers * goff / 4, 0.f, st->stream);
     if (e == hipSuccess) e = launch_fill_f32(st->grads[1], n_layers * goff / 4, 0.f, st->stream);
-    st->grad_clean[0].assign(n_layers, 3);
-    st->grad_clean[1].assign(n_layers, 3);
+    st->grad_clean[0].assign(n_layers, kClean);
+    st->grad_clean[1].assign(n_layers, kClean);
     for (int c = 0; c < st->n_chunks && e == hipSuccess; ++c)
         for (int l = 0; l < st->L && e == hipSuccess; ++l) {
             e = launch_fill_f32((float*)st->param(c, l, BP_LN1_G), st->H, 1.f, st->stream);
@@ -330,8 +330,8 @@ int Stage::make_view(Stage** out) {
     v->slot_capacity = slot_capacity;
     v->pend[0].resize(n_chunks);
     v->pend[1].resize(n_chunks);
-    v->grad_clean[0].assign(grad_clean[0].size(), 3);
-    v->grad_clean[1].assign(grad_clean[1].size(), 3);
+    v->grad_clean[0].assign(grad_clean[0].size(), kClean);
+    v->grad_clean[1].assign(grad_clean[1].size(), kClean);
     int rc = v->lane_alloc(*v, true);
     if (rc) { delete v; return rc; }
     *out = v;
@@ -366,12 +366,11 @@ Stage::~Stage() {
         if (s.fwd_done) hipEventDestroy(s.fwd_done);
     }
     for (int dir = 0; dir < 2; ++dir)
-        for (auto& grp : pend[dir])
-            {
-                for (auto& it : grp.items) hipFree(it.buf);
-                for (auto& kept : grp.kept)
-                    for (auto& it : kept) hipFree(it.buf);
-            }
+        for (auto& grp : pend[dir]) {
+            for (auto& it : grp.items) hipFree(it.buf);
+            for (auto& kept : grp.kept)
+                for (auto& it : kept.items) hipFree(it.buf);
+        }
     for (auto e : sched_ev) if (e) hipEventDestroy(e);
     for (auto e : ev_matrix) if (e) hipEventDestroy(e);
     if (ev_vectors) hipEventDestroy(ev_vectors);
@@ -469,7 +468,7 @@ int Stage::get_grad(int chunk, int layer, int id, float* host, size_t n) {
     } else if ((rc = sync_all())) {
         return rc;
     }
-    if (grad_clean[0][(size_t)chunk * L + layer] & (tensor_is_matrix(id) ? 1 : 2)) {   // nothing since the last clear
+    if (grad_clean[0][(size_t)chunk * L + layer] & (k_of[id] < 0 ? kVectors : 1 << k_of[id])) {   // nothing since the last clear
         memset(host, 0, n * sizeof(float));
         return BP_OK;
     }
@@ -490,8 +489,8 @@ int Stage::zero_grad() {
     // waiting for their group belong to what is being cleared and are dropped.
     int rc = drop_pending();
     if (rc) return rc;
-    grad_clean[0].assign(grad_clean[0].size(), 3);
-    grad_clean[1].assign(grad_clean[1].size(), 3);
+    grad_clean[0].assign(grad_clean[0].size(), kClean);
+    grad_clean[1].assign(grad_clean[1].size(), kClean);
     return BP_OK;
 }
 
@@ -505,16 +504,16 @@ int Stage::merge_directions() {
     hipStream_t gs = side_stream();
     for (size_t i = 0; i < grad_clean[0].size(); ++i) {
         const int c0 = grad_clean[0][i], c1 = grad_clean[1][i];
-        if (c1 == 3) continue;
-        if (c1 != 0 || (c0 != 0 && c0 != 3))
+        if (c1 == kClean) continue;
+        if (c1 != 0 || (c0 != 0 && c0 != kClean))
             return fail(BP_ESTATE, "merge_directions: layer %zu is partly written", i);
         float* g0 = (float*)((char*)grads[0] + i * g_layer_bytes);
         float* g1 = (float*)((char*)grads[1] + i * g_layer_bytes);
-        hipError_t e = c0 == 3 ? hipMemcpyAsync(g0, g1, g_layer_bytes, hipMemcpyDeviceToDevice, gs)
+        hipError_t e = c0 == kClean ? hipMemcpyAsync(g0, g1, g_layer_bytes, hipMemcpyDeviceToDevice, gs)
                                : launch_add_f32(g0, g1, n, gs);
         if (e != hipSuccess) return fail(BP_EHIP, "merge_directions: %s", hipGetErrorString(e));
         grad_clean[0][i] = 0;
-        grad_clean[1][i] = 3;
+        grad_clean[1][i] = kClean;
     }
     return BP_OK;
 }
@@ -523,9 +522,9 @@ int Stage::merge_directions() {
 
 // Gradient of weight matrix k (0: W2, 1: W1, 2: Wo, 3: Wqkv) of one layer over a group's waiting
 // micro-batches plus, when cur_x (the current micro-batch's stash of this layer) is given, the
-// current one: a single GEMM whose contraction runs over all their tokens.
+// current one: a single GEMM whose contraction runs over all their tokens.  The first one after a clear overwrites.
 int Stage::wgrad_one(int dir, int chunk, int l, int k, const std::vector<PendingMb>& items, const void* cur_x,
-                     const void* cur_dy, int acc, hipStream_t ss) {
+                     const void* cur_dy, hipStream_t ss) {
     static const int ids[4] = {BP_W2, BP_W1, BP_WO, BP_WQKV};
     const size_t sx[4] = {s_g, s_m, s_ctx, s_a}, qy[4] = {q_dz, q_du, q_dy, q_dqkv};
     const int Mk[4] = {F, H, H, H}, Nk[4] = {H, F, H, 3 * H};
@@ -567,10 +566,11 @@ int Stage::wgrad_one(int dir, int chunk, int l, int k, const std::vector<Pending
         ys[n] = cur_dy; ++n;
     }
     if (n == 0) return BP_OK;
+    uint8_t& clean = grad_clean[dir][(size_t)chunk * L + l];
     GemmArgs g;
     g.A = xs[0]; g.B = ys[0]; g.C = grad(dir, chunk, l, ids[k]); g.bias = nullptr; g.residual = nullptr;
     g.M = Mk[k]; g.N = Nk[k]; g.K = T; g.lda = Mk[k]; g.ldb = Nk[k]; g.ldc = Nk[k];
-    g.a_t = 1; g.b_t = 0; g.accumulate = acc;
+    g.a_t = 1; g.b_t = 0; g.accumulate = clean >> k & 1 ? 2 : 1;
     g.nseg = n;
     for (int i = 1; i < n; ++i) { g.A_more[i - 1] = xs[i]; g.B_more[i - 1] = ys[i]; }
     // all weight-gradient GEMMs run on one stream (the side stream, or the main one when the two
@@ -581,7 +581,30 @@ int Stage::wgrad_one(int dir, int chunk, int l, int k, const std::vector<Pending
     Scoped sc(this, BP_K_GEMM, 2.0 * Mk[k] * Nk[k] * (double)T * n, 0);
     hipError_t e = launch_gemm(dtype, g, ss);
     if (e != hipSuccess) return fail(BP_EHIP, "weight-gradient GEMM: %s", hipGetErrorString(e));
+    clean &= ~(1 << k);
     return BP_OK;
+}
+
+// The same for a group that waits, unless it has been done.
+int Stage::wgrad_waiting(int dir, int chunk, int l, int k, WaitingGroup& grp, hipStream_t ss) {
+    if (grp.done[l] >> k & 1) return BP_OK;
+    if (int rc = wgrad_one(dir, chunk, l, k, grp.items, nullptr, nullptr, ss)) return rc;
+    grp.done[l] |= 1 << k;
+    return BP_OK;
+}
+
+int Stage::multiply_layer(int dir, int chunk, int l, WaitingGroup& grp, hipStream_t ss) {
+    for (int k = 3; k >= 0; --k)
+        if (int rc = wgrad_waiting(dir, chunk, l, k, grp, ss)) return rc;
+    return BP_OK;
+}
+
+// The open group takes no more micro-batches: behind the kept ones, if it has any.
+void Stage::close_group(PendGroup& grp) {
+    if (grp.items.empty()) return;
+    grp.kept.emplace_back();
+    grp.kept.back().items.swap(grp.items);
+    grp.kept.back().done.assign(L, 0);
 }
 
 // Behind the last contribution to a weight gradient of direction 0: get_grad waits for this one only.
@@ -599,17 +622,6 @@ int Stage::mark_ready(int dir, int chunk, int l, int k, hipStream_t ss) {
     return BP_OK;
 }
 
-// The four GEMMs of one layer for a complete group that was kept.
-int Stage::multiply_kept(int dir, int chunk, int l, const std::vector<PendingMb>& items, hipStream_t ss) {
-    uint8_t& clean = grad_clean[dir][(size_t)chunk * L + l];
-    for (int k = 3; k >= 0; --k) {
-        if (is_first_read(l, k)) continue;              // multiplied when the group was complete
-        if (int rc = wgrad_one(dir, chunk, l, k, items, nullptr, nullptr, (clean & 1) ? 2 : 1, ss)) return rc;
-    }
-    clean &= ~1;
-    return BP_OK;
-}
-
 // Memory is short: the kept groups multiply now, and their stashes and buffers go back to the pools.  *any: there were some.
 int Stage::give_back_kept(bool* any) {
     *any = false;
@@ -618,29 +630,32 @@ int Stage::give_back_kept(bool* any) {
     for (int dir = 0; dir < 2; ++dir)
         for (int c = 0; c < n_chunks; ++c) {
             PendGroup& grp = pend[dir][c];
-            for (auto& kept : grp.kept) {
+            while (!grp.kept.empty()) {
                 for (int l = 0; l < L; ++l)
-                    if ((rc = multiply_kept(dir, c, l, kept, ss))) return rc;
-                if ((rc = release_group(kept, ss))) return rc;
+                    if ((rc = multiply_layer(dir, c, l, grp.kept[0], ss))) return rc;
+                forget_ready();
+                if ((rc = side_work_ends(ss)) || (rc = release_group(grp.kept[0].items, ss))) return rc;
+                grp.kept.erase(grp.kept.begin());
                 *any = true;
             }
-            grp.kept.clear();
-            grp.first_written = false;
         }
-    if (*any) {
-        forget_ready();
-        if (ss != stream) {
-            hipError_t e = hipEventRecord(ev_misc, ss);
-            if (e != hipSuccess) return fail(BP_EHIP, "give_back_kept: %s", hipGetErrorString(e));
-            call_done_pending = true;
-        }
-    }
+    return BP_OK;
+}
+
+// The next backward waits for everything the side stream holds now.  Comes before buffers that this work reads go back to
+// their pools.
+int Stage::side_work_ends(hipStream_t ss) {
+    if (ss == stream) return BP_OK;
+    hipError_t e = hipEventRecord(ev_misc, ss);
+    if (e != hipSuccess) return fail(BP_EHIP, "end of the side work: %s", hipGetErrorString(e));
+    call_done_pending = true;
     return BP_OK;
 }
 
 // The group's stashes and buffers become reusable once the side stream has passed this point.
 int Stage::release_group(std::vector<PendingMb>& items, hipStream_t ss) {
-    for (PendingMb& it : items) {
+    while (!items.empty()) {
+        const PendingMb it = items.back();
         StashSlot& sl = slots[it.slot];
         if (ss != stream) {
             hipError_t e = hipSuccess;
@@ -651,8 +666,8 @@ int Stage::release_group(std::vector<PendingMb>& items, hipStream_t ss) {
         }
         sl.held = false;
         pend_pool.push_back(it.buf);
+        items.pop_back();
     }
-    items.clear();
     return BP_OK;
 }
 
@@ -674,30 +689,17 @@ int Stage::flush_group(int dir, int chunk) {
         forget_ready();
     }
     int rc;
-    for (int l = 0; l < L; ++l) {       // the order in which the gradients are usually read
-        uint8_t& clean = grad_clean[dir][(size_t)chunk * L + l];
+    close_group(grp);
+    for (int l = 0; l < L; ++l)         // the order in which the gradients are usually read
         for (int k = 3; k >= 0; --k) {
-            int acc = grp.acc(clean, l, k);
-            for (const auto& kept : grp.kept) {
-                if (is_first_read(l, k)) continue;
-                if ((rc = wgrad_one(dir, chunk, l, k, kept, nullptr, nullptr, acc, ss))) return rc;
-                acc = 1;
-            }
-            if ((rc = wgrad_one(dir, chunk, l, k, grp.items, nullptr, nullptr, acc, ss))) return rc;
+            for (auto& kept : grp.kept)
+                if ((rc = wgrad_waiting(dir, chunk, l, k, kept, ss))) return rc;
             if ((rc = mark_ready(dir, chunk, l, k, ss))) return rc;
         }
-        clean &= ~1;
-    }
+    if ((rc = side_work_ends(ss))) return rc;   // the next backward must not overwrite buffers these GEMMs still read
     for (auto& kept : grp.kept)
-        if ((rc = release_group(kept, ss))) return rc;
+        if ((rc = release_group(kept.items, ss))) return rc;
     grp.kept.clear();
-    grp.first_written = false;
-    if ((rc = release_group(grp.items, ss))) return rc;
-    if (ss != stream) {     // the next backward must not overwrite buffers these GEMMs still read
-        hipError_t e = hipEventRecord(ev_misc, ss);
-        if (e != hipSuccess) return fail(BP_EHIP, "flush_group: %s", hipGetErrorString(e));
-        call_done_pending = true;
-    }
     return BP_OK;
 }
 
@@ -714,20 +716,17 @@ int Stage::drop_pending() {
     hipStream_t ss = side_stream();
     bool any = false;
     for (int dir = 0; dir < 2; ++dir)
+        for (auto& grp : pend[dir]) any = any || !grp.items.empty() || !grp.kept.empty();
+    // column sums of those calls may still be running, on buffers that the next backward takes from the pool
+    int rc = any ? side_work_ends(ss) : BP_OK;
+    for (int dir = 0; dir < 2; ++dir)
         for (auto& grp : pend[dir]) {
-            any = any || !grp.items.empty() || !grp.kept.empty();
-            int rc = release_group(grp.items, ss);      // column sums of those calls may still be running
+            if (!rc) rc = release_group(grp.items, ss);
             for (auto& kept : grp.kept)
-                if (!rc) rc = release_group(kept, ss);
+                if (!rc) rc = release_group(kept.items, ss);
             if (rc) return rc;
             grp.kept.clear();
-            grp.first_written = false;
         }
-    if (any && ss != stream) {      // ... and read the buffers that the next backward takes from the pool
-        hipError_t e = hipEventRecord(ev_misc, ss);
-        if (e != hipSuccess) return fail(BP_EHIP, "drop_pending: %s", hipGetErrorString(e));
-        call_done_pending = true;
-    }
     return BP_OK;
 }
 
@@ -980,6 +979,11 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         layer_done_pending[0] = layer_done_pending[1] = false;
     }
 
+    struct FailGuard {      // a call that fails half-way leaves side work that no event covers
+        Stage* call; hipStream_t ss;
+        ~FailGuard() { if (call && call->side_work_ends(ss)) hipStreamSynchronize(ss); }
+    } failed{this, ss};
+
     // Grouped weight gradients: unless this call completes its group, the four weight-gradient
     // GEMMs of every layer are postponed; the tensors they need (dz, du, dy, dqkv) are then
     // produced straight into a buffer that lives until the group is complete, and the stash stays
@@ -1000,14 +1004,14 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
     const bool keep = completes && keeps_groups(ss) && live_slots() > 1;
     bool defer = !completes || keep || (leaves_events(ss) && live_slots() == 1);
     // the oldest kept group makes room: its GEMMs run beside this call's chain, layer by layer
-    std::vector<PendingMb> oldest;
+    WaitingGroup oldest;
     if (keep && (grp.kept_items() + grp.items.size() + 1) * (size_t)T > kKeptTokens && !grp.kept.empty()) {
-        oldest.swap(grp.kept.front());
+        std::swap(oldest, grp.kept.front());
         grp.kept.erase(grp.kept.begin());
     }
-    struct OldestGuard {    // a call that fails half-way: back to where it came from
-        PendGroup& grp; std::vector<PendingMb>& items;
-        ~OldestGuard() { if (!items.empty()) grp.kept.insert(grp.kept.begin(), items); }
+    struct OldestGuard {    // a call that fails half-way: back to where it came from, with what is done of it
+        PendGroup& grp; WaitingGroup& oldest;
+        ~OldestGuard() { if (!oldest.items.empty()) grp.kept.insert(grp.kept.begin(), oldest); }
     } oldest_guard{grp, oldest};
     vectors_ready = false;                  // column reductions are on their way
     if (!leaves_events(ss)) forget_ready(); // ... and GEMMs without events behind them
@@ -1033,9 +1037,9 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             if (!completes) return rc;
             qbuf = nullptr;             // no room for the one buffer more: multiply along the way
             defer = false;
-            if (!oldest.empty()) {
+            if (!oldest.items.empty()) {
                 grp.kept.insert(grp.kept.begin(), oldest);
-                oldest.clear();
+                oldest = WaitingGroup();
             }
         }
     }
@@ -1061,7 +1065,6 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         auto P = [&](int id) { return param(chunk, l, id); };
         auto G = [&](int id) { return grad(dir, chunk, l, id); };
         uint8_t& clean = grad_clean[dir][(size_t)chunk * L + l];
-        auto acc = [&](int k) { return grp.acc(clean, l, k); };
         char* qb = defer ? qbuf + (size_t)l * q_layer_bytes : nullptr;
         void* dx = l == 0 ? grad_in : defer ? (void*)(qb - q_layer_bytes + q_dz) : ws_dx[l % 3];
         void* big1 = defer ? (void*)(qb + q_du) : ws_big1[p];
@@ -1073,7 +1076,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             layer_done_pending[p] = false;
         }
         auto wgrad_along = [&](int k, const void* dy) {
-            const int rc = wgrad_one(dir, chunk, l, k, grp.items, sb, dy, acc(k), ss);
+            const int rc = wgrad_one(dir, chunk, l, k, grp.items, sb, dy, ss);
             return rc ? rc : mark_ready(dir, chunk, l, k, ss);
         };
         // column-sum partial regions: db2 | (dgamma2, dbeta2) | dbo | dbqkv | (dgamma1, dbeta1) | db1
@@ -1131,7 +1134,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         {   // every bias and LayerNorm-parameter gradient of the layer in one batched reduction
             ColsumBatch cb;
             cb.n = 6;
-            cb.overwrite = (clean & 2) ? 1 : 0;
+            cb.overwrite = (clean & kVectors) ? 1 : 0;
             cb.jobs[0] = ColsumJob{dz, nullptr, nullptr, nullptr, H, G(BP_B2), nullptr, p_b2};
             cb.jobs[1] = ColsumJob{h1, sb + s_y, (const float*)(sb + s_mean2), (const float*)(sb + s_rstd2), H,
                                    G(BP_LN2_B), G(BP_LN2_G), p_ln2};
@@ -1143,8 +1146,8 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             Scoped sc(this, BP_K_COLSUM, 0, 0);
             BP_LAUNCH(launch_colsum_batch(dtype, T, cb, ss));
         }
-        clean &= defer ? ~2 : 0;
-        if (!oldest.empty() && (rc = multiply_kept(dir, chunk, l, oldest, ss))) return rc;
+        clean &= ~kVectors;
+        if (!oldest.items.empty() && (rc = multiply_layer(dir, chunk, l, oldest, ss))) return rc;
         if (two) {
             BP_HIP(hipEventRecord(ev_layer_done[p], ss));
             layer_done_pending[p] = true;
@@ -1177,26 +1180,20 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
         grp.items.push_back(PendingMb{slot, qbuf});
         qbuf = nullptr;                         // owned by the group now
         note_held();                            // (before the flush: a complete group holds the most)
-        if (!oldest.empty()) {                  // the next backward takes the buffers that these GEMMs read
-            if ((rc = release_group(oldest, ss))) return rc;
-            BP_HIP(hipEventRecord(ev_misc, ss));
-            call_done_pending = true;
+        if (completes) close_group(grp);
+        if (!oldest.items.empty()) {            // the next backward takes the buffers that these GEMMs read
+            if ((rc = side_work_ends(ss)) || (rc = release_group(oldest.items, ss))) return rc;
         }
         if (keep) {
             for (int l = 0; l < L; ++l)
-                for (int k = 3; k >= 0; --k) {
-                    if (!is_first_read(l, k)) continue;
-                    const uint8_t clean = grad_clean[dir][(size_t)chunk * L + l];
-                    if ((rc = wgrad_one(dir, chunk, l, k, grp.items, nullptr, nullptr, grp.acc(clean, l, k), ss))) return rc;
-                    grp.first_written = true;
-                }
-            grp.kept.emplace_back();
-            grp.kept.back().swap(grp.items);
+                for (int k = 3; k >= 0; --k)
+                    if (is_first_read(l, k) && (rc = wgrad_waiting(dir, chunk, l, k, grp.kept.back(), ss))) return rc;
         } else if (completes && (rc = flush_group(dir, chunk))) {
             return rc;
         }
     } else {
-        if ((rc = release_group(grp.items, ss))) return rc;
+        // (after a deferring call the layers' own events order the workspaces)
+        if ((rc = side_work_ends(ss)) || (rc = release_group(grp.items, ss))) return rc;
         if (two) {
             // the stash may be handed to a new forward only after the side stream has read it
             if (!slots[slot].side_done)
@@ -1205,10 +1202,7 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             slots[slot].side_pending = true;
         }
     }
-    if (two && !defer) {            // (after a deferring call the layers' own events order the workspaces)
-        BP_HIP(hipEventRecord(ev_misc, ss));
-        call_done_pending = true;
-    }
+    failed.call = nullptr;
 #undef BP_HIP
     return BP_OK;
 }

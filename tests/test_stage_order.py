@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import synth_inputs as si
-from paper_2410_19367_amd.binding import BP_BF16, BP_EHIP, BP_ENOMEM, BP_F32, BP_OK, TENSOR_IDS, bp_op, bp_opts
+from paper_2410_19367_amd.binding import BP_BF16, BP_EHIP, BP_ENOMEM, BP_ESTATE, BP_F32, BP_OK, TENSOR_IDS, bp_op, bp_opts
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 MATRICES = ("wqkv", "wo", "w1", "w2")
@@ -182,3 +182,46 @@ def test_group_buffer_short_of_memory(rec, layers, forward_ahead):
         _iteration(r, 16, before=before, ahead=7)
         got = r.gradients()
     _same_sums(got, _expect(rec, 16, layers=layers))
+
+
+# where: the call that makes the oldest kept group multiply, the first read, a call short of memory while a group is kept
+@pytest.mark.parametrize("where", ["oldest", "read", "short"])
+@pytest.mark.parametrize("what,nth", [("wgrad", 0), ("wgrad", 1), ("wgrad", 2), ("wgrad", 5), ("wgrad", 10), ("event", 4), ("event", 9), ("event", 15)])
+def test_failed_launch_counts_nothing_twice(rec, where, what, nth):
+    """A launch (or an event) fails inside the multiplication of waiting groups and the caller repeats the call: every
+    product is in the sums once.  (Column sums of the layers that the failed backward had done are not looked at: that
+    call is repeated as a whole.)"""
+    call = {"oldest": 23, "short": 9}.get(where)
+    n = 26
+    with Rec(rec, layers=3) as r:
+        failed = []
+        for mb in range(n + 2):
+            if mb < n:
+                r.ok(r.forward(mb))
+            b = mb - 2
+            if b < 0:
+                continue
+            if b == call:
+                if where == "short":
+                    r.fill_up(r.q - 1)
+                rec.rec_fail(what.encode(), nth)
+                if r.backward(b) == BP_OK:      # fewer of them than that
+                    rec.rec_fail(b"", -1)
+                    continue
+                failed.append(b)
+                if where == "short":
+                    rec.rec_memory(1 << 50)
+                if r.backward(b) == BP_ESTATE:      # it failed behind its last launch: the micro-batch is in
+                    assert what == "event"
+                continue
+            r.ok(r.backward(b))
+        if where == "read":
+            rec.rec_fail(what.encode(), nth)
+            host = np.zeros(1024, np.float32)
+            if rec.bp_stage_get_grad(r.h, 0, 0, 0, host.ctypes.data, 1024) != BP_OK:
+                failed.append("read")
+            rec.rec_fail(b"", -1)
+        got = {k: r.terms(*k) for k in r.names if k[2] in MATRICES}
+        assert failed or what == "event"
+    ref = _expect(rec, n, layers=3)
+    _same_sums(got, {k: ref[k] for k in got})
