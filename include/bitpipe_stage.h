@@ -75,9 +75,11 @@ typedef struct bp_opts {
                            max_inflight) plus their output gradients until it is complete or
                            until bp_stage_get_grad / bp_run_schedule's merge flushes it.
                            With 0 and 16 MB of gradients or more in a chunk, groups that complete while
-                           other stashes are live are kept too, up to 16384 tokens and 8 GiB of them,
-                           so that their products run while the first gradients are read; a given
-                           size keeps no complete group.
+                           other stashes are live are kept too, so that their products run while the
+                           first gradients are read: up to 16384 tokens of a chunk and direction and
+                           8 GiB of the object, and only while an eighth of the device's memory is free.
+                           They multiply earlier, and everything idle goes back to the device, when an
+                           allocation of the object finds no room.  A given size keeps no complete group.
                            bp_run_schedule uses groups no larger than the number of backward
                            calls a (direction, stage) gets in the iteration.                  */
     int stash_recompute;/* 0: the stash keeps everything the backward reads, 16*T*H elements per

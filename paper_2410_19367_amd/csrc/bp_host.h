@@ -161,15 +161,19 @@ struct Stage : LaneState {
     bool reads_early() const { return !is_view && (size_t)L * g_layer_bytes >= ((size_t)16 << 20); }
     bool leaves_events(hipStream_t on) const { return on != stream && wgrad_group > 1 && reads_early(); }
     // Complete groups are kept until the reads behind the last backward (see Stage::backward) if the library chose the
-    // group size itself, as many as hold kKeptTokens tokens (what a default group holds at most) and 8 GiB: about what the
-    // GEMMs of the last group leave of the time that the link takes (per element of a weight matrix 70 ps of link
-    // against 26 ps of GEMM over 16384 tokens).  Not with the reduced stash, which is for callers short of memory.
-    static constexpr size_t kKeptTokens = 16384;
+    // group size itself: of a (direction, chunk) as many as hold kKeptTokens tokens (what a default group holds at most),
+    // about what the GEMMs of the last group leave of the time that the link takes (per element of a weight matrix 70 ps
+    // of link against 26 ps of GEMM over 16384 tokens), of the object no more than kKeptBytes, and none unless an eighth of
+    // the device is free: the caller's other allocations come first.  Not with the reduced stash, which is for callers
+    // short of memory.
+    static constexpr size_t kKeptTokens = 16384, kKeptBytes = (size_t)8 << 30;
     bool own_group = false;
     bool keeps_groups(hipStream_t on) const {
         return own_group && !lean && leaves_events(on) && (size_t)wgrad_group * T <= kKeptTokens &&
-               (kKeptTokens / T + 1) * (size_t)L * (s_layer_bytes + q_layer_bytes) <= ((size_t)8 << 30);
+               (kKeptTokens / T + 1) * kept_bytes_each() <= kKeptBytes;
     }
+    size_t kept_bytes_each() const { return (size_t)L * (s_layer_bytes + q_layer_bytes); }     // of one micro-batch
+    size_t kept_bytes() const;                                                                 // of the object
     static bool is_first_read(int l, int k) { return l == 0 && k == 3; }    // Wqkv of layer 0
     void forget_ready() { matrix_ready.assign(matrix_ready.size(), 0); vectors_ready = false; }
     size_t q_dz = 0, q_du = 0, q_dy = 0, q_dqkv = 0, q_layer_bytes = 0;
@@ -194,6 +198,7 @@ struct Stage : LaneState {
     bool is_view = false;
     int device = 0;                      // HIP device the object lives on
     std::vector<Stage*> views;
+    Stage* owner = nullptr;              // of a view: the object whose lane it is
     bool copy_grad_out = false;          // backward copies grad_out first (its side stream must not read caller memory)
     int lane_alloc(LaneState& ln, bool with_stream);
     void lane_free(LaneState& ln, bool with_stream);
@@ -244,7 +249,10 @@ struct Stage : LaneState {
     int mark_ready(int dir, int chunk, int l, int k, hipStream_t ss);
     int multiply_layer(int dir, int chunk, int l, WaitingGroup& grp, hipStream_t ss);
     void close_group(PendGroup& grp);
+    int multiply_kept(int dir, int chunk);
     int give_back_kept(bool* any);
+    int free_idle();
+    int alloc(void** p, size_t bytes);
     int side_work_ends(hipStream_t ss);
     int release_group(std::vector<PendingMb>& items, hipStream_t ss);
     int flush_group(int dir, int chunk);

@@ -431,12 +431,8 @@ int Stage::run_schedule(const Layout& L, const bp_op* order, int n_ops, int D, c
         sync_all();
         hipFree(sched_act); hipFree(sched_grad); hipFree(sched_loss);
         sched_act = sched_grad = nullptr; sched_loss = nullptr; sched_n = 0;
-        if (hipMalloc(&sched_act, (size_t)N * 2 * THb) != hipSuccess ||
-            hipMalloc(&sched_grad, (size_t)N * THb) != hipSuccess ||
-            hipMalloc((void**)&sched_loss, ((size_t)N + (size_t)N * 1024) * sizeof(float)) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(BP_ENOMEM, "allocating the iteration's hand-off buffers failed");
-        }
+        if ((rc = alloc(&sched_act, (size_t)N * 2 * THb)) || (rc = alloc(&sched_grad, (size_t)N * THb)) ||
+            (rc = alloc((void**)&sched_loss, ((size_t)N + (size_t)N * 1024) * sizeof(float)))) return rc;
         sched_n = N;
     }
     // an order may keep every (stage, mb) stashed at once; slots get memory only when used

@@ -250,31 +250,31 @@ int Stage::lane_alloc(LaneState& ln, bool with_stream) {
     const size_t big = std::max((size_t)F, (size_t)3 * H);
     int rc = BP_OK;
     for (int p = 0; p < 2 && !rc; ++p) {
-        (rc = dev_alloc(&ln.ws_big1[p], (size_t)T * big * esz)) ||
-            (rc = dev_alloc(&ln.ws_big2[p], (size_t)T * 3 * H * esz)) ||
-            (rc = dev_alloc(&ln.ws_h1[p], TH)) || (rc = dev_alloc(&ln.ws_h2[p], TH)) ||
-            (rc = dev_alloc(&ln.ws_h5[p], TH)) ||
-            (rc = dev_alloc((void**)&ln.ws_colsum[p],
-                            std::max<size_t>(colsum_chunks(T) * ((size_t)9 * H + F), 1024) * sizeof(float)));
+        (rc = alloc(&ln.ws_big1[p], (size_t)T * big * esz)) ||
+            (rc = alloc(&ln.ws_big2[p], (size_t)T * 3 * H * esz)) ||
+            (rc = alloc(&ln.ws_h1[p], TH)) || (rc = alloc(&ln.ws_h2[p], TH)) ||
+            (rc = alloc(&ln.ws_h5[p], TH)) ||
+            (rc = alloc((void**)&ln.ws_colsum[p],
+                        std::max<size_t>(colsum_chunks(T) * ((size_t)9 * H + F), 1024) * sizeof(float)));
     }
-    for (int i = 0; i < 3 && !rc; ++i) rc = dev_alloc(&ln.ws_dx[i], TH);
-    if (!rc) rc = dev_alloc(&ln.ws_h4, TH);
-    if (!rc) rc = dev_alloc(&ln.ws_gout, TH);
+    for (int i = 0; i < 3 && !rc; ++i) rc = alloc(&ln.ws_dx[i], TH);
+    if (!rc) rc = alloc(&ln.ws_h4, TH);
+    if (!rc) rc = alloc(&ln.ws_gout, TH);
     if (!rc && dtype == BP_BF16) {
         ln.ws_splitk_elems = (size_t)4 * T * H;
-        rc = dev_alloc((void**)&ln.ws_splitk, ln.ws_splitk_elems * sizeof(float));
+        rc = alloc((void**)&ln.ws_splitk, ln.ws_splitk_elems * sizeof(float));
         // weight gradients with few output tiles (H x H, or a narrow MLP) and a long token axis
         ln.ws_splitk_side_elems = std::min((size_t)4 * H * std::max(H, F), (size_t)64 << 20);
-        if (!rc) rc = dev_alloc((void**)&ln.ws_splitk_side, ln.ws_splitk_side_elems * sizeof(float));
+        if (!rc) rc = alloc((void**)&ln.ws_splitk_side, ln.ws_splitk_side_elems * sizeof(float));
     }
     if (!rc && lean) {
-        (rc = dev_alloc(&ln.fw_a, TH)) || (rc = dev_alloc(&ln.fw_m, TH)) || (rc = dev_alloc(&ln.fw_g, TF)) ||
-            (rc = dev_alloc((void**)&ln.re_stats, (size_t)2 * T * sizeof(float)));
+        (rc = alloc(&ln.fw_a, TH)) || (rc = alloc(&ln.fw_m, TH)) || (rc = alloc(&ln.fw_g, TF)) ||
+            (rc = alloc((void**)&ln.re_stats, (size_t)2 * T * sizeof(float)));
         for (int i = 0; i < kMaxGemmSegments && !rc; ++i)
-            (rc = dev_alloc(&ln.re_x[0][i], TF)) || (rc = dev_alloc(&ln.re_x[1][i], TH)) ||
-                (rc = dev_alloc(&ln.re_x[2][i], TH));
+            (rc = alloc(&ln.re_x[0][i], TF)) || (rc = alloc(&ln.re_x[1][i], TH)) ||
+                (rc = alloc(&ln.re_x[2][i], TH));
     }
-    if (!rc) rc = dev_alloc((void**)&ln.ws_delta, (size_t)B * heads * S * sizeof(float));
+    if (!rc) rc = alloc((void**)&ln.ws_delta, (size_t)B * heads * S * sizeof(float));
     if (rc) return rc;
     hipError_t e = hipSuccess;
     if (with_stream) e = hipStreamCreateWithFlags(&ln.stream, hipStreamNonBlocking);
@@ -315,6 +315,7 @@ int Stage::make_view(Stage** out) {
     Stage* v = new (std::nothrow) Stage();
     if (!v) return fail(BP_ENOMEM, "host allocation failed");
     v->is_view = true;
+    v->owner = this;
     v->device = device;
     v->L = L; v->H = H; v->heads = heads; v->d = d; v->S = S; v->B = B; v->T = T; v->F = F; v->n_chunks = n_chunks;
     v->causal = causal; v->dtype = dtype; v->max_inflight = max_inflight; v->esz = esz; v->eps = eps;
@@ -421,7 +422,7 @@ int Stage::set_param(int chunk, int layer, int id, const float* host, size_t n) 
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
     } else {
         float* tmp = nullptr;
-        if ((rc = dev_alloc((void**)&tmp, n * sizeof(float)))) return rc;
+        if ((rc = alloc((void**)&tmp, n * sizeof(float)))) return rc;
         e = hipMemcpyAsync(tmp, host, n * sizeof(float), hipMemcpyHostToDevice, stream);
         if (e == hipSuccess) e = launch_cast_from_f32(dtype, tmp, dst, n, stream);
         if (e == hipSuccess) e = launch_transpose(dtype, rows, cols, dst, param_t(chunk, layer, id), stream);
@@ -622,24 +623,64 @@ int Stage::mark_ready(int dir, int chunk, int l, int k, hipStream_t ss) {
     return BP_OK;
 }
 
-// Memory is short: the kept groups multiply now, and their stashes and buffers go back to the pools.  *any: there were some.
+// The kept groups of one (direction, chunk) multiply now, and their stashes and buffers go back to the pools.
+int Stage::multiply_kept(int dir, int chunk) {
+    hipStream_t ss = side_stream();
+    PendGroup& grp = pend[dir][chunk];
+    int rc;
+    while (!grp.kept.empty()) {
+        for (int l = 0; l < L; ++l)
+            if ((rc = multiply_layer(dir, chunk, l, grp.kept[0], ss))) return rc;
+        forget_ready();
+        if ((rc = side_work_ends(ss)) || (rc = release_group(grp.kept[0].items, ss))) return rc;
+        grp.kept.erase(grp.kept.begin());
+    }
+    return BP_OK;
+}
+
+// Memory is short: so for all of them.  *any: there were some.
 int Stage::give_back_kept(bool* any) {
     *any = false;
-    hipStream_t ss = side_stream();
-    int rc;
     for (int dir = 0; dir < 2; ++dir)
         for (int c = 0; c < n_chunks; ++c) {
-            PendGroup& grp = pend[dir][c];
-            while (!grp.kept.empty()) {
-                for (int l = 0; l < L; ++l)
-                    if ((rc = multiply_layer(dir, c, l, grp.kept[0], ss))) return rc;
-                forget_ready();
-                if ((rc = side_work_ends(ss)) || (rc = release_group(grp.kept[0].items, ss))) return rc;
-                grp.kept.erase(grp.kept.begin());
-                *any = true;
-            }
+            *any = *any || !pend[dir][c].kept.empty();
+            if (int rc = multiply_kept(dir, c)) return rc;
         }
     return BP_OK;
+}
+
+size_t Stage::kept_bytes() const {
+    size_t n = 0;
+    for (int dir = 0; dir < 2; ++dir)
+        for (const auto& grp : pend[dir]) n += grp.kept_items();
+    return n * kept_bytes_each();
+}
+
+// Idle stashes and group buffers of the object and of its views back to the device.
+int Stage::free_idle() {
+    if (int rc = sync_all()) return rc;
+    for (void* b : pend_pool) hipFree(b);
+    pend_pool.clear();
+    for (auto& sl : slots)
+        if (sl.buf && !sl.live && !sl.held) {
+            hipFree(sl.buf);
+            sl.buf = nullptr;
+            sl.side_pending = false;
+        }
+    for (Stage* v : views)
+        if (int rc = v->free_idle()) return rc;
+    return BP_OK;
+}
+
+// Every allocation behind the object's creation: where the device has no room, kept groups multiply and what is idle goes
+// back before the call fails.
+int Stage::alloc(void** p, size_t bytes) {
+    int rc = dev_alloc(p, bytes);
+    if (rc != BP_ENOMEM) return rc;
+    Stage* all = owner ? owner : this;
+    bool any;
+    if ((rc = all->give_back_kept(&any)) || (rc = all->free_idle())) return rc;
+    return dev_alloc(p, bytes);
 }
 
 // The next backward waits for everything the side stream holds now.  Comes before buffers that this work reads go back to
@@ -749,7 +790,7 @@ int Stage::set_seqlens(int mb, const int32_t* host) {
     int32_t* dev = nullptr;
     if (it != lens.end()) dev = it->second;
     else {
-        int rc = dev_alloc((void**)&dev, B * sizeof(int32_t));
+        int rc = alloc((void**)&dev, B * sizeof(int32_t));
         if (rc) return rc;
         lens[mb] = dev;
     }
@@ -806,6 +847,7 @@ int Stage::acquire_slot(int chunk, int mb, int* out) {
             if (rc2) return rc2;
             for (size_t i = 0; any && i < slots.size(); ++i)
                 if (slots[i].buf && !slots[i].live && !slots[i].held) { pick = (int)i; rc = BP_OK; break; }
+            if (rc) rc = alloc(&slots[pick].buf, (size_t)L * s_layer_bytes);
         }
         if (rc) return rc;
     }
@@ -1001,14 +1043,26 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
     // over this, and 1 % less at H 5120, where single products fill the chip.
     PendGroup& grp = pend[dir][chunk];
     const bool completes = (int)grp.items.size() + 1 >= wgrad_group;
-    const bool keep = completes && keeps_groups(ss) && live_slots() > 1;
-    bool defer = !completes || keep || (leaves_events(ss) && live_slots() == 1);
-    // the oldest kept group makes room: its GEMMs run beside this call's chain, layer by layer
-    WaitingGroup oldest;
-    if (keep && (grp.kept_items() + grp.items.size() + 1) * (size_t)T > kKeptTokens && !grp.kept.empty()) {
-        std::swap(oldest, grp.kept.front());
-        grp.kept.erase(grp.kept.begin());
+    bool keep = completes && keeps_groups(ss) && live_slots() > 1;
+    if (keep) {
+        size_t room = 0, total = 0;
+        if (hipMemGetInfo(&room, &total) != hipSuccess) (void)hipGetLastError();
+        keep = total && room >= total / 8;
     }
+    // The oldest kept group of the (direction, chunk) makes room: its GEMMs run beside this call's chain, layer by layer.
+    // Where the others of the object leave none, the group is not kept.
+    WaitingGroup oldest;
+    if (keep) {
+        const size_t more = grp.items.size() + 1;
+        if ((grp.kept_items() + more) * (size_t)T > kKeptTokens || kept_bytes() + more * kept_bytes_each() > kKeptBytes) {
+            keep = !grp.kept.empty();
+            if (keep) {
+                std::swap(oldest, grp.kept.front());
+                grp.kept.erase(grp.kept.begin());
+            }
+        }
+    }
+    bool defer = !completes || keep || (leaves_events(ss) && live_slots() == 1);
     struct OldestGuard {    // a call that fails half-way: back to where it came from, with what is done of it
         PendGroup& grp; WaitingGroup& oldest;
         ~OldestGuard() { if (!oldest.items.empty()) grp.kept.insert(grp.kept.begin(), oldest); }
@@ -1028,6 +1082,8 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
                     layer_done_pending[0] = layer_done_pending[1] = false;
                 }
                 rc = BP_OK;
+            } else {
+                rc = alloc((void**)&qbuf, (size_t)L * q_layer_bytes);   // (an idle stash's memory)
             }
         }
         if (!rc && !qbuf) {
@@ -1043,6 +1099,9 @@ int Stage::backward(int chunk, int mb, const void* grad_out, void* grad_in, int 
             }
         }
     }
+    // products along the way come behind those of the groups before, so that the order of the sums does not depend on
+    // what memory there is
+    if (!defer && (rc = multiply_kept(dir, chunk))) return rc;
     struct PoolGuard {      // hand the buffer back if the call fails half-way
         Stage* st; char*& b;
         ~PoolGuard() { if (b) st->pend_pool.push_back(b); }

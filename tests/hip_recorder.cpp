@@ -52,7 +52,9 @@ std::vector<std::vector<u64>> read_back(1);       // id 0: zeros
 std::set<std::string> errors;
 std::string error_text, fail_name;
 long fail_in = -1;
-size_t total_bytes = (size_t)1 << 50, used_bytes = 0;
+const size_t total_bytes = (size_t)288 << 30;
+size_t used_bytes = 0, others_bytes = 0;
+size_t free_bytes() { return total_bytes - used_bytes - others_bytes; }
 addr next_addr = (addr)1 << 44;
 std::map<std::string, long> launches;
 
@@ -221,7 +223,7 @@ void* allocate(size_t bytes, bool caller) {
 extern "C" {
 
 hipError_t hipMalloc(void** p, size_t bytes) {
-    if (used_bytes + bytes > total_bytes) return hipErrorOutOfMemory;
+    if (bytes > free_bytes()) return hipErrorOutOfMemory;
     used_bytes += bytes;
     *p = allocate(bytes, false);
     return hipSuccess;
@@ -237,7 +239,7 @@ hipError_t hipFree(void* p) {
     allocs.erase(it);
     return hipSuccess;
 }
-hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = total_bytes - used_bytes; *t = total_bytes; return hipSuccess; }
+hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = free_bytes(); *t = total_bytes; return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "ok" : "made to fail"; }
@@ -292,7 +294,7 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDevicept
 void rec_reset() {
     allocs.clear(); contents.clear(); pinned.clear(); errors.clear(); read_back.assign(1, {});
     host.clear(); fail_in = -1; launches.clear();
-    total_bytes = (size_t)1 << 50; used_bytes = 0;
+    used_bytes = others_bytes = 0;
     for (Str* s : streams) { s->c.clear(); s->seq = 0; }
 }
 const char* rec_errors() {
@@ -300,7 +302,9 @@ const char* rec_errors() {
     for (auto& e : errors) error_text += e + "\n";
     return error_text.c_str();
 }
-void rec_memory(size_t free_bytes) { total_bytes = used_bytes + free_bytes; }
+void rec_others_leave(size_t bytes) {            // of the device's memory, what the object does not hold now
+    others_bytes = total_bytes - used_bytes - std::min(bytes, total_bytes - used_bytes);
+}
 size_t rec_used() { return used_bytes; }
 void rec_fail(const char* name, long in) { fail_name = name; fail_in = in; }
 int rec_still_to_fail() { return fail_in >= 0; }

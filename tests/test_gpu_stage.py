@@ -232,8 +232,8 @@ def test_kept_groups_give_the_bits_of_given_groups(n_micro, n_chunks, layers):
 
 
 def test_kept_groups_give_way_when_memory_is_short():
-    """With room on the device for a few stashes only, kept groups multiply at once and hand over theirs: nothing
-    fails that went through without keeping, and the bits stay."""
+    """With room on the device for a few stashes only, groups are not kept: nothing fails that went through without
+    keeping, and the bits stay.  (Groups that are kept when the room goes: the next test.)"""
     import torch
     e = _EarlyReads(n_micro=26, wgrad_group=0, forward_ahead=1, n_chunks=1, layers=2)
     peaks, results = [], []
@@ -253,9 +253,69 @@ def test_kept_groups_give_way_when_memory_is_short():
             results.append({k: g.grad(*k) for k in e.names})
             del hog, keep
             torch.cuda.empty_cache()
-    assert peaks[1] < peaks[0], peaks               # kept groups did give way
+    assert peaks[1] < peaks[0], peaks               # fewer stashes were held
     ref, got = results
     _assert_same(got, ref, "short of memory")
+
+
+@pytest.mark.parametrize("layers", [1, 2])
+@pytest.mark.parametrize("what", ["group buffer", "parameter"])
+def test_memory_runs_out_while_a_group_is_kept(what, layers):
+    """The device fills up after a group of eight has been kept: the next group buffer, or the temporary of a parameter
+    that is set, takes the place of what is kept, and every gradient has the bits of the same groups given."""
+    import torch
+    n_micro = 16
+    cfg = si.scaled(si.CONFIGS[1], name="runs_out", layers=layers, hidden=3072, heads=24, seq=512, microbatch=4, causal=True,
+                    n_chunks=1, n_micro=n_micro)
+    params = si.make_params(cfg, 0, 0.1, bulk=True)
+    names = [(0, l, n) for l in range(layers) for n in si.PARAM_NAMES]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    shape = (n_micro, cfg.microbatch, cfg.seq, cfg.hidden)
+    x, go = [torch.randn(shape, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2)]
+    z, dx = torch.empty_like(x), torch.empty_like(x)
+    group_buffer, spare = layers * 9 * cfg.T * cfg.hidden * 2, 48 << 20
+    assert min(group_buffer, 4 * cfg.hidden * cfg.F) > 2 * spare
+
+    def run(wgrad_group, fill_at):
+        hog = []
+        with hz.GpuStage(cfg, wgrad_group=wgrad_group, max_inflight=3) as g:
+            g.load_params(params)
+            for mb in range(n_micro + 1):
+                if mb < n_micro:
+                    g.bp.bp_stage_forward(g.h, 0, mb, x[mb], z[mb])
+                if mb == 0:
+                    continue
+                if mb - 1 == fill_at:
+                    # the forwards' stashes first, so that what is short is the buffer (or the temporary) alone
+                    torch.cuda.synchronize()
+                    held = g.bp.bp_stage_held_bytes(g.h)
+                    assert held["group_stash"] >= 8 * g.bp.bp_stage_stash_bytes(g.h), held
+                    rest = torch.empty(spare, dtype=torch.uint8, device="cuda")
+                    size = torch.cuda.mem_get_info()[0]
+                    while size > 20 << 20:          # until nothing larger is to be had (the free size is an estimate)
+                        try:
+                            hog.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+                        except torch.cuda.OutOfMemoryError:
+                            size //= 2
+                    del rest
+                    torch.cuda.empty_cache()
+                    if what == "parameter":
+                        g.bp.bp_stage_set_param(g.h, 0, layers - 1, g.bp.TENSOR_IDS["w1"], params[0][layers - 1]["w1"])
+                g.bp.bp_stage_backward(g.h, 0, mb - 1, go[mb - 1], dx[mb - 1])
+                if mb - 1 == fill_at:
+                    held = g.bp.bp_stage_held_bytes(g.h)
+                    assert held["group_stash"] <= 2 * g.bp.bp_stage_stash_bytes(g.h), held
+            return {k: g.grad(*k) for k in names}
+
+    ref = run(8, -1)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    try:
+        got = run(0, 9)
+    finally:
+        torch.cuda.empty_cache()                    # the others leave
+    _assert_same(got, ref, "ran out")
 
 
 @pytest.mark.parametrize("hidden,dtype", [(64, "f32"), (1024, "bf16"), (4096, "bf16"), (4104, "bf16")])
