@@ -433,14 +433,16 @@ int Stage::set_param(int chunk, int layer, int id, const float* host, size_t n) 
     return BP_OK;
 }
 
-// The device's view of a host range that is pinned from its first to its last byte, else null.
+// The device's view of a host range that lies in one pinned allocation, else null.
 static float* pinned_range(void* host, size_t bytes) {
-    hipPointerAttribute_t first, last;
-    if ((uintptr_t)host % sizeof(float) == 0 && hipPointerGetAttributes(&first, host) == hipSuccess &&
-        first.type == hipMemoryTypeHost && first.devicePointer &&
-        hipPointerGetAttributes(&last, (char*)host + bytes - 1) == hipSuccess && last.type == hipMemoryTypeHost &&
-        (char*)last.devicePointer == (char*)first.devicePointer + bytes - 1)
-        return (float*)first.devicePointer;
+    hipPointerAttribute_t at;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if ((uintptr_t)host % sizeof(float) == 0 && hipPointerGetAttributes(&at, host) == hipSuccess &&
+        at.type == hipMemoryTypeHost && at.devicePointer &&
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)at.devicePointer) == hipSuccess &&
+        (char*)at.devicePointer >= (char*)base && (char*)at.devicePointer + bytes <= (char*)base + size)
+        return (float*)at.devicePointer;
     (void)hipGetLastError();
     return nullptr;
 }

@@ -331,3 +331,18 @@ def test_sums_keep_their_order_when_the_device_fills_up(rec, layers, fill_at):
         _iteration(r, 26, before=before)
         got = r.gradients()
     _same_sums(got, _expect(rec, 26, layers=layers))
+
+
+@pytest.mark.parametrize("pieces,kernel", [([(0, 1024)], True), ([(0, 2048)], True), ([(0, 1023)], False), ([(1, 1023)], False), ([], False),
+                                           ([(0, 256), (768, 256)], False), ([(0, 512), (512, 512)], False)])
+def test_small_reads_write_pinned_memory_only(rec, pieces, kernel):
+    """A vector is written by a kernel only where one pinned allocation holds all of the destination; two pinned pieces
+    with other memory between them (or two that touch) go through the runtime's copy."""
+    with Rec(rec) as r:
+        _iteration(r, 2)
+        host = np.zeros(2048, np.float32)
+        for first, n in pieces:
+            rec.rec_pin(host.ctypes.data + 4 * first, 4 * n)
+        before = rec.rec_launches(b"read_small")
+        assert len(r.terms(0, 0, "bo", host)) == 2
+        assert (rec.rec_launches(b"read_small") > before) == kernel
