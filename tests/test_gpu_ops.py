@@ -288,13 +288,16 @@ def test_attention_ragged_lengths(B, S, heads, d, causal, lens, dtype):
 
 
 # Launches with enough blocks for those of 128 rows (on 256 CUs): an odd number of 64-row tiles, valid lengths around
-# the halves of a tile and of a block, every head width with a kernel of its own and one without, all batch entries
-# together and one after the other; forward alone (256 blocks), forward and dQ alone (causal beyond S 512)
+# the halves of a tile and of a block, every head width with a kernel of its own and one without; causal blocks in the three
+# orders that wide launches have: folded up to 512 of them, heaviest first of all batch entries together up to 1024, one entry
+# after the other above; forward alone (256 blocks), forward and dQ alone (causal beyond S 512)
 @pytest.mark.parametrize("B,S,heads,d,causal,lens", [
     (16, 192, 16, 64, True, None), (16, 192, 16, 64, False, [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 191, 192]),
     (16, 192, 16, 40, False, [192, 96, 33, 64] * 4), (16, 128, 32, 128, True, None), (16, 192, 16, 96, True, None),
     (16, 192, 16, 128, False, [160, 161, 128, 1] * 4), (16, 64, 64, 64, True, None), (16, 192, 16, 80, True, None),
     (5, 320, 48, 24, True, None), (4, 512, 16, 128, False, [512, 479, 480, 200]), (8, 576, 16, 96, True, None),
+    (24, 320, 16, 64, True, None), (18, 192, 32, 40, True, None), (17, 256, 32, 128, True, None), (13, 320, 28, 96, True, None),
+    (8, 192, 48, 64, True, None),
 ])
 def test_attention_blocks_of_128_rows(B, S, heads, d, causal, lens):
     test_attention_fwd_bwd(B, S, heads, d, causal, lens, "bf16")
