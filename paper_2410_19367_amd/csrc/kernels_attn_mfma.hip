@@ -404,39 +404,39 @@ __global__ __launch_bounds__(256 * NT, NT == 1 ? 2 : 1) void attn_fwd_mfma_kerne
     // merge the key sub-ranges: waves 1 .. NSUB-1 of a query group hand (m, l, O^T) to wave 0 through LDS
     float l = halves_sum(lsum), mm = m;
     if constexpr (!WIDE) {
-    __syncthreads();                                    // all tile reads are over; LDS is free
-    constexpr int XO = DT * 16 * 64 + 128;              // [DT*16][64 lanes] + m[64] + l[64]
-    float* xo = (float*)smem + (size_t)qg * (NSUB - 1) * XO;
-    if (sub != 0) {
-        float* mine = xo + (size_t)(sub - 1) * XO;
+        __syncthreads();                                    // all tile reads are over; LDS is free
+        constexpr int XO = DT * 16 * 64 + 128;              // [DT*16][64 lanes] + m[64] + l[64]
+        float* xo = (float*)smem + (size_t)qg * (NSUB - 1) * XO;
+        if (sub != 0) {
+            float* mine = xo + (size_t)(sub - 1) * XO;
+#pragma unroll
+            for (int t2 = 0; t2 < DT; ++t2)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mine[(t2 * 16 + v) * 64 + lane] = ot[t2][v];
+            mine[DT * 16 * 64 + lane] = m;
+            mine[DT * 16 * 64 + 64 + lane] = l;
+        }
+        __syncthreads();
+        if (sub != 0) return;
+        // (m is finite: key 0 lies in this wave's sub-range)
+#pragma unroll
+        for (int j = 0; j < NSUB - 1; ++j) mm = fmaxf(mm, xo[(size_t)j * XO + DT * 16 * 64 + lane]);
+        const float a0 = fast_exp2(m - mm);
+        l *= a0;
 #pragma unroll
         for (int t2 = 0; t2 < DT; ++t2)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) mine[(t2 * 16 + v) * 64 + lane] = ot[t2][v];
-        mine[DT * 16 * 64 + lane] = m;
-        mine[DT * 16 * 64 + 64 + lane] = l;
-    }
-    __syncthreads();
-    if (sub != 0) return;
-    // (m is finite: key 0 lies in this wave's sub-range)
+            for (int v = 0; v < 16; ++v) ot[t2][v] *= a0;
 #pragma unroll
-    for (int j = 0; j < NSUB - 1; ++j) mm = fmaxf(mm, xo[(size_t)j * XO + DT * 16 * 64 + lane]);
-    const float a0 = fast_exp2(m - mm);
-    l *= a0;
+        for (int j = 0; j < NSUB - 1; ++j) {
+            const float* other = xo + (size_t)j * XO;
+            const float aj = fast_exp2(other[DT * 16 * 64 + lane] - mm);
+            l += other[DT * 16 * 64 + 64 + lane] * aj;
 #pragma unroll
-    for (int t2 = 0; t2 < DT; ++t2)
+            for (int t2 = 0; t2 < DT; ++t2)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) ot[t2][v] *= a0;
-#pragma unroll
-    for (int j = 0; j < NSUB - 1; ++j) {
-        const float* other = xo + (size_t)j * XO;
-        const float aj = fast_exp2(other[DT * 16 * 64 + lane] - mm);
-        l += other[DT * 16 * 64 + 64 + lane] * aj;
-#pragma unroll
-        for (int t2 = 0; t2 < DT; ++t2)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) ot[t2][v] += other[(t2 * 16 + v) * 64 + lane] * aj;
-    }
+                for (int v = 0; v < 16; ++v) ot[t2][v] += other[(t2 * 16 + v) * 64 + lane] * aj;
+        }
     }
     if ((RAG || WIDE) && q_lane >= a.S) return;
     const float inv = 1.f / l;
@@ -544,31 +544,31 @@ __device__ __forceinline__ void attn_bwd_dq_block(const AttnArgs& a, float scale
         const char* sv = sk + TILE;
 #pragma unroll
         for (int kh = kh0; kh < (WIDE ? 2 : kh0 + 1); ++kh) {
-        const int kw = k0 + 32 * kh;
-        if ((a.causal && kw > q_wave + 31) || kw >= klen) break;
-        // (a value that is not finite makes dP of the queries that do not attend it NaN)
-        if (RAG && a.causal && kw + 31 > q_wave &&
-            (!rows_finite<D>(sk, 32 * kh, lane, dr) || !rows_finite<D>(sv, 32 * kh, lane, dr))) by_rows = true;
-        f32x16 sacc, dp;
+            const int kw = k0 + 32 * kh;
+            if ((a.causal && kw > q_wave + 31) || kw >= klen) break;
+            // (a value that is not finite makes dP of the queries that do not attend it NaN)
+            if (RAG && a.causal && kw + 31 > q_wave &&
+                (!rows_finite<D>(sk, 32 * kh, lane, dr) || !rows_finite<D>(sv, 32 * kh, lane, dr))) by_rows = true;
+            f32x16 sacc, dp;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { sacc[v] = 0.f; dp[v] = DELTA_FIRST ? -delta : 0.f; }
+            for (int v = 0; v < 16; ++v) { sacc[v] = 0.f; dp[v] = DELTA_FIRST ? -delta : 0.f; }
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            if (16 * s >= dr) continue;
-            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sk, 32 * kh, s, lane), qf[s], sacc, 0, 0, 0);
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sv, 32 * kh, s, lane), dof[s], dp, 0, 0, 0);
-        }
-        if ((a.causal && kw + 31 > q_wave) || kw + 32 > klen) {     // the diagonal, or padded keys: p = 0
-            stay_a_branch();
-            const int last = a.causal ? min(q_lane, klen - 1) : klen - 1;     // last key this query attends
+            for (int s = 0; s < KS; ++s) {
+                if (16 * s >= dr) continue;
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sk, 32 * kh, s, lane), qf[s], sacc, 0, 0, 0);
+                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sv, 32 * kh, s, lane), dof[s], dp, 0, 0, 0);
+            }
+            if ((a.causal && kw + 31 > q_wave) || kw + 32 > klen) {     // the diagonal, or padded keys: p = 0
+                stay_a_branch();
+                const int last = a.causal ? min(q_lane, klen - 1) : klen - 1;     // last key this query attends
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (kw + acc_row(v, h) > last) sacc[v] = -INFINITY;
+            }
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                if (kw + acc_row(v, h) > last) sacc[v] = -INFINITY;
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-            dp[v] = fast_exp2(__builtin_fmaf(sacc[v], c, -lse2)) * (DELTA_FIRST ? dp[v] : dp[v] - delta);   // dS^T
-        contract<D, DT, RAG>(sk, 32 * kh, lane, dr, dp, dq);
+                dp[v] = fast_exp2(__builtin_fmaf(sacc[v], c, -lse2)) * (DELTA_FIRST ? dp[v] : dp[v] - delta);   // dS^T
+            contract<D, DT, RAG>(sk, 32 * kh, lane, dr, dp, dq);
         }
     }
     if (RAG && a.causal && any_wave(by_rows, smem)) {
@@ -578,15 +578,15 @@ __device__ __forceinline__ void attn_bwd_dq_block(const AttnArgs& a, float scale
     if (WIDE && q_lane >= a.S) return;
     float* xo = (float*)smem + (WIDE ? 0 : qg * (DT * 16 * 64));
     if constexpr (!WIDE) {
-    __syncthreads();
-    if (kh0 == 1) {
+        __syncthreads();
+        if (kh0 == 1) {
 #pragma unroll
-        for (int t2 = 0; t2 < DT; ++t2)
+            for (int t2 = 0; t2 < DT; ++t2)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) xo[(t2 * 16 + v) * 64 + lane] = dq[t2][v];
-    }
-    __syncthreads();
-    if (kh0 == 1 || (RAG && q_lane >= a.S)) return;
+                for (int v = 0; v < 16; ++v) xo[(t2 * 16 + v) * 64 + lane] = dq[t2][v];
+        }
+        __syncthreads();
+        if (kh0 == 1 || (RAG && q_lane >= a.S)) return;
     }
     bf16_t* out = (bf16_t*)a.dqkv + ((size_t)b * a.S + q_lane) * ld + head * dr;
 #pragma unroll
@@ -747,65 +747,65 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const AttnArgs& a, float scal
         const char* sdo = sq + TILE;
 #pragma unroll
         for (int qh = qh0; qh < (WIDE ? 2 : qh0 + 1); ++qh) {
-        const int qw = q0 + 32 * qh;                     // first query of this wave's half
-        if (a.causal && qw + 31 < k_wave) continue;      // no query of this half reaches this wave's keys
-        const float* s_nlse = (const float*)(sq + 2 * TILE) + 32 * qh;
-        const float* s_ndlt = (const float*)(sq + 2 * TILE) + 64 + 32 * qh;
-        const bool need_mask = a.causal && qw < k_wave + 31;
-        if (RAG && need_mask && (!rows_finite<D>(sq, 32 * qh, lane, dr) || !rows_finite<D>(sdo, 32 * qh, lane, dr) ||
-                                 !stats_finite(s_nlse, s_ndlt, lane))) by_rows = true;
-        f32x16 sacc, dp;
+            const int qw = q0 + 32 * qh;                     // first query of this wave's half
+            if (a.causal && qw + 31 < k_wave) continue;      // no query of this half reaches this wave's keys
+            const float* s_nlse = (const float*)(sq + 2 * TILE) + 32 * qh;
+            const float* s_ndlt = (const float*)(sq + 2 * TILE) + 64 + 32 * qh;
+            const bool need_mask = a.causal && qw < k_wave + 31;
+            if (RAG && need_mask && (!rows_finite<D>(sq, 32 * qh, lane, dr) || !rows_finite<D>(sdo, 32 * qh, lane, dr) ||
+                                     !stats_finite(s_nlse, s_ndlt, lane))) by_rows = true;
+            f32x16 sacc, dp;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { sacc[v] = 0.f; dp[v] = s_ndlt[acc_row(v, h)]; }
+            for (int v = 0; v < 16; ++v) { sacc[v] = 0.f; dp[v] = s_ndlt[acc_row(v, h)]; }
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            if (16 * s >= dr) continue;
-            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sq, 32 * qh, s, lane), kf[s], sacc, 0, 0, 0);
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sdo, 32 * qh, s, lane), vf[s], dp, 0, 0, 0);
-        }
-        // masked scores become -inf before the exponential (p = 0, dS = 0); both conditions are
-        // wave-uniform branches, taken only on the diagonal tile and in a block with padded keys
-        if (need_mask) {
-            stay_a_branch();
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (k_lane > qw + acc_row(v, h)) sacc[v] = -INFINITY;
-        }
-        if (RAG && q0 + 64 > a.S) {                      // queries past the end: p = 0
-            stay_a_branch();
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (qw + acc_row(v, h) >= a.S) sacc[v] = -INFINITY;
-        }
-        if (some_padded) {
-            stay_a_branch();
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (k_lane >= klen) sacc[v] = -INFINITY;
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            sacc[v] = fast_exp2(__builtin_fmaf(sacc[v], c, s_nlse[acc_row(v, h)]));      // P
-            dp[v] *= sacc[v];                                                            // dS = P (dP - delta)
-        }
-        if constexpr (RAG) {
-            contract<D, DT, true>(sdo, 32 * qh, lane, dr, sacc, dv);
-            contract<D, DT, true>(sq, 32 * qh, lane, dr, dp, dk);
-        } else {
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            const bf16x8 pb = acc_to_b(sacc, s2);
-            const bf16x8 db = acc_to_b(dp, s2);
-#pragma unroll
-            for (int t2 = 0; t2 < DT; ++t2) {
-                if (32 * t2 >= dr) continue;
-                dv[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    frag_cols<D>(sdo, 32 * qh + 16 * s2, t2 * 32, lane), pb, dv[t2], 0, 0, 0);
-                dk[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    frag_cols<D>(sq, 32 * qh + 16 * s2, t2 * 32, lane), db, dk[t2], 0, 0, 0);
+            for (int s = 0; s < KS; ++s) {
+                if (16 * s >= dr) continue;
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sq, 32 * qh, s, lane), kf[s], sacc, 0, 0, 0);
+                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(sdo, 32 * qh, s, lane), vf[s], dp, 0, 0, 0);
             }
-        }
-        }
+            // masked scores become -inf before the exponential (p = 0, dS = 0); both conditions are
+            // wave-uniform branches, taken only on the diagonal tile and in a block with padded keys
+            if (need_mask) {
+                stay_a_branch();
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (k_lane > qw + acc_row(v, h)) sacc[v] = -INFINITY;
+            }
+            if (RAG && q0 + 64 > a.S) {                      // queries past the end: p = 0
+                stay_a_branch();
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (qw + acc_row(v, h) >= a.S) sacc[v] = -INFINITY;
+            }
+            if (some_padded) {
+                stay_a_branch();
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (k_lane >= klen) sacc[v] = -INFINITY;
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                sacc[v] = fast_exp2(__builtin_fmaf(sacc[v], c, s_nlse[acc_row(v, h)]));      // P
+                dp[v] *= sacc[v];                                                            // dS = P (dP - delta)
+            }
+            if constexpr (RAG) {
+                contract<D, DT, true>(sdo, 32 * qh, lane, dr, sacc, dv);
+                contract<D, DT, true>(sq, 32 * qh, lane, dr, dp, dk);
+            } else {
+#pragma unroll
+                for (int s2 = 0; s2 < 2; ++s2) {
+                    const bf16x8 pb = acc_to_b(sacc, s2);
+                    const bf16x8 db = acc_to_b(dp, s2);
+#pragma unroll
+                    for (int t2 = 0; t2 < DT; ++t2) {
+                        if (32 * t2 >= dr) continue;
+                        dv[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            frag_cols<D>(sdo, 32 * qh + 16 * s2, t2 * 32, lane), pb, dv[t2], 0, 0, 0);
+                        dk[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            frag_cols<D>(sq, 32 * qh + 16 * s2, t2 * 32, lane), db, dk[t2], 0, 0, 0);
+                    }
+                }
+            }
         }
         put_delta(t + 1, smem + ((t + 1) & 1) * STAGE);
     }
@@ -816,18 +816,18 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const AttnArgs& a, float scal
     if (WIDE && k_lane >= a.S) return;
     float* xo = (float*)smem + (WIDE ? 0 : kg * (2 * DT * 16 * 64));
     if constexpr (!WIDE) {
-    __syncthreads();
-    if (qh0 == 1) {
+        __syncthreads();
+        if (qh0 == 1) {
 #pragma unroll
-        for (int t2 = 0; t2 < DT; ++t2)
+            for (int t2 = 0; t2 < DT; ++t2)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                xo[(t2 * 16 + v) * 64 + lane] = dk[t2][v];
-                xo[((DT + t2) * 16 + v) * 64 + lane] = dv[t2][v];
-            }
-    }
-    __syncthreads();
-    if (qh0 == 1 || (RAG && k_lane >= a.S)) return;
+                for (int v = 0; v < 16; ++v) {
+                    xo[(t2 * 16 + v) * 64 + lane] = dk[t2][v];
+                    xo[((DT + t2) * 16 + v) * 64 + lane] = dv[t2][v];
+                }
+        }
+        __syncthreads();
+        if (qh0 == 1 || (RAG && k_lane >= a.S)) return;
     }
 #pragma unroll
     for (int t2 = 0; t2 < DT; ++t2)
