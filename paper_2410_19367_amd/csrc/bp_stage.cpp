@@ -448,7 +448,9 @@ static float* pinned_range(void* host, size_t bytes) {
 }
 
 // Up to this size the runtime copies with a kernel of its own, which finds no room beside GEMM blocks that fill a CU;
-// above, over the DMA engines (8.6 us instead of 11.7).  Reads beside the last weight gradients, H 2048, two layers: 28.9 -> 28.1 ms.
+// above, over the DMA engines (8.6 us instead of 11.7; a read of 50 MB takes 892 us and 2048 x 6144 x 16384 GEMMs on another
+// stream 380 us each, side by side or alone.  Under rocprofv3 the runtime copies those with kernels too, and the GEMMs beside
+// them last as long as the copies).  Reads beside the last weight gradients, H 2048, two layers: 28.9 -> 28.1 ms.
 constexpr size_t kSmallRead = 16384;
 
 int Stage::get_grad(int chunk, int layer, int id, float* host, size_t n) {

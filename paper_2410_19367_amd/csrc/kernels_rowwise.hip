@@ -589,8 +589,9 @@ hipError_t launch_cast_from_f32(int dtype, const float* src, void* dst, size_t n
     return hipGetLastError();
 }
 
-// A small tensor into pinned host memory.  16 registers and no LDS, so that its waves fit beside the two waves per
-// SIMD of a 248-register GEMM block: the runtime's copy kernel for small sizes waits until such a block ends.
+// A small tensor into pinned host memory.  Four vector registers a lane (eight allocated) and no LDS, so that its waves fit
+// beside the two waves per SIMD of a 248-register GEMM block: the runtime's copy kernel for small sizes waits until such a
+// block ends.
 __global__ __launch_bounds__(256) void read_small_kernel(const float* __restrict__ src, float* __restrict__ dst, int n) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < n) dst[i] = src[i];
